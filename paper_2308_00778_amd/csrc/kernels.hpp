@@ -15,7 +15,7 @@
 //                   astrometric: segmented reduction over the star key (rows
 //                     are sorted by star), plain stores, no atomics;
 //                   attitude: left to the bucket-order pass (k_att_hist +
-//                     k_att_reduce: rows sorted by the bucket of their
+//                     k_slice_reduce: rows sorted by the bucket of their
 //                     attitude start, per-workgroup FP64 LDS histograms, no
 //                     device atomics) by default; scatter-add with device
 //                     atomics in the ATT instances (attitude mode 0);
@@ -34,6 +34,8 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 namespace avugsr {
 
@@ -185,6 +187,70 @@ __device__ __forceinline__ double max_partials(const double* part, int n, double
     double v = 0.0;
     for (int k = threadIdx.x; k < n; k += kBlock) v = fmax(v, part[k]);
     return block_max(v, lds);
+}
+
+// ------------------------------------------------------- histogram slices
+// The LDS histograms of a section, one slice per workgroup: slice of bucket b's
+// workgroup g at S[((b G + g) K + r) naxes span + axis span + off], column
+// b width + off of an axis of len columns (off < span; with several buckets
+// span > width, so that a column lies in the windows of at most two). gl threads share
+// the G slices of one column.
+struct SliceView {
+    const double* S;
+    int64_t nb, width, span, len, base;
+    int32_t naxes, G, gl;
+    __device__ __host__ int64_t cols() const { return naxes * len; }
+    __device__ __host__ int ct() const { return kBlock / gl; }  // columns per tile
+    __device__ __host__ int64_t tiles() const { return (cols() + ct() - 1) / ct(); }
+};
+
+// Sum of the slices of column `col` (axis-major within the section) and
+// right-hand side r, valid on threads [0, ct): a tile of ct columns, gl threads
+// each taking every gl-th slice, then the gl partial sums in a fixed order.
+// With one thread per column the sum is a serial chain of G loads: 44-59 us
+// for one bucket's 256 slices whatever the columns (n_dfa = 60 ... 10^4);
+// all threads of the block call this.
+template <int K>
+__device__ __forceinline__ double slice_tile_sum(const SliceView& V, bool ok, int64_t col, int r,
+                                                 double* red /* kBlock */)
+{
+    const int ct = V.ct(), g0 = threadIdx.x / ct;
+    double sum = 0.0;
+    if (ok) {
+        int64_t c = col;
+        int ax = 0;
+        while (c >= V.len) {
+            c -= V.len;
+            ++ax;
+        }
+        const int64_t bq = c / V.width, bhi = bq < V.nb - 1 ? bq : V.nb - 1;
+        const int64_t slice = (int64_t)K * V.naxes * V.span;
+        for (int64_t bk = bhi; bk >= 0 && c - bk * V.width < V.span; --bk) {
+            const double* p =
+                V.S + bk * V.G * slice + ((int64_t)r * V.naxes + ax) * V.span + (c - bk * V.width);
+            int g = g0;
+            auto batch = [&](auto n) {  // n loads in flight
+                constexpr int N = decltype(n)::value;
+                for (; g + (N - 1) * V.gl < V.G; g += N * V.gl) {
+                    double a[N];
+#pragma unroll
+                    for (int k = 0; k < N; ++k) a[k] = p[(g + k * V.gl) * slice];
+#pragma unroll
+                    for (int k = 0; k < N; ++k) sum += a[k];
+                }
+            };
+            batch(std::integral_constant<int, 8>());
+            batch(std::integral_constant<int, 4>());
+            batch(std::integral_constant<int, 1>());
+        }
+    }
+    if (V.gl == 1) return sum;
+    __syncthreads();
+    red[threadIdx.x] = sum;
+    __syncthreads();
+    if (g0 == 0)
+        for (int l = 1; l < V.gl; ++l) sum += red[l * ct + threadIdx.x];
+    return sum;
 }
 
 // ------------------------------------------------------------------- aprod 1
@@ -1697,7 +1763,7 @@ __global__ __launch_bounds__(NT) void k_att_dot(int64_t ld, const T* __restrict_
 // g takes blocks g, g + G, ..., so the G streams advance through memory
 // together): an LDS histogram hist[axis][W + 3][KS] gets a * u for the 12
 // coefficients of each of its rows and the KS right-hand sides of one sweep,
-// then is stored as S2[w][r][axis][W + 3]; k_att_reduce adds the slices. The
+// then is stored as S2[w][r][axis][W + 3]; k_slice_reduce adds the slices. The
 // histogram and S2 are FP64 whatever Acc is: gfx950's LDS FP64 atomic add
 // runs at 7.6x the rate of the FP32 one (measured, random addresses over
 // 150 KB: 1550 vs 204 G/s), and the sums are more accurate. U is in bucket
@@ -1832,30 +1898,28 @@ __global__ __launch_bounds__(NT) void k_att_hist(int64_t ld, const T* __restrict
     }
 }
 
-// q_att[(axis n_dfa + c) K + r] += sum of the slices of the (at most two)
-// buckets whose window holds column c.
+// q[(base + axis len + c) K + r] += sum of the slices of every workgroup whose
+// histogram holds column c (SliceView). The slices are read along the columns
+// (consecutive threads, consecutive columns of one right-hand side), by V.gl
+// threads per column; blockIdx.y, gridDim.y split the right-hand sides.
+// Bound by the latency of the slice loads where the columns are few (256
+// slices of 180 ... 30,000 columns: 44-59 -> 4-6 us), by the bytes of the
+// slices otherwise.
 template <typename Acc, int K>
-__global__ __launch_bounds__(kBlock) void k_att_reduce(const double* __restrict__ S2, int64_t nb,
-                                                        int G, int64_t width, int64_t n_dfa,
-                                                        Acc* __restrict__ qatt,
-                                                        const Scalars* __restrict__ sc)
+__global__ __launch_bounds__(kBlock) void k_slice_reduce(SliceView V, Acc* __restrict__ q,
+                                                          const Scalars* __restrict__ sc)
 {
-    const int64_t span = width + kParAxis - 1;
-    const int64_t total = (int64_t)kAxes * n_dfa * K;
-    for (int64_t idx = (int64_t)blockIdx.x * kBlock + threadIdx.x; idx < total;
-         idx += (int64_t)gridDim.x * kBlock) {
-        const int64_t col = idx / K;
-        const int r = (int)(idx - col * K);
-        if (sc != nullptr && (sc[r].done || sc[r].beta_zero)) continue;
-        const int64_t ax = col / n_dfa, c = col - ax * n_dfa;
-        const int64_t bhi = c / width < nb - 1 ? c / width : nb - 1;
-        double sum = 0.0;
-        for (int64_t bk = bhi; bk >= 0 && c - bk * width < span; --bk) {
-            const int64_t off = c - bk * width;
-            for (int g = 0; g < G; ++g)
-                sum += S2[(((bk * G + g) * K + r) * kAxes + ax) * span + off];
+    __shared__ double red[kBlock];
+    Acc* __restrict__ qs = q + V.base * K;
+    const int64_t total = V.cols(), tiles = V.tiles();
+    for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        const int64_t col = tile * V.ct() + (threadIdx.x & (V.ct() - 1));
+        for (int r = blockIdx.y; r < K; r += gridDim.y) {
+            const double sum = slice_tile_sum<K>(V, col < total, col, r, red);
+            if (threadIdx.x >= V.ct() || col >= total) continue;
+            if (sc != nullptr && (sc[r].done || sc[r].beta_zero)) continue;
+            qs[col * K + r] = (Acc)((double)qs[col * K + r] + sum);
         }
-        qatt[idx] = (Acc)((double)qatt[idx] + sum);
     }
 }
 

@@ -520,6 +520,34 @@ void launch_fused(const lsqr_handle* h, Path<Acc>& P, hipStream_t st, bool pre)
         launch_instr_tail<T, Acc, 1, false>(h, P.u, row_map(h), P.q, P.f_hcols, h->sc, st);
 }
 
+// Threads that share the G slices of one column: as many as it takes to fill
+// the chip with the section's columns, 1024 threads a compute unit (few columns
+// are a serial chain of G loads; with many, more threads only add the sum over
+// them: 600,000 columns of 8 slices, 4 threads each, cost 30 us more).
+inline int slice_lanes(const lsqr_handle* h, int64_t cols, int64_t G)
+{
+    int gl = 1;
+    while (gl < 16 && 2 * gl <= G && cols * gl < (int64_t)h->num_cu * 1024) gl *= 2;
+    return gl;
+}
+
+inline SliceView att_slice_view(const lsqr_handle* h, const double* S)
+{
+    return {S, h->nbk, h->bwidth, att_span(h), h->sv.n_dfa, h->sv.att_base, kAxes, h->att_g,
+            slice_lanes(h, kAxes * h->sv.n_dfa, h->att_g)};
+}
+
+template <typename Acc, int K>
+void launch_slice_reduce(const lsqr_handle* h, const SliceView& V, Acc* q, const Scalars* sc,
+                         hipStream_t st)
+{
+    // one block for all right-hand sides of a tile's columns (its K stores share
+    // lines) where the columns alone fill the chip, else a block for each
+    const int64_t grid = std::min<int64_t>(V.tiles(), (int64_t)h->num_cu * 8);
+    hipLaunchKernelGGL((k_slice_reduce<Acc, K>), dim3(grid, grid < h->num_cu * 2 ? K : 1),
+                       dim3(kBlock), 0, st, V, q, sc);
+}
+
 // Attitude part of aprod2 in bucket order: per-workgroup LDS histograms of
 // each bucket's columns, then their sum. ub: the row vector in bucket order,
 // or (gperm = perm) in star order, read through the permutation.
@@ -544,9 +572,7 @@ void launch_att_pass(lsqr_handle* h, const Acc* ub, Acc* q, const Scalars* sc, h
         if (h->pipe) go(N(), Y());
         else go(N(), N());
     }
-    hipLaunchKernelGGL((k_att_reduce<Acc, 1>), dim3(h->nbc), dim3(kBlock), 0, st,
-                       (const double*)h->S2, h->nbk, h->att_g, h->bwidth, h->sv.n_dfa,
-                       q + h->sv.att_base, sc);
+    launch_slice_reduce<Acc, 1>(h, att_slice_view(h, h->S2), q, sc, st);
 }
 
 // q += A^T u for the LSQR loop (and lsqr_aprod2): the constraint rows (u[m..]),
@@ -1223,9 +1249,7 @@ void batch_att_pass(lsqr_handle* h, hipStream_t st)
                            (const int64_t*)h->bstart, h->bwidth, h->att_g, (const Acc*)tb.U,
                            B.S2, B.sc, (const int32_t*)nullptr);
     });
-    hipLaunchKernelGGL((k_att_reduce<Acc, K>), dim3(h->nbc), dim3(kBlock), 0, st,
-                       (const double*)B.S2, h->nbk, h->att_g, h->bwidth, h->sv.n_dfa,
-                       tb.Q + h->sv.att_base * K, B.sc);
+    launch_slice_reduce<Acc, K>(h, att_slice_view(h, B.S2), tb.Q, B.sc, st);
 }
 
 template <typename T, typename Acc, int K>
