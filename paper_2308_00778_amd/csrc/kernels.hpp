@@ -253,6 +253,200 @@ __device__ __forceinline__ double slice_tile_sum(const SliceView& V, bool ok, in
     return sum;
 }
 
+// Runs f(section, column, sum) for every column of the two slice sections, on
+// the thread that holds its sum, and plain(j) for the other columns, tile by
+// tile over the grid (the slice tiles first: they take longest). plain columns:
+// [0, n) without the sections (att before ins).
+template <typename F, typename P>
+__device__ __forceinline__ void for_columns(const SliceView& att, const SliceView& ins, int64_t n,
+                                            double* red /* kBlock */, F&& slice, P&& plain)
+{
+    const int64_t na = att.tiles(), ni = na + ins.tiles();
+    const int64_t np = n - att.cols() - ins.cols();
+    const int64_t nt = ni + (np + kBlock - 1) / kBlock;
+    for (int64_t tile = blockIdx.x; tile < nt; tile += gridDim.x) {
+        if (tile < ni) {
+            const bool first = tile < na;
+            const SliceView& V = first ? att : ins;
+            const int64_t col =
+                (first ? tile : tile - na) * V.ct() + (threadIdx.x & (V.ct() - 1));
+            const bool ok = col < V.cols();
+            const double sum = slice_tile_sum<1>(V, ok, col, 0, red);
+            if (ok && threadIdx.x < V.ct()) slice(V.base + col, sum);
+        } else {
+            int64_t j = (tile - ni) * kBlock + threadIdx.x;
+            if (j >= np) continue;
+            if (j >= att.base) j += att.cols();
+            if (j >= ins.base) j += ins.cols();
+            plain(j);
+        }
+    }
+}
+
+// Partials of the global columns: gpart[blk stride + g], blk < nblk, g < ng.
+struct GlobView {
+    const void* part;
+    int64_t base;
+    int32_t nblk, stride, ng;
+};
+
+// f(column, sum of its partials) on thread 0 of the last block.
+template <typename Acc, typename F>
+__device__ __forceinline__ void for_globals(const GlobView& G, double* red, F&& f)
+{
+    if (blockIdx.x != gridDim.x - 1) return;
+    const Acc* part = static_cast<const Acc*>(G.part);
+    for (int g = 0; g < G.ng; ++g) {
+        double v = 0.0;
+        for (int k = threadIdx.x; k < G.nblk; k += kBlock)
+            v += (double)part[(int64_t)k * G.stride + g];
+        const double r = block_sum(v, red);
+        if (threadIdx.x == 0) f(G.base + g, r);
+    }
+}
+
+// q += the slices' sums and the global columns' partials (the last step of an
+// aprod2 outside the iterations, where k_col_a does the same on the way).
+template <typename Acc>
+__global__ __launch_bounds__(kBlock) void k_section_sums(SliceView att, SliceView ins, GlobView glob,
+                                                          Acc* __restrict__ q,
+                                                          const Scalars* __restrict__ sc)
+{
+    __shared__ double red[kBlock];
+    if (sc != nullptr && (sc->done || sc->beta_zero)) return;
+    auto add = [q](int64_t j, double sum) { q[j] = (Acc)((double)q[j] + sum); };
+    for_columns(att, ins, att.cols() + ins.cols(), red, add, [](int64_t) {});
+    for_globals<Acc>(glob, red, add);
+}
+
+// ------------------------------------------------------------ stopping tests
+// ddnorm, xnorm, acond and the stopping tests of Paige & Saunders: what one
+// iteration adds to the state s. (The state itself is not copied into
+// registers: it would go through scratch.)
+struct StopUpdate {
+    double ddnorm, xnorm, acond;
+    int32_t itn, istop, done;
+};
+
+__device__ __forceinline__ StopUpdate stop_update(const Scalars& s, double dd, double xx)
+{
+    StopUpdate o;
+    const double ddnorm = s.ddnorm + dd;
+    const double xnorm = sqrt(xx);
+    const double anorm = s.anorm;
+    const double acond = anorm * sqrt(ddnorm);
+    const double rnorm = s.rnorm, arnorm = s.arnorm, bnorm = s.bnorm;
+    o.ddnorm = ddnorm;
+    o.xnorm = xnorm;
+    o.acond = acond;
+    o.itn = s.itn + 1;
+
+    const double test1 = rnorm / bnorm;
+    const double test2 = (anorm * rnorm) > 0.0 ? arnorm / (anorm * rnorm) : 0.0;
+    const double test3 = acond > 0.0 ? 1.0 / acond : 0.0;
+    const double t1 = test1 / (1.0 + anorm * xnorm / bnorm);
+    const double rtol = s.btol + s.atol * anorm * xnorm / bnorm;
+    int32_t istop = 0;
+    if (o.itn >= s.itn_limit) istop = 7;
+    if (s.tests) {
+        if (1.0 + test3 <= 1.0) istop = 6;
+        if (1.0 + test2 <= 1.0) istop = 5;
+        if (1.0 + t1 <= 1.0) istop = 4;
+        if (test3 <= s.ctol) istop = 3;
+        if (test2 <= s.atol) istop = 2;
+        if (test1 <= rtol) istop = 1;
+    }
+    // Relative form of the normal-equation test, for correction problems whose
+    // residual is dominated by the irreducible least-squares residual.
+    if (s.rel_ar > 0.0 && arnorm <= s.rel_ar * s.arnorm0) istop = 2;
+    o.istop = istop;
+    o.done = istop != 0 ? 1 : s.done;
+    return o;
+}
+
+// *to = *from by the first threads of a block (the caller synchronises).
+__device__ __forceinline__ void copy_state(Scalars* to, const Scalars* from)
+{
+    static_assert(sizeof(Scalars) % 4 == 0 && sizeof(Scalars) / 4 <= kBlock, "one word a thread");
+    if (threadIdx.x < sizeof(Scalars) / 4)
+        reinterpret_cast<uint32_t*>(to)[threadIdx.x] =
+            reinterpret_cast<const uint32_t*>(from)[threadIdx.x];
+}
+
+// The stopping tests of the previous iteration, made by the first row pass of
+// the next one. A single-workgroup kernel for them costs 4-5 us and a launch
+// gap per iteration; here every workgroup sums the same partials in the same
+// order beside staging its LDS, and workgroup 0 stores the state. The state is
+// read from B (written by k_col_b) and stored to A, which no workgroup of this
+// pass reads, so the order of the workgroups does not matter; the kernels that
+// follow read A. B null: nothing pending, A is current.
+struct Gate {
+    const Scalars* B;
+    Scalars* A;
+    const double* dd;
+    const double* xx;
+    int32_t n;
+};
+
+// Sum of n partials by the first kBlock threads of a block of NT, in the order
+// of sum_partials; valid on thread 0. lds >= kWavesPerBlock.
+template <int NT>
+__device__ __forceinline__ double sum_partials_nt(const double* part, int n, double* lds)
+{
+    double v = 0.0;
+    if (threadIdx.x < kBlock)
+        for (int k = threadIdx.x; k < n; k += kBlock) v += part[k];
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_down(v, off);
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    __syncthreads();
+    if (lane == 0 && w < kWavesPerBlock) lds[w] = v;
+    __syncthreads();
+    double r = 0.0;
+    if (threadIdx.x == 0)
+        for (int k = 0; k < kWavesPerBlock; ++k) r += lds[k];
+    return r;
+}
+
+// True while the solve runs (uniform over the block); coef: coef_u of the step.
+template <int NT>
+__device__ __forceinline__ bool gate_open(const Gate& G, double* red, int32_t* flag, double* coef)
+{
+    if (G.B == nullptr) {
+        *coef = G.A->coef_u;
+        return G.A->done == 0;
+    }
+    if (G.B->done) return false;  // A was final already
+    *coef = G.B->coef_u;
+    if (blockIdx.x == 0) copy_state(G.A, G.B);  // before the barriers of the sums
+    const double dd = sum_partials_nt<NT>(G.dd, G.n, red);
+    const double xx = sum_partials_nt<NT>(G.xx, G.n, red);
+    if (threadIdx.x == 0) {
+        const StopUpdate o = stop_update(*G.B, dd, xx);
+        *flag = o.done;
+        if (blockIdx.x == 0) {
+            G.A->ddnorm = o.ddnorm;
+            G.A->xnorm = o.xnorm;
+            G.A->acond = o.acond;
+            G.A->itn = o.itn;
+            G.A->istop = o.istop;
+            G.A->done = o.done;
+        }
+    }
+    __syncthreads();
+    return *flag == 0;
+}
+
+// The same as a kernel of its own: after the last iteration of a launch, and
+// where the next iteration's first pass has no gate.
+__global__ __launch_bounds__(kBlock) void k_scalar_stop(Gate gate)
+{
+    __shared__ double red[kWavesPerBlock];
+    __shared__ int32_t flag;
+    double coef;
+    (void)gate_open<kBlock>(gate, red, &flag, &coef);
+}
+
 // ------------------------------------------------------------------- aprod 1
 // Eq. (2) for one row: sum over the 24 coefficients in section order.
 // xi: the instrumental slice of x (x + instr_base, or its copy in LDS).
@@ -645,74 +839,115 @@ __global__ __launch_bounds__(NT) void k_aprod2(SysView s, const VU* __restrict__
 // ------------------------------------------------------ fused iteration pass
 // One sweep over the rows in star order doing both operator products of an
 // LSQR step (Eq. 2 and Eq. 3). Because u~_{i+1} = Abar v_i - (alpha_i/beta_i) u~_i
-// is row-local, each row's new value is known as soon as the row's 24
+// is row-local, each row's new value is known as soon as the row's
 // coefficients are in registers, and the same registers then feed
 // A^T u~_{i+1} for the astrometric (per-star segments), instrumental (LDS
 // histogram) and global (per-workgroup partial) columns. beta_{i+1} = ||u~||
 // is applied afterwards by the column kernel (v~ = p .* A^T u~ / beta - beta v),
 // so A is read once per iteration for these sections; the attitude columns
-// are left to the row-reordered pass, which reads u~_{i+1}.
-//   x: vp = p .* v (Acc), x3: its interleaved attitude section (kAttX3),
+// are left to the bucket-order pass, which reads u~_{i+1}, except in kAttAll.
+//   x: vp = p .* v (Acc), x3: its interleaved attitude section,
 //   u: u~ [m], overwritten (row i at u[inv[i]], or u[i] without inv),
 //   part[blockIdx.x]: FP64 sum of squares of the
 //   stored u~, q: A^T u~ accumulator (astro, instr, glob sections),
-//   gpart[blockIdx.x]: global-column partial, wb: star-aligned wave ranges.
+//   gpart[blockIdx.x]: global-column partials, wb: star-aligned wave ranges.
 // Dynamic LDS: the FP64 histogram of instrumental columns [0, hcols) (see
-// k_att_hist; columns from hcols on are left to k_instr_tail) and, after it,
-// the instrumental slice of x (LDSX, n_instr_cols Acc).
+// k_att_hist; columns from hcols on are left to k_instr_tail), in kAttAll that
+// of the attitude columns ([axis][n_dfa]), then the instrumental slice of x
+// (LDSX, n_instr_cols Acc) and the interleaved attitude section (WIN).
 // AM, the attitude part of the dot product: kAttX reads three 4-value windows
 // of x, kAttX3 one 12-value window of x3, kAttPre none: k_att_dot has already
 // replaced u~ by (attitude part of A vp) - coef u~, so the row adds that;
 // kAttGather: k_att_dot has written the attitude part of every row to datt in
 // bucket order, the row reads it at datt[inv[i]] and keeps u~ in star order
 // (u[i]), so that u~ is read and written sequentially and the only permuted
-// access is that read.
+// access is that read. kAttAll: the attitude values come from x3 (WIN: its copy
+// in LDS) and the attitude columns are scattered into their LDS histogram too,
+// so the iteration reads A once, in one pass.
 // us (optional): a star-order copy of the new u~ (us[i]), written
 // sequentially for the instrumental tail passes that follow, which then read
 // it without the permutation.
-enum { kAttX = 0, kAttX3 = 1, kAttPre = 2, kAttGather = 3 };
-template <typename T, typename Acc, int NT, bool LDSX, int AM, bool CIDX>
+// satt (kAttAll), sins (optional): the workgroup's histograms are stored as
+// slices there (SliceView) instead of being added to q with device atomics.
+// GEN > 0: section sizes from the system view (general layouts with at most GEN
+// global columns: five of them cost 20 registers more); the loads stay unrolled,
+// each under a uniform test. A2: Eq. (3) alone, u unchanged.
+enum { kAttX = 0, kAttX3 = 1, kAttPre = 2, kAttGather = 3, kAttAll = 4 };
+constexpr int kGlobMax = 5;  // global columns of a general layout
+
+template <typename T, typename Acc, int NT, bool LDSX, int AM, bool CIDX, int GEN = 0,
+          bool WIN = false, bool A2 = false>
 __global__ __launch_bounds__(NT) void k_fused(SysView s, const Acc* __restrict__ x,
                                                const Acc* __restrict__ x3, Acc* __restrict__ u,
                                                Acc* __restrict__ q, const int64_t* __restrict__ wb,
                                                Acc* __restrict__ gpart, double* __restrict__ part,
-                                               int64_t hcols, const Scalars* __restrict__ sc,
+                                               int64_t hcols, Gate gate,
                                                const int32_t* __restrict__ inv,
                                                const Acc* __restrict__ datt = nullptr,
-                                               Acc* __restrict__ us = nullptr)
+                                               Acc* __restrict__ us = nullptr,
+                                               double* __restrict__ satt = nullptr,
+                                               double* __restrict__ sins = nullptr)
 {
+    constexpr bool kNoAtt = AM == kAttPre || AM == kAttGather;
+    constexpr int kAtt = kAxes * kParAxis;
+    constexpr int NG = GEN ? GEN : 1;
+    constexpr int W = NT / kWave;
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    __shared__ Acc gred[NT / kWave];
-    __shared__ double sred[NT / kWave];
-    if (sc->done) return;
+    __shared__ Acc gred[NG * W];
+    __shared__ double sred[W];
+    __shared__ int32_t gflag;
+    const int na = GEN ? s.na : kAstro, ni = GEN ? s.ni : kInstr, ng = GEN ? s.ng : 1;
+    const bool att = !kNoAtt && (!GEN || s.natt > 0);
+    const int oatt = GEN ? s.off_att : kOffAtt, oins = GEN ? s.off_instr : kOffInstr,
+              oglob = GEN ? s.off_glob : kOffGlob;
 
     const T* __restrict__ val = static_cast<const T*>(s.val);
     const int64_t m = s.m;
-    const int64_t ninst = s.n_instr_cols;
+    const int64_t ninst = GEN && ni == 0 ? 0 : s.n_instr_cols;
+    const int64_t hatt = AM == kAttAll && att ? kAxes * s.n_dfa : 0;
     double* hist = reinterpret_cast<double*>(smem_raw);
-    const Acc* xi = x + s.instr_base;
-    for (int64_t j = threadIdx.x; j < hcols; j += NT) hist[j] = 0.0;
-    if (LDSX) {
-        const int64_t off = (hcols * 8 + 15) & ~(int64_t)15;
+    double* ahist = hist + hcols;
+    const Acc* xi = A2 ? nullptr : x + s.instr_base;
+    const Acc* xw = x3;
+    for (int64_t j = threadIdx.x; j < hcols + hatt; j += NT) hist[j] = 0.0;
+    if (LDSX && !A2) {
+        const int64_t off = ((hcols + hatt) * 8 + 15) & ~(int64_t)15;
         Acc* xl = reinterpret_cast<Acc*>(smem_raw + off);
         for (int64_t j = threadIdx.x; j < ninst; j += NT) xl[j] = xi[j];
         xi = xl;
+        if (WIN) {
+            Acc* wl = xl + ninst;
+            for (int64_t j = threadIdx.x; j < hatt; j += NT) wl[j] = x3[j];
+            xw = wl;
+        }
+    }
+    Acc coef = (Acc)0;
+    if (!A2) {
+        double cf = 0.0;
+        if (!gate_open<NT>(gate, sred, &gflag, &cf)) return;
+        coef = (Acc)cf;
+    } else if (gate.A != nullptr && (gate.A->done || gate.A->beta_zero)) {
+        return;
     }
     __syncthreads();
 
-    const Acc coef = (Acc)sc->coef_u;
-    const Acc xg = x[s.glob_base];
+    Acc xg[NG];
+#pragma unroll
+    for (int g = 0; g < NG; ++g) xg[g] = (!A2 && g < ng) ? x[s.glob_base + g] : (Acc)0;
     const int lane = threadIdx.x & (kWave - 1);
-    const int64_t wave = (int64_t)blockIdx.x * (NT / kWave) + threadIdx.x / kWave;
+    const int64_t wave = (int64_t)blockIdx.x * W + threadIdx.x / kWave;
     const int64_t rb = wb[wave], re = wb[wave + 1];
     Acc* __restrict__ qins = q + s.instr_base;
 
     double ssq = 0.0;
-    Acc gsum = (Acc)0;
-    SegAcc<Acc, kAstro> seg;
-    auto astro_emit = [q](int64_t star, const Acc (&tot)[kAstro]) {
+    Acc gsum[NG];
 #pragma unroll
-        for (int j = 0; j < kAstro; ++j) q[kAstro * star + j] += tot[j];
+    for (int g = 0; g < NG; ++g) gsum[g] = (Acc)0;
+    SegAcc<Acc, kAstro> seg;
+    auto astro_emit = [=](int64_t star, const Acc (&tot)[kAstro]) {
+#pragma unroll
+        for (int j = 0; j < kAstro; ++j)
+            if (!GEN || j < na) q[(int64_t)na * star + j] += tot[j];
     };
 
     // 64-row aligned chunks, as in k_aprod2; lanes outside [rb, re) compute on
@@ -723,89 +958,129 @@ __global__ __launch_bounds__(NT) void k_fused(SysView s, const Acc* __restrict__
         const int64_t ic = i < rb ? rb : (i < re ? i : re - 1);
         const int64_t stc = star_of<CIDX>(s, ic);
         const int64_t st = i < re ? stc : kNoStar;
-        constexpr bool kNoAtt = AM == kAttPre || AM == kAttGather;
-        const int64_t t = kNoAtt ? 0 : ldnt(&s.att[ic]);
-        T a[kPar];
-#pragma unroll
-        for (int c = 0; c < kPar; ++c)
-            if (!kNoAtt || c < kOffAtt || c >= kOffInstr) a[c] = ldnt(&val[c * m + ic]);
+        const int64_t t = att ? ldnt(&s.att[ic]) : 0;
+        T aa[kAstro], at[kAtt], ai[kInstr], ag[NG];
         int32_t ix[kInstr];
 #pragma unroll
-        for (int j = 0; j < kInstr; ++j) ix[j] = instr_of<CIDX>(s, j, ic);
+        for (int j = 0; j < kAstro; ++j)
+            aa[j] = !GEN || j < na ? ldnt(&val[j * m + ic]) : (T)0;
+        if (!kNoAtt) {
+            if (att) {
+#pragma unroll
+                for (int c = 0; c < kAtt; ++c) at[c] = ldnt(&val[(oatt + c) * m + ic]);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < kInstr; ++j)
+            ai[j] = !GEN || j < ni ? ldnt(&val[(oins + j) * m + ic]) : (T)0;
+#pragma unroll
+        for (int g = 0; g < NG; ++g)
+            ag[g] = !GEN || g < ng ? ldnt(&val[(oglob + g) * m + ic]) : (T)0;
+#pragma unroll
+        for (int j = 0; j < kInstr; ++j) ix[j] = !GEN || j < ni ? instr_of<CIDX>(s, j, ic) : 0;
         const int64_t pu = (AM != kAttGather && inv) ? (int64_t)ldnt(&inv[ic]) : ic;
         const Acc dg = AM == kAttGather ? datt[ldnt(&inv[ic])] : (Acc)0;
         const Acc uo = u[pu];
 
-        // Eq. (2): the row's dot product with vp, in section order
         Acc d = (Acc)0;
-        const Acc* xa = x + kAstro * stc;
+        if (A2) {
+            d = ok ? uo : (Acc)0;
+        } else {
+            // Eq. (2): the row's dot product with vp, in section order
+            const Acc* xa = x + na * stc;
 #pragma unroll
-        for (int j = 0; j < kAstro; ++j) d += (Acc)a[j] * xa[j];
-        if (!kNoAtt) {
+            for (int j = 0; j < kAstro; ++j)
+                if (!GEN || j < na) d += (Acc)aa[j] * xa[j];
+            if (!kNoAtt) {
+                if (att) {
 #pragma unroll
-            for (int ax = 0; ax < kAxes; ++ax) {
+                    for (int ax = 0; ax < kAxes; ++ax) {
 #pragma unroll
-                for (int qq = 0; qq < kParAxis; ++qq) {
-                    const Acc xv = AM == kAttX3 ? x3[kAxes * (t + qq) + ax]
-                                                : x[s.att_base + ax * s.n_dfa + t + qq];
-                    d += (Acc)a[kOffAtt + ax * kParAxis + qq] * xv;
+                        for (int qq = 0; qq < kParAxis; ++qq) {
+                            const Acc xv = AM == kAttX ? x[s.att_base + ax * s.n_dfa + t + qq]
+                                                       : xw[kAxes * (t + qq) + ax];
+                            d += (Acc)at[ax * kParAxis + qq] * xv;
+                        }
+                    }
                 }
             }
-        }
 #pragma unroll
-        for (int j = 0; j < kInstr; ++j) d += (Acc)a[kOffInstr + j] * xi[ix[j]];
-        d += (Acc)a[kOffGlob] * xg;
-        if (AM == kAttPre)
-            d += uo;
-        else if (AM == kAttGather)
-            d += dg - coef * uo;
-        else
-            d -= coef * uo;
-        if (ok) u[pu] = d;
-        if (ok && us) us[ic] = d;
-        if (!ok) d = (Acc)0;
-        ssq += (double)d * (double)d;
+            for (int j = 0; j < kInstr; ++j)
+                if (!GEN || j < ni) d += (Acc)ai[j] * xi[ix[j]];
+#pragma unroll
+            for (int g = 0; g < NG; ++g)
+                if (!GEN || g < ng) d += (Acc)ag[g] * xg[g];
+            if (AM == kAttPre)
+                d += uo;
+            else if (AM == kAttGather)
+                d += dg - coef * uo;
+            else
+                d -= coef * uo;
+            if (ok) u[pu] = d;
+            if (ok && us) us[ic] = d;
+            if (!ok) d = (Acc)0;
+            ssq += (double)d * (double)d;
+        }
 
-        // Eq. (3) with the new value, attitude columns excluded
+        // Eq. (3) with the new value
         if (ok) {
+            if (AM == kAttAll) {
+                if (att) {
+#pragma unroll
+                    for (int ax = 0; ax < kAxes; ++ax)
+#pragma unroll
+                        for (int qq = 0; qq < kParAxis; ++qq)
+                            atomicAdd(&ahist[ax * s.n_dfa + t + qq],
+                                      (double)((Acc)at[ax * kParAxis + qq] * d));
+                }
+            }
 #pragma unroll
             for (int j = 0; j < kInstr; ++j) {
-                if (ix[j] < hcols) atomicAdd(&hist[ix[j]], (double)((Acc)a[kOffInstr + j] * d));
+                if ((!GEN || j < ni) && ix[j] < hcols)
+                    atomicAdd(&hist[ix[j]], (double)((Acc)ai[j] * d));
             }
         }
-        gsum += (Acc)a[kOffGlob] * d;
+#pragma unroll
+        for (int g = 0; g < NG; ++g) gsum[g] += (Acc)ag[g] * d;
         Acc pa[kAstro];
 #pragma unroll
-        for (int j = 0; j < kAstro; ++j) pa[j] = (Acc)a[j] * d;
-        seg_chunk(seg, st, pa, lane, astro_emit);
+        for (int j = 0; j < kAstro; ++j) pa[j] = (Acc)aa[j] * d;
+        if (!GEN || na > 0) seg_chunk(seg, st, pa, lane, astro_emit);
     }
     seg_finish(seg, lane, astro_emit);
 
-    // per-workgroup partials: global column and ||u~||^2
+    // per-workgroup partials: global columns and ||u~||^2
 #pragma unroll
     for (int off = kWave / 2; off > 0; off >>= 1) {
-        gsum += __shfl_down(gsum, off);
-        ssq += __shfl_down(ssq, off);
+#pragma unroll
+        for (int g = 0; g < NG; ++g) gsum[g] += __shfl_down(gsum[g], off);
+        if (!A2) ssq += __shfl_down(ssq, off);
     }
     if (lane == 0) {
-        gred[threadIdx.x / kWave] = gsum;
+#pragma unroll
+        for (int g = 0; g < NG; ++g) gred[g * W + threadIdx.x / kWave] = gsum[g];
         sred[threadIdx.x / kWave] = ssq;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (threadIdx.x < NG) {
         Acc g = (Acc)0;
+        for (int k = 0; k < W; ++k) g += gred[threadIdx.x * W + k];
+        gpart[(int64_t)blockIdx.x * NG + threadIdx.x] = g;
+    }
+    if (!A2 && threadIdx.x == 0) {
         double r = 0.0;
-        for (int k = 0; k < NT / kWave; ++k) {
-            g += gred[k];
-            r += sred[k];
-        }
-        gpart[blockIdx.x] = g;
+        for (int k = 0; k < W; ++k) r += sred[k];
         part[blockIdx.x] = r;
     }
     for (int64_t j = threadIdx.x; j < hcols; j += NT) {
         const double v = hist[j];
-        if (v != 0.0) atomicAdd(&qins[j], (Acc)v);
+        if (sins)
+            sins[blockIdx.x * hcols + j] = v;
+        else if (v != 0.0)
+            atomicAdd(&qins[j], (Acc)v);
     }
+    if (AM == kAttAll)
+        for (int64_t j = threadIdx.x; j < hatt; j += NT) satt[blockIdx.x * hatt + j] = ahist[j];
 }
 
 // Instrumental columns [c0, c1) of Eq. (3) (or of the squared column norms,
@@ -886,7 +1161,6 @@ __global__ __launch_bounds__(NT) void k_instr_tail(SysView s, const Acc* __restr
 // section sizes and value-row offsets come from the system view at run time,
 // aprod1 and aprod2 run as separate passes, and the attitude columns go
 // through the bucket-order pass (or device atomics) as in the full layout.
-constexpr int kGlobMax = 5;
 
 // Eq. (2) for a general layout; modes, y placement (inv) and part as k_aprod1.
 template <typename T, typename Acc, typename VX, typename VY, int MODE>
@@ -1028,22 +1302,6 @@ __global__ __launch_bounds__(kBlock) void k_gen_aprod2(SysView s, const VU* __re
     }
 }
 
-// q[glob_base + g] += sum over workgroups of gpart[blk * kGlobMax + g], g < ng.
-template <typename Acc>
-__global__ __launch_bounds__(kBlock) void k_gen_glob_sum(const Acc* __restrict__ gpart, int nblk,
-                                                          int ng, Acc* __restrict__ qglob,
-                                                          const Scalars* __restrict__ sc)
-{
-    __shared__ double red[kWavesPerBlock];
-    if (sc != nullptr && (sc->done || sc->beta_zero)) return;
-    for (int g = 0; g < ng; ++g) {
-        double v = 0.0;
-        for (int k = threadIdx.x; k < nblk; k += kBlock) v += (double)gpart[(int64_t)k * kGlobMax + g];
-        const double r = block_sum(v, red);
-        if (threadIdx.x == 0) qglob[g] = (Acc)((double)qglob[g] + r);
-    }
-}
-
 // --------------------------------------------------------- constraint rows
 // Equations appended below the observation rows (Sect. 2): a few long sparse
 // rows, in CSR form with FP64 values. One workgroup per row (grid-stride
@@ -1083,6 +1341,42 @@ __global__ __launch_bounds__(kBlock) void k_con_aprod1(int64_t nc,
                 rowssq[r] = (double)nv * (double)nv;
             }
         }
+    }
+}
+
+// Both products of an LSQR step on the constraint rows: u_r = dot_r - coef_u u_r
+// (as k_con_aprod1), rowssq[r] = u_r^2, and q[col[e]] += val[e] u_r with the
+// new value, by the workgroup that holds the row (its entries are read again
+// from L2).
+template <typename Acc>
+__global__ __launch_bounds__(kBlock) void k_con_step(int64_t nc, const int64_t* __restrict__ rowptr,
+                                                      const int64_t* __restrict__ col,
+                                                      const double* __restrict__ val,
+                                                      const Acc* __restrict__ x,
+                                                      Acc* __restrict__ u, Acc* __restrict__ q,
+                                                      const Scalars* __restrict__ sc,
+                                                      double* __restrict__ rowssq)
+{
+    __shared__ double red[kWavesPerBlock];
+    __shared__ Acc nu;
+    if (sc->done) return;
+    const Acc coef = (Acc)sc->coef_u;
+    for (int64_t r = blockIdx.x; r < nc; r += gridDim.x) {
+        const int64_t e0 = rowptr[r], e1 = rowptr[r + 1];
+        Acc d = (Acc)0;
+        for (int64_t e = e0 + threadIdx.x; e < e1; e += kBlock) d += (Acc)val[e] * (Acc)x[col[e]];
+        const double t = block_sum((double)d, red);
+        if (threadIdx.x == 0) {
+            const Acc nv = (Acc)((Acc)t - coef * u[r]);
+            u[r] = nv;
+            rowssq[r] = (double)nv * (double)nv;
+            nu = nv;
+        }
+        __syncthreads();
+        const Acc ur = nu;
+        for (int64_t e = e0 + threadIdx.x; e < e1; e += kBlock)
+            atomicAdd(&q[col[e]], (Acc)val[e] * ur);
+        __syncthreads();  // nu is rewritten for the next row
     }
 }
 
@@ -1147,69 +1441,154 @@ __global__ __launch_bounds__(kBlock) void k_validate_con_cols(int64_t nnz,
     if (bad) atomicOr(flag, bad);
 }
 
-// Second stage of the global-column reduction: q[glob] += sum of partials.
-template <typename Acc>
-__global__ __launch_bounds__(kBlock) void k_glob_sum(const Acc* __restrict__ gpart, int nblk,
-                                                      Acc* __restrict__ qglob,
-                                                      const Scalars* __restrict__ sc)
-{
-    __shared__ double red[kWavesPerBlock];
-    if (sc != nullptr && (sc->done || sc->beta_zero)) return;
-    double v = 0.0;
-    for (int k = threadIdx.x; k < nblk; k += kBlock) v += (double)gpart[k];
-    const double r = block_sum(v, red);
-    if (threadIdx.x == 0) *qglob = (Acc)((double)*qglob + r);
-}
-
 // ---------------------------------------------------------- column vectors
-// v~ = p .* q / beta - beta v ; q = 0 ; alpha^2 partials.
+// Norm of the new row vector from its partials (part[0, npart), and the squares
+// con[0, ncon) of its constraint entries); npart = 0: beta is in the state.
+struct BetaView {
+    const double* part;
+    const double* con;
+    int32_t npart, ncon;
+};
+
+// beta = ||u~||, v~ = p .* q / beta - beta v ; q = 0 ; alpha^2 partials. The
+// slices and partials of the sections that the row passes left in their
+// histograms are added to q on the way, so that neither they nor beta take a
+// launch of their own. Every workgroup sums the same partials of beta in the
+// same order; workgroup 0 stores beta, anorm and beta_zero, which the others
+// do not read.
 template <typename Acc>
 __global__ __launch_bounds__(kBlock) void k_col_a(int64_t n, const double* __restrict__ p,
                                                    Acc* __restrict__ q, double* __restrict__ v,
-                                                   const Scalars* __restrict__ sc,
+                                                   Scalars* __restrict__ sc, BetaView bv,
+                                                   SliceView att, SliceView ins, GlobView glob,
                                                    double* __restrict__ part)
 {
-    __shared__ double red[kWavesPerBlock];
-    if (sc->done || sc->beta_zero) return;
-    const double beta = sc->beta;
+    __shared__ double red[kBlock];
+    __shared__ double bsh;
+    if (sc->done) return;
+    if (bv.npart > 0) {
+        double t = 0.0;
+        for (int k = threadIdx.x; k < bv.npart; k += kBlock) t += bv.part[k];
+        for (int k = threadIdx.x; k < bv.ncon; k += kBlock) t += bv.con[k];
+        const double ssq = block_sum(t, red);
+        if (threadIdx.x == 0) {
+            const double b = sqrt(ssq);
+            bsh = b;
+            if (blockIdx.x == 0) {
+                sc->beta = b;
+                if (b > 0.0) {
+                    const double a = sc->alpha;
+                    sc->anorm = sqrt(sc->anorm * sc->anorm + a * a + b * b);
+                    sc->beta_zero = 0;
+                } else {
+                    sc->beta_zero = 1;
+                }
+            }
+        }
+    } else if (threadIdx.x == 0) {
+        bsh = sc->beta;
+    }
+    __syncthreads();
+    const double beta = bsh;
+    if (!(beta > 0.0)) return;
     const double ib = 1.0 / beta;
     double ssq = 0.0;
-    for (int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x; j < n;
-         j += (int64_t)gridDim.x * kBlock) {
-        const double qj = (double)q[j];
+    auto column = [&](int64_t j, double sum) {
+        const double qj = (double)q[j] + sum;
         q[j] = (Acc)0;
         const double vt = p[j] * qj * ib - beta * v[j];
         v[j] = vt;
         ssq += vt * vt;
-    }
+    };
+    for_columns(att, ins, n - glob.ng, red, column, [&](int64_t j) { column(j, 0.0); });
+    for_globals<Acc>(glob, red, column);
     const double r = block_sum(ssq, red);
     if (threadIdx.x == 0) part[blockIdx.x] = r;
 }
 
-// v = v~/alpha ; vp = p .* v ; y += t1 w ; w = v + t2 w ;
+// alpha_{i+1} = ||v~|| and the plane rotation eliminating beta_{i+1}.
+__device__ __forceinline__ void rotate_update(Scalars& s, double ssq)
+{
+    double alpha = s.alpha;
+    if (!s.beta_zero) alpha = sqrt(ssq);
+    const double beta = s.beta;
+    const double rhobar = s.rhobar;
+    const double rho = sqrt(rhobar * rhobar + beta * beta);
+    const double c = rhobar / rho;
+    const double sn = beta / rho;
+    const double theta = sn * alpha;
+    const double phi = c * s.phibar;
+    s.alpha = alpha;
+    s.rho = rho;
+    s.c = c;
+    s.s = sn;
+    s.theta = theta;
+    s.rhobar = -c * alpha;
+    s.phi = phi;
+    s.phibar = sn * s.phibar;
+    s.t1 = phi / rho;
+    s.t2 = -theta / rho;
+    s.inv_alpha = alpha > 0.0 ? 1.0 / alpha : 1.0;
+    s.coef_u = beta > 0.0 ? alpha / beta : 0.0;
+    s.rnorm = s.phibar;
+    s.arnorm = alpha * fabs(c) * s.phibar;
+}
+
+// Place of column j of the attitude section in the interleaved copy vp3.
+__device__ __forceinline__ int64_t att_place(int64_t c, int64_t n_dfa)
+{
+    const int ax = (c >= n_dfa) + (c >= 2 * n_dfa);
+    return kAxes * (c - ax * n_dfa) + ax;
+}
+
+// alpha and the rotation, v = v~/alpha ; vp = p .* v (and its attitude section
+// interleaved by axis, vp3, when there is one) ; y += t1 w ; w = v + t2 w ;
 // partials of ||w/rho||^2 and ||y||^2 ; var (optional) += (w/rho)^2, the
 // per-iteration variance term of Algorithm 1 (diagonal estimate of
-// (Abar^T Abar)^-1, rescaled by p^2 after the loop).
+// (Abar^T Abar)^-1, rescaled by p^2 after the loop). Every workgroup sums the
+// same partc and makes the same rotation from the state A; workgroup 0 stores
+// the new state to B, which the stopping tests read (Gate).
 template <typename VP>
 __global__ __launch_bounds__(kBlock) void k_col_b(int64_t n, const double* __restrict__ p,
                                                    double* __restrict__ v,
                                                    double* __restrict__ w,
                                                    double* __restrict__ y, VP* __restrict__ vp,
-                                                   const Scalars* __restrict__ sc,
+                                                   VP* __restrict__ vp3, int64_t att_base,
+                                                   int64_t n_dfa, const Scalars* __restrict__ A,
+                                                   Scalars* __restrict__ B,
+                                                   const double* __restrict__ partc, int npartc,
                                                    double* __restrict__ part_dd,
                                                    double* __restrict__ part_xx,
                                                    double* __restrict__ var)
 {
     __shared__ double red[kWavesPerBlock];
-    if (sc->done) return;
-    const double ia = sc->beta_zero ? 1.0 : sc->inv_alpha;
-    const double t1 = sc->t1, t2 = sc->t2, ir = 1.0 / sc->rho;
+    __shared__ double bc[4];
+    if (A->done) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) *B = *A;
+        return;
+    }
+    const double ssq = sum_partials(partc, npartc, red);
+    if (threadIdx.x == 0) {
+        Scalars s = *A;
+        rotate_update(s, ssq);
+        bc[0] = s.beta_zero ? 1.0 : s.inv_alpha;
+        bc[1] = s.t1;
+        bc[2] = s.t2;
+        bc[3] = 1.0 / s.rho;
+        if (blockIdx.x == 0) *B = s;
+    }
+    __syncthreads();
+    const double ia = bc[0], t1 = bc[1], t2 = bc[2], ir = bc[3];
+    const int64_t natt = vp3 ? kAxes * n_dfa : 0;
     double dd = 0.0, xx = 0.0;
     for (int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x; j < n;
          j += (int64_t)gridDim.x * kBlock) {
         const double vj = v[j] * ia;
         v[j] = vj;
-        vp[j] = (VP)(p[j] * vj);
+        const VP vpj = (VP)(p[j] * vj);
+        vp[j] = vpj;
+        const int64_t ca = j - att_base;
+        if (ca >= 0 && ca < natt) vp3[att_place(ca, n_dfa)] = vpj;
         const double wj = w[j];
         const double dk = wj * ir;
         dd += dk * dk;
@@ -1225,22 +1604,27 @@ __global__ __launch_bounds__(kBlock) void k_col_b(int64_t n, const double* __res
     if (threadIdx.x == 0) part_xx[blockIdx.x] = r;
 }
 
-// Initial v = v~/alpha_1 ; vp = p .* v ; w = v ; y = 0.
+// Initial v = v~/alpha_1 ; vp = p .* v (vp3 as in k_col_b) ; w = v ; y = 0.
 template <typename VP>
 __global__ __launch_bounds__(kBlock) void k_col_init(int64_t n, const double* __restrict__ p,
                                                       double* __restrict__ v,
                                                       double* __restrict__ w,
                                                       double* __restrict__ y,
-                                                      VP* __restrict__ vp,
+                                                      VP* __restrict__ vp, VP* __restrict__ vp3,
+                                                      int64_t att_base, int64_t n_dfa,
                                                       const Scalars* __restrict__ sc)
 {
     const double ia = sc->inv_alpha;
+    const int64_t natt = vp3 ? kAxes * n_dfa : 0;
     for (int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x; j < n;
          j += (int64_t)gridDim.x * kBlock) {
         const double vj = v[j] * ia;
         v[j] = vj;
         w[j] = vj;
-        vp[j] = (VP)(p[j] * vj);
+        const VP vpj = (VP)(p[j] * vj);
+        vp[j] = vpj;
+        const int64_t ca = j - att_base;
+        if (ca >= 0 && ca < natt) vp3[att_place(ca, n_dfa)] = vpj;
         y[j] = 0.0;
     }
 }
@@ -1372,101 +1756,6 @@ __global__ __launch_bounds__(kBlock) void k_scalar_init_alpha(const double* __re
     sc->inv_alpha = alpha > 0.0 ? 1.0 / alpha : 1.0;
     sc->coef_u = alpha / sc->beta;
     if (sc->arnorm == 0.0) sc->done = 1;  // A^T b = 0: x = 0 (istop 0)
-}
-
-// beta_{i+1} = ||u~|| ; anorm update.
-__global__ __launch_bounds__(kBlock) void k_scalar_beta(const double* __restrict__ part,
-                                                         int nblk, Scalars* __restrict__ sc)
-{
-    __shared__ double red[kWavesPerBlock];
-    if (sc->done) return;
-    const double ssq = sum_partials(part, nblk, red);
-    if (threadIdx.x != 0) return;
-    const double beta = sqrt(ssq);
-    sc->beta = beta;
-    if (beta > 0.0) {
-        const double a = sc->alpha;
-        sc->anorm = sqrt(sc->anorm * sc->anorm + a * a + beta * beta);
-        sc->beta_zero = 0;
-    } else {
-        sc->beta_zero = 1;
-    }
-}
-
-// alpha_{i+1} = ||v~|| and the plane rotation eliminating beta_{i+1}.
-__global__ __launch_bounds__(kBlock) void k_scalar_alpha(const double* __restrict__ part,
-                                                          int nblk, Scalars* __restrict__ sc)
-{
-    __shared__ double red[kWavesPerBlock];
-    if (sc->done) return;
-    const double ssq = sum_partials(part, nblk, red);
-    if (threadIdx.x != 0) return;
-    double alpha = sc->alpha;
-    if (!sc->beta_zero) alpha = sqrt(ssq);
-    const double beta = sc->beta;
-    const double rhobar = sc->rhobar;
-    const double rho = sqrt(rhobar * rhobar + beta * beta);
-    const double c = rhobar / rho;
-    const double sn = beta / rho;
-    const double theta = sn * alpha;
-    const double phi = c * sc->phibar;
-    sc->alpha = alpha;
-    sc->rho = rho;
-    sc->c = c;
-    sc->s = sn;
-    sc->theta = theta;
-    sc->rhobar = -c * alpha;
-    sc->phi = phi;
-    sc->phibar = sn * sc->phibar;
-    sc->t1 = phi / rho;
-    sc->t2 = -theta / rho;
-    sc->inv_alpha = alpha > 0.0 ? 1.0 / alpha : 1.0;
-    sc->coef_u = beta > 0.0 ? alpha / beta : 0.0;
-    sc->rnorm = sc->phibar;
-    sc->arnorm = alpha * fabs(c) * sc->phibar;
-}
-
-// ddnorm, xnorm, acond and the stopping tests of Paige & Saunders.
-__global__ __launch_bounds__(kBlock) void k_scalar_stop(const double* __restrict__ part_dd,
-                                                         const double* __restrict__ part_xx,
-                                                         int nblk, Scalars* __restrict__ sc)
-{
-    __shared__ double red[kWavesPerBlock];
-    if (sc->done) return;
-    const double dd = sum_partials(part_dd, nblk, red);
-    const double xx = sum_partials(part_xx, nblk, red);
-    if (threadIdx.x != 0) return;
-    const double ddnorm = sc->ddnorm + dd;
-    const double xnorm = sqrt(xx);
-    const double anorm = sc->anorm;
-    const double acond = anorm * sqrt(ddnorm);
-    const double rnorm = sc->rnorm, arnorm = sc->arnorm, bnorm = sc->bnorm;
-    sc->ddnorm = ddnorm;
-    sc->xnorm = xnorm;
-    sc->acond = acond;
-    const int32_t itn = sc->itn + 1;
-    sc->itn = itn;
-
-    const double test1 = rnorm / bnorm;
-    const double test2 = (anorm * rnorm) > 0.0 ? arnorm / (anorm * rnorm) : 0.0;
-    const double test3 = acond > 0.0 ? 1.0 / acond : 0.0;
-    const double t1 = test1 / (1.0 + anorm * xnorm / bnorm);
-    const double rtol = sc->btol + sc->atol * anorm * xnorm / bnorm;
-    int32_t istop = 0;
-    if (itn >= sc->itn_limit) istop = 7;
-    if (sc->tests) {
-        if (1.0 + test3 <= 1.0) istop = 6;
-        if (1.0 + test2 <= 1.0) istop = 5;
-        if (1.0 + t1 <= 1.0) istop = 4;
-        if (test3 <= sc->ctol) istop = 3;
-        if (test2 <= sc->atol) istop = 2;
-        if (test1 <= rtol) istop = 1;
-    }
-    // Relative form of the normal-equation test, for correction problems whose
-    // residual is dominated by the irreducible least-squares residual.
-    if (sc->rel_ar > 0.0 && arnorm <= sc->rel_ar * sc->arnorm0) istop = 2;
-    sc->istop = istop;
-    if (istop != 0) sc->done = 1;
 }
 
 // ------------------------------------------------------------------- set-up
@@ -1624,16 +1913,22 @@ __global__ __launch_bounds__(kBlock) void k_att_gather(const T* __restrict__ val
 // issue order, so a store issued before the next row's loads would be waited
 // for together with them (one store round trip per row); after them it is
 // not.
-template <typename T, typename Acc, int K, int KS, int NT, bool SEP = false, bool PIPE = (K == 1)>
+// GATED (single right-hand side): the pass makes the previous iteration's
+// stopping tests first (Gate); otherwise sc holds the K current states.
+template <typename T, typename Acc, int K, int KS, int NT, bool SEP = false, bool PIPE = (K == 1),
+          bool GATED = false>
 __global__ __launch_bounds__(NT) void k_att_dot(int64_t ld, const T* __restrict__ att_sorted,
                                                  const int32_t* __restrict__ tloc,
                                                  const int64_t* __restrict__ bstart,
                                                  int64_t width, int G, int64_t n_dfa,
                                                  const Acc* __restrict__ x3, Acc* __restrict__ u,
-                                                 const Scalars* __restrict__ sc)
+                                                 const Scalars* __restrict__ sc,
+                                                 Gate gate = Gate{})
 {
     static_assert(K % KS == 0, "sweeps of KS right-hand sides cover the tile");
     extern __shared__ __align__(16) unsigned char smem_raw[];
+    __shared__ double red[kWavesPerBlock];
+    __shared__ int32_t gflag;
     Acc* win = reinterpret_cast<Acc*>(smem_raw);
     const int64_t span = width + kParAxis - 1;
     const int64_t bk = blockIdx.x / G, g = blockIdx.x - bk * G;
@@ -1645,12 +1940,14 @@ __global__ __launch_bounds__(NT) void k_att_dot(int64_t ld, const T* __restrict_
     for (int s0 = 0; s0 < K; s0 += KS) {
         uint32_t live = 0;
         Acc coef[KS];
+        if constexpr (!GATED) {
 #pragma unroll
-        for (int j = 0; j < KS; ++j) {
-            live |= (sc[s0 + j].done ? 0u : 1u) << j;
-            coef[j] = (Acc)sc[s0 + j].coef_u;
+            for (int j = 0; j < KS; ++j) {
+                live |= (sc[s0 + j].done ? 0u : 1u) << j;
+                coef[j] = (Acc)sc[s0 + j].coef_u;
+            }
+            if (live == 0) continue;  // uniform over the grid
         }
-        if (live == 0) continue;  // uniform over the grid
         if (KS == K) {
             for (int64_t e = threadIdx.x; e < kAxes * ncol * K; e += NT)
                 win[e] = x3[kAxes * c0 * K + e];
@@ -1659,6 +1956,12 @@ __global__ __launch_bounds__(NT) void k_att_dot(int64_t ld, const T* __restrict_
                 const int64_t col = e / KS;
                 win[e] = x3[(kAxes * c0 + col) * K + s0 + (e - col * KS)];
             }
+        }
+        if constexpr (GATED) {  // beside the window's loads
+            double cf = 0.0;
+            if (!gate_open<NT>(gate, red, &gflag, &cf)) return;
+            live = 1u;
+            coef[0] = (Acc)cf;
         }
         __syncthreads();
         constexpr int kAtt = kAxes * kParAxis;

@@ -1,16 +1,20 @@
 // Host side of the AVU-GSR LSQR library: handle, workspace, the LSQR
 // iteration driven on one GPU, and the C ABI declared in include/lsqr.h.
 //
-// One LSQR iteration (Paige & Saunders 1982; the paper's Algorithm 1 loop) is
-// eight kernels on one stream, with every scalar kept on the device:
-//   aprod1      u~ <- A (p.*v) - (alpha/beta) u~      [+ ||u~||^2 partials]
-//   beta        beta = ||u~||, anorm
-//   aprod2      q  <- A^T u~                           [astro/att/instr/glob]
-//   glob_sum    second stage of the global-column reduction
-//   col_a       v~ = p.*q/beta - beta v               [+ ||v~||^2 partials]
-//   alpha       alpha = ||v~||, plane rotation, estimates
-//   col_b       v = v~/alpha, y += (phi/rho) w, w = v - (theta/rho) w
-//   stop        ddnorm, xnorm, acond, stopping tests, itn
+// One LSQR iteration (Paige & Saunders 1982; the paper's Algorithm 1 loop) on
+// one stream, with every scalar kept on the device:
+//   row passes  u~ <- A (p.*v) - (alpha/beta) u~      [+ ||u~||^2 partials]
+//               q  <- A^T u~                           [astro/att/instr/glob]
+//   col_a       beta = ||u~||; v~ = p.*q/beta - beta v [+ ||v~||^2 partials]
+//   col_b       alpha = ||v~||, plane rotation, estimates;
+//               v = v~/alpha, y += (phi/rho) w, w = v - (theta/rho) w
+//   and, in the next iteration's first row pass (or k_scalar_stop),
+//               ddnorm, xnorm, acond, stopping tests, itn
+// The row passes are one sweep over A (kAttAll) where the attitude and
+// instrumental histograms fit in LDS, else three: the attitude products in
+// bucket order, the fused pass, the attitude histograms. A scalar step is
+// made by the kernel that needs it, in every workgroup from the same partials
+// in the same order, not by a launch of its own (4-5 us and a gap each).
 // u~ is the unnormalised left vector (u = u~/beta); keeping it unnormalised
 // saves a pass over the row-sized vector per iteration. Preconditioning
 // (column scaling by p, Sect. 2) is applied on the column vectors, so the
@@ -120,6 +124,8 @@ constexpr int kWavesPerCU = 16;                 // row ranges per compute unit i
 // +1.6 ms at 100).
 constexpr int kAttBlock = 1024;  // attitude-pass workgroup (one per CU: the histogram fills LDS)
 constexpr int kMaxTile = 16;     // right-hand sides of the widest k-tile
+// Constraint rows whose squares k_col_a sums itself; more go through k_con_ssq.
+constexpr int64_t kConDirect = 1024;
 
 // Working vectors of one arithmetic precision of the LSQR loop.
 template <typename Acc>
@@ -166,7 +172,7 @@ struct lsqr_handle {
     double* w = nullptr;    // [n]
     double* y = nullptr;    // [n] iterate in the scaled space
     double* part1 = nullptr;                    // [max(nb1, nb2) + 1]
-    double* partc = nullptr;                    // [nbc]
+    double* partc = nullptr;                    // [4 CUs]
     double* partdd = nullptr;                   // [nbc]
     double* partxx = nullptr;                   // [nbc]
     double* gpart_raw = nullptr;                // [nb2] FP64 partials of lsqr_aprod2
@@ -179,7 +185,8 @@ struct lsqr_handle {
     const double* con_val = nullptr;
     double* con_ssq = nullptr;  // [nc] squares of the new row-vector entries
     int con_grid = 0;           // workgroups of the constraint kernels
-    Scalars* sc = nullptr;                      // device scalars
+    Scalars* sc = nullptr;      // device scalars: the current state, and the one between k_col_b
+                                // and the stopping tests (Gate)
     Scalars* sc_host = nullptr;                 // pinned mirror
 
     Path<double> p64;
@@ -202,6 +209,8 @@ struct lsqr_handle {
     float* x3_raw32 = nullptr;    // the same for lsqr_aprod1_f32
     float* gpart_raw32 = nullptr; // global-column partials of lsqr_aprod2_f32
     bool att_ready = false;
+    bool att_locked = false;      // a solve or aprod2 has run: the bucket options are settled
+    double* S1 = nullptr;         // slices of the one-pass histograms (attitude, then instrumental)
 
     // variance estimate of the last lsqr_solve (LSQR_OPT_VARIANCE)
     double* var = nullptr;        // [n] sum of (w/rho)^2 in the scaled space
@@ -279,10 +288,51 @@ inline bool use_fused(const lsqr_handle* h)
     return h->fused && att_pass_on(h) && !h->generic;
 }
 
+// Bytes of LDS of the one-pass form (kAttAll) with *win: the vector's
+// instrumental slice (1) and its attitude section too (2) staged beside the
+// FP64 histograms of the attitude and instrumental columns; 0 when the
+// histograms alone do not fit.
+inline size_t one_pass_lds(const lsqr_handle* h, int64_t vbytes, int* win)
+{
+    const int64_t ninst = h->sv.ni > 0 ? h->sv.n_instr_cols : 0;
+    const int64_t natt = h->sv.natt > 0 ? kAxes * h->sv.n_dfa : 0;
+    const int64_t hist = ((natt + ninst) * 8 + 15) & ~(int64_t)15;
+    *win = 0;
+    if (hist > kLdsInstrBudget) return 0;
+    int64_t lds = hist;
+    if (lds + ninst * vbytes <= kLdsInstrBudget) {
+        lds += ninst * vbytes;
+        *win = 1;
+        if (lds + natt * vbytes <= kLdsInstrBudget) {
+            lds += natt * vbytes;
+            *win = 2;
+        }
+    }
+    return (size_t)std::max<int64_t>(lds, 16);
+}
+
+// Single-RHS row passes in one sweep over A: where the histograms of the
+// attitude and instrumental columns fit in LDS together, unless options ask
+// for another form (a bucket count asks for the bucket order).
+inline bool one_pass_on(const lsqr_handle* h)
+{
+    int win = 0;
+    return h->fused == 2 && h->att_mode == 1 && h->att_buckets == 0 &&
+           h->sv.m < ((int64_t)1 << 31) && h->sv.n_dfa < ((int64_t)1 << 31) &&
+           one_pass_lds(h, 8, &win) > 0;
+}
+
 // Effective fused mode of a single-RHS iteration: 0 separate passes, 1 fused
 // pass with the attitude dot product, 2 attitude pre-pass + fused pass, 3 the
-// same with the row vector kept in star order.
-inline int fused_mode(const lsqr_handle* h) { return use_fused(h) ? h->fused : 0; }
+// same with the row vector kept in star order, kOnePass one sweep for
+// everything. General layouts run 2 (with an attitude section), one pass or 0.
+constexpr int kOnePass = 4;
+inline int fused_mode(const lsqr_handle* h)
+{
+    if (one_pass_on(h)) return kOnePass;
+    if (h->generic) return att_pass_on(h) && h->fused == 2 ? 2 : 0;
+    return use_fused(h) ? h->fused : 0;
+}
 
 // Fused mode 3 keeps the single-RHS row vector in star order: the star-order
 // pass reads and writes it sequentially, and the bucket-order passes reach it
@@ -299,10 +349,11 @@ inline bool rhs_lanes_on(const lsqr_handle* h) { return h->rhs_lanes && use_fuse
 inline int n_part(const lsqr_handle* h, int nb) { return nb + (h->nc > 0 ? 1 : 0); }
 
 // Placement of the single-RHS solver's row vector: bucket order in attitude
-// mode 1 (row i at u[invperm[i]]) except in fused mode 3.
+// mode 1 (row i at u[invperm[i]]) except in fused mode 3 and in one pass.
 inline const int32_t* row_map(const lsqr_handle* h)
 {
-    return (att_pass_on(h) && !star_order_u(h)) ? h->invperm : nullptr;
+    const int mode = fused_mode(h);
+    return (att_pass_on(h) && mode != 3 && mode != kOnePass) ? h->invperm : nullptr;
 }
 
 // Placement of a batched k-tile's row vectors: bucket order in attitude mode 1.
@@ -451,68 +502,114 @@ void launch_interleave_att(const lsqr_handle* h, const V* x, V* x3, const Scalar
                        h->sv.att_base, h->sv.n_dfa, x3, sc);
 }
 
+// Where the scalars are: the current state, or pending stopping tests (Gate).
+inline Gate gate_of(const lsqr_handle* h, bool pending)
+{
+    return {pending ? h->sc + 1 : nullptr, h->sc, h->partdd, h->partxx, h->nbc};
+}
+
+// Calls f with std::true_type or std::false_type for each flag.
+template <typename F>
+void by_flag(bool a, F&& f)
+{
+    if (a) f(std::true_type());
+    else f(std::false_type());
+}
+
 // The fused pass (aprod1 and the astrometric, instrumental and global part of
 // aprod2 in one sweep) over the main-pass grid.
-template <typename T, typename Acc, bool LDSX, int AM>
-void launch_fused_as(const lsqr_handle* h, Path<Acc>& P, const Acc* x3, hipStream_t st)
+template <typename T, typename Acc, bool LDSX, int AM, int GEN = 0>
+void launch_fused_as(const lsqr_handle* h, Path<Acc>& P, const Acc* x3, const Gate& gate,
+                     hipStream_t st)
 {
     // kAttGather reads the pre-pass output through invperm; u~ is in star order
     const int32_t* inv = AM == kAttGather ? (const int32_t*)h->invperm : row_map(h);
     const Acc* datt = AM == kAttGather ? (const Acc*)P.datt : nullptr;
-    if (h->sv.star32)
-        hipLaunchKernelGGL((k_fused<T, Acc, kBlock2, LDSX, AM, true>), dim3(h->nb2), dim3(kBlock2),
-                           P.lds_f, st, h->sv, (const Acc*)P.vp, x3, P.u, P.q, h->wb, P.gpart,
-                           h->part1, P.f_hcols, h->sc, inv, datt, P.ustar);
-    else
-        hipLaunchKernelGGL((k_fused<T, Acc, kBlock2, LDSX, AM, false>), dim3(h->nb2),
-                           dim3(kBlock2), P.lds_f, st, h->sv, (const Acc*)P.vp, x3, P.u, P.q,
-                           h->wb, P.gpart, h->part1, P.f_hcols, h->sc, inv, datt, P.ustar);
+    by_flag(GEN == 0 && h->sv.star32 != nullptr, [&](auto cidx) {
+        constexpr bool C = decltype(cidx)::value && GEN == 0;
+        hipLaunchKernelGGL((k_fused<T, Acc, kBlock2, LDSX, AM, C, GEN>), dim3(h->nb2),
+                           dim3(kBlock2), P.lds_f, st, h->sv, (const Acc*)P.vp, x3, P.u, P.q, h->wb,
+                           P.gpart, h->part1, P.f_hcols, gate, inv, datt, P.ustar,
+                           (double*)nullptr, (double*)nullptr);
+    });
+}
+
+// The one-pass form: the LSQR step (A2 = false: x = vp, x3 = its interleaved
+// attitude section, u updated), or Eq. (3) alone for u in row order (A2). The
+// histograms go to the slices S1.
+template <typename T, typename Acc, bool A2>
+void launch_one_pass(const lsqr_handle* h, const Acc* x, const Acc* x3, Acc* u, Acc* q, Acc* gpart,
+                     const Gate& gate, hipStream_t st)
+{
+    int win = 0;
+    size_t lds = one_pass_lds(h, (int64_t)sizeof(Acc), &win);
+    const int64_t ninst = h->sv.ni > 0 ? h->sv.n_instr_cols : 0;
+    const int64_t natt = h->sv.natt > 0 ? kAxes * h->sv.n_dfa : 0;
+    if (A2) lds = (size_t)std::max<int64_t>((ninst + natt) * 8, 16);
+    double* satt = h->S1;
+    double* sins = h->S1 + natt * h->nb2;
+    auto go = [&](auto ldsx, auto wn, auto cidx, auto gen) {
+        hipLaunchKernelGGL((k_fused<T, Acc, kBlock2, decltype(ldsx)::value, kAttAll,
+                                    decltype(cidx)::value, decltype(gen)::value,
+                                    decltype(wn)::value, A2>),
+                           dim3(h->nb2), dim3(kBlock2), lds, st, h->sv, x, x3, u, q, h->wb, gpart,
+                           h->part1, ninst, gate, (const int32_t*)nullptr, (const Acc*)nullptr,
+                           (Acc*)nullptr, satt, sins);
+    };
+    using Y = std::true_type;
+    using N = std::false_type;
+    auto by_win = [&](auto cidx, auto gen) {
+        if constexpr (A2) go(N(), N(), cidx, gen);
+        else if (win == 2) go(Y(), Y(), cidx, gen);
+        else if (win == 1) go(Y(), N(), cidx, gen);
+        else go(N(), N(), cidx, gen);
+    };
+    if (h->generic && h->sv.ng > 1) by_win(N(), std::integral_constant<int, kGlobMax>());
+    else if (h->generic) by_win(N(), std::integral_constant<int, 1>());
+    else if (h->sv.star32) by_win(Y(), std::integral_constant<int, 0>());
+    else by_win(N(), std::integral_constant<int, 0>());
 }
 
 // Attitude part of aprod1 in bucket order (x3 must hold the interleaved
 // attitude section of vp): folded into u~ in fused mode 2, written alone to
 // the bucket-order vector datt in fused mode 3.
 template <typename T, typename Acc, bool SEP, bool PIPE>
-void launch_att_dot_as(const lsqr_handle* h, Path<Acc>& P, hipStream_t st)
+void launch_att_dot_as(const lsqr_handle* h, Path<Acc>& P, const Gate& gate, hipStream_t st)
 {
     const size_t lds = (size_t)(kAxes * att_span(h)) * sizeof(Acc);
-    hipLaunchKernelGGL((k_att_dot<T, Acc, 1, 1, kAttBlock, SEP, PIPE>), dim3(att_slices(h)),
+    hipLaunchKernelGGL((k_att_dot<T, Acc, 1, 1, kAttBlock, SEP, PIPE, true>), dim3(att_slices(h)),
                        dim3(kAttBlock), lds, st, h->att_ld, (const T*)h->att_sorted,
                        (const int32_t*)h->tloc, (const int64_t*)h->bstart, h->bwidth, h->att_g,
-                       h->sv.n_dfa, (const Acc*)P.vp3, SEP ? P.datt : P.u, h->sc);
+                       h->sv.n_dfa, (const Acc*)P.vp3, SEP ? P.datt : P.u, (const Scalars*)nullptr,
+                       gate);
 }
 
 template <typename T, typename Acc>
-void launch_att_dot(const lsqr_handle* h, Path<Acc>& P, hipStream_t st)
+void launch_att_dot(const lsqr_handle* h, Path<Acc>& P, const Gate& gate, hipStream_t st)
 {
-    if (star_order_u(h)) {
-        if (h->pipe) launch_att_dot_as<T, Acc, true, true>(h, P, st);
-        else launch_att_dot_as<T, Acc, true, false>(h, P, st);
-    } else {
-        if (h->pipe) launch_att_dot_as<T, Acc, false, true>(h, P, st);
-        else launch_att_dot_as<T, Acc, false, false>(h, P, st);
-    }
+    by_flag(star_order_u(h), [&](auto sep) {
+        by_flag(h->pipe, [&](auto pipe) {
+            launch_att_dot_as<T, Acc, decltype(sep)::value, decltype(pipe)::value>(h, P, gate, st);
+        });
+    });
 }
 
 // pre: the attitude part of the row products is already in u~ (fused mode 2)
 // or in datt (fused mode 3)
 template <typename T, typename Acc>
-void launch_fused(const lsqr_handle* h, Path<Acc>& P, hipStream_t st, bool pre)
+void launch_fused(const lsqr_handle* h, Path<Acc>& P, const Gate& gate, hipStream_t st, bool pre)
 {
     const Acc* x3 = h->att_il ? (const Acc*)P.vp3 : nullptr;
-    if (pre && star_order_u(h)) {
-        if (P.f_ldsx) launch_fused_as<T, Acc, true, kAttGather>(h, P, nullptr, st);
-        else launch_fused_as<T, Acc, false, kAttGather>(h, P, nullptr, st);
-    } else if (pre) {
-        if (P.f_ldsx) launch_fused_as<T, Acc, true, kAttPre>(h, P, nullptr, st);
-        else launch_fused_as<T, Acc, false, kAttPre>(h, P, nullptr, st);
-    } else if (P.f_ldsx) {
-        if (x3) launch_fused_as<T, Acc, true, kAttX3>(h, P, x3, st);
-        else launch_fused_as<T, Acc, true, kAttX>(h, P, x3, st);
-    } else {
-        if (x3) launch_fused_as<T, Acc, false, kAttX3>(h, P, x3, st);
-        else launch_fused_as<T, Acc, false, kAttX>(h, P, x3, st);
-    }
+    by_flag(P.f_ldsx, [&](auto ldsx) {
+        constexpr bool L = decltype(ldsx)::value;
+        if (h->generic && h->sv.ng > 1)
+            launch_fused_as<T, Acc, L, kAttPre, kGlobMax>(h, P, nullptr, gate, st);
+        else if (h->generic) launch_fused_as<T, Acc, L, kAttPre, 1>(h, P, nullptr, gate, st);
+        else if (pre && star_order_u(h)) launch_fused_as<T, Acc, L, kAttGather>(h, P, nullptr, gate, st);
+        else if (pre) launch_fused_as<T, Acc, L, kAttPre>(h, P, nullptr, gate, st);
+        else if (x3) launch_fused_as<T, Acc, L, kAttX3>(h, P, x3, gate, st);
+        else launch_fused_as<T, Acc, L, kAttX>(h, P, x3, gate, st);
+    });
     // the tail windows read u~ in star order when the fused pass wrote a copy
     if (P.ustar)
         launch_instr_tail<T, Acc, 1, false>(h, P.ustar, nullptr, P.q, P.f_hcols, h->sc, st);
@@ -537,6 +634,52 @@ inline SliceView att_slice_view(const lsqr_handle* h, const double* S)
             slice_lanes(h, kAxes * h->sv.n_dfa, h->att_g)};
 }
 
+constexpr SliceView kNoSlices = {nullptr, 1, 1, 1, 0, 0, 1, 1, 1};
+
+// The one-pass slices: one bucket that holds the section, a slice per workgroup.
+inline SliceView one_pass_att(const lsqr_handle* h)
+{
+    if (h->sv.natt == 0) return kNoSlices;
+    const int64_t d = h->sv.n_dfa;
+    return {h->S1, 1, d, d, d, h->sv.att_base, kAxes, h->nb2,
+            slice_lanes(h, kAxes * d, h->nb2)};
+}
+
+inline SliceView one_pass_instr(const lsqr_handle* h)
+{
+    if (h->sv.ni == 0) return kNoSlices;
+    const int64_t c = h->sv.n_instr_cols;
+    const int64_t natt = h->sv.natt > 0 ? kAxes * h->sv.n_dfa : 0;
+    return {h->S1 + natt * h->nb2, 1, c, c, c, h->sv.instr_base, 1, h->nb2,
+            slice_lanes(h, c, h->nb2)};
+}
+
+// Global-column partials of a row pass of nblk workgroups (stride: k_gen_aprod2
+// leaves kGlobMax per workgroup, k_fused as many as its instance holds).
+inline GlobView glob_view(const lsqr_handle* h, const void* part, int nblk, int stride)
+{
+    return {part, h->sv.glob_base, nblk, stride, h->sv.ng};
+}
+
+inline int fused_globs(const lsqr_handle* h) { return h->generic && h->sv.ng > 1 ? kGlobMax : 1; }
+
+// Blocks of a kernel over n columns of which the sections' slices are summed.
+inline int column_grid(const lsqr_handle* h, int64_t n, const SliceView& att, const SliceView& ins)
+{
+    const int64_t tiles = att.tiles() + ins.tiles() + cdiv(n - att.cols() - ins.cols(), kBlock);
+    return (int)std::max<int64_t>(1, std::min<int64_t>((int64_t)h->num_cu * 4, tiles));
+}
+
+// q += the slices' sums and the global partials of an aprod2
+template <typename Acc>
+void launch_section_sums(const lsqr_handle* h, const SliceView& att, const SliceView& ins,
+                         const GlobView& glob, Acc* q, const Scalars* sc, hipStream_t st)
+{
+    hipLaunchKernelGGL((k_section_sums<Acc>),
+                       dim3(column_grid(h, att.cols() + ins.cols(), att, ins)), dim3(kBlock), 0, st,
+                       att, ins, glob, q, sc);
+}
+
 template <typename Acc, int K>
 void launch_slice_reduce(const lsqr_handle* h, const SliceView& V, Acc* q, const Scalars* sc,
                          hipStream_t st)
@@ -548,11 +691,27 @@ void launch_slice_reduce(const lsqr_handle* h, const SliceView& V, Acc* q, const
                        dim3(kBlock), 0, st, V, q, sc);
 }
 
+// The column steps of an iteration: beta, v~ (with the sections' slices and
+// the global partials), alpha and the rotation, v, w, y, vp.
+template <typename Acc>
+void launch_columns(const lsqr_handle* h, Path<Acc>& P, const BetaView& beta, const SliceView& att,
+                    const SliceView& ins, const GlobView& glob, hipStream_t st)
+{
+    const int64_t n = h->sv.n;
+    const int grid = column_grid(h, n, att, ins);
+    hipLaunchKernelGGL((k_col_a<Acc>), dim3(grid), dim3(kBlock), 0, st, n, h->p, P.q, h->v, h->sc,
+                       beta, att, ins, glob, h->partc);
+    hipLaunchKernelGGL((k_col_b<Acc>), dim3(h->nbc), dim3(kBlock), 0, st, n, h->p, h->v, h->w,
+                       h->y, P.vp, h->sv.natt > 0 ? P.vp3 : nullptr, h->sv.att_base, h->sv.n_dfa,
+                       (const Scalars*)h->sc, h->sc + 1, (const double*)h->partc, grid, h->partdd,
+                       h->partxx, (std::is_same<Acc, double>::value && h->var_on) ? h->var : nullptr);
+}
+
 // Attitude part of aprod2 in bucket order: per-workgroup LDS histograms of
-// each bucket's columns, then their sum. ub: the row vector in bucket order,
+// each bucket's columns, left as slices in S2. ub: the row vector in bucket order,
 // or (gperm = perm) in star order, read through the permutation.
 template <typename T, typename Acc>
-void launch_att_pass(lsqr_handle* h, const Acc* ub, Acc* q, const Scalars* sc, hipStream_t st,
+void launch_att_pass(lsqr_handle* h, const Acc* ub, const Scalars* sc, hipStream_t st,
                      const int32_t* gperm)
 {
     const size_t lds = (size_t)(kAxes * att_span(h) * 8);
@@ -572,7 +731,6 @@ void launch_att_pass(lsqr_handle* h, const Acc* ub, Acc* q, const Scalars* sc, h
         if (h->pipe) go(N(), Y());
         else go(N(), N());
     }
-    launch_slice_reduce<Acc, 1>(h, att_slice_view(h, h->S2), q, sc, st);
 }
 
 // q += A^T u for the LSQR loop (and lsqr_aprod2): the constraint rows (u[m..]),
@@ -589,82 +747,104 @@ void launch_aprod2(lsqr_handle* h, const Acc* u, const int32_t* inv, Acc* q, Acc
     const dim3 g(h->nb2), bm(kBlock2), b(kBlock);
     const bool att = !att_pass_on(h);
     launch_con_aprod2<Acc, Acc>(h, u + h->sv.m, q, sc, st);
-    if (h->generic) {  // any layout: runtime section sizes, 256-thread workgroups
-        if (att)
-            hipLaunchKernelGGL((k_gen_aprod2<T, Acc, Acc, false, true>), dim3(h->nba), b, lds, st,
-                               h->sv, u, q, h->wb, gpart, hcols, sc, inv);
-        else
-            hipLaunchKernelGGL((k_gen_aprod2<T, Acc, Acc, false, false>), dim3(h->nba), b, lds, st,
-                               h->sv, u, q, h->wb, gpart, hcols, sc, inv);
-        hipLaunchKernelGGL((k_gen_glob_sum<Acc>), dim3(1), b, 0, st, gpart, h->nba, h->sv.ng,
-                           q + h->sv.glob_base, sc);
-        launch_instr_tail<T, Acc, 1, false>(h, u, inv, q, hcols, sc, st);
-        if (!att) launch_att_pass<T, Acc>(h, ub, q, sc, st, gperm);
+    if (fused_mode(h) == kOnePass) {
+        launch_one_pass<T, Acc, true>(h, nullptr, nullptr, const_cast<Acc*>(u), q, gpart,
+                                      Gate{nullptr, const_cast<Scalars*>(sc), nullptr, nullptr, 0},
+                                      st);
+        launch_section_sums<Acc>(h, one_pass_att(h), one_pass_instr(h), glob_view(h, gpart, h->nb2, fused_globs(h)), q, sc, st);
         return;
     }
-    if (att && h->astro_scan)
-        hipLaunchKernelGGL((k_aprod2<T, Acc, Acc, false, true, true, kBlock2>), g, bm, lds, st, h->sv,
-                           u, q, h->wb, gpart, hcols, sc, inv);
-    else if (att)
-        hipLaunchKernelGGL((k_aprod2<T, Acc, Acc, false, true, false, kBlock2>), g, bm, lds, st,
-                           h->sv, u, q, h->wb, gpart, hcols, sc, inv);
-    else if (h->astro_scan)
-        hipLaunchKernelGGL((k_aprod2<T, Acc, Acc, false, false, true, kBlock2>), g, bm, lds, st,
-                           h->sv, u, q, h->wb, gpart, hcols, sc, inv);
-    else
-        hipLaunchKernelGGL((k_aprod2<T, Acc, Acc, false, false, false, kBlock2>), g, bm, lds, st,
-                           h->sv, u, q, h->wb, gpart, hcols, sc, inv);
-    hipLaunchKernelGGL((k_glob_sum<Acc>), dim3(1), b, 0, st, gpart, h->nb2, q + h->sv.glob_base, sc);
+    int nblk = h->nb2;
+    if (h->generic) {  // any layout: runtime section sizes, 256-thread workgroups
+        nblk = h->nba;
+        by_flag(att, [&](auto a) {
+            hipLaunchKernelGGL((k_gen_aprod2<T, Acc, Acc, false, decltype(a)::value>),
+                               dim3(h->nba), b, lds, st, h->sv, u, q, h->wb, gpart, hcols, sc, inv);
+        });
+    } else {
+        by_flag(att, [&](auto a) {
+            by_flag(h->astro_scan, [&](auto scan) {
+                hipLaunchKernelGGL((k_aprod2<T, Acc, Acc, false, decltype(a)::value,
+                                             decltype(scan)::value, kBlock2>),
+                                   g, bm, lds, st, h->sv, u, q, h->wb, gpart, hcols, sc, inv);
+            });
+        });
+    }
     launch_instr_tail<T, Acc, 1, false>(h, u, inv, q, hcols, sc, st);
-    if (!att) launch_att_pass<T, Acc>(h, ub, q, sc, st, gperm);
+    if (!att) launch_att_pass<T, Acc>(h, ub, sc, st, gperm);
+    launch_section_sums<Acc>(h, att ? kNoSlices : att_slice_view(h, h->S2), kNoSlices,
+                             glob_view(h, gpart, nblk, h->generic ? kGlobMax : 1), q, sc, st);
 }
 
-// One LSQR iteration; ev (optional) = kEvIter events: [0, 1] around aprod1
-// (with the fused pass: the attitude pre-pass, if any, and that pass), [2, 3]
-// around aprod2 (the attitude pass), [4] after the pre-pass.
+// One LSQR iteration; pending: the previous iteration's stopping tests are
+// still to be made (k_scalar_stop makes the last one's). ev (optional) =
+// kEvIter events: [0, 1] around aprod1 (with the fused pass: the attitude
+// pre-pass, if any, and that pass), [2, 3] around aprod2 (the attitude pass),
+// [4] after the pre-pass.
 template <typename T, typename Acc>
-void launch_iteration(lsqr_handle* h, Path<Acc>& P, hipStream_t st, hipEvent_t* ev)
+void launch_iteration(lsqr_handle* h, Path<Acc>& P, hipStream_t st, hipEvent_t* ev, bool pending)
 {
-    const int64_t n = h->sv.n;
+    const int64_t m = h->sv.m;
+    const int mode = fused_mode(h);
+    const bool gated = mode != 0;  // the first row pass makes the pending tests
+    const Gate none = gate_of(h, false), gate = gate_of(h, gated && pending);
+    SliceView att = kNoSlices, ins = kNoSlices;
+    GlobView glob = glob_view(h, P.gpart, h->nb2, fused_globs(h));
+    BetaView beta = {h->part1, h->con_ssq, h->nb2, 0};
     if (ev) (void)hipEventRecord(ev[0], st);
-    const bool pre = fused_mode(h) >= 2;
-    const bool il = (h->att_il || pre) && h->sv.natt > 0 && !h->generic;
-    if (il) launch_interleave_att<Acc>(h, P.vp, P.vp3, h->sc, st);
-    if (pre) launch_att_dot<T, Acc>(h, P, st);
+    if (mode >= 2 && mode != kOnePass) launch_att_dot<T, Acc>(h, P, gate, st);
     if (ev) (void)hipEventRecord(ev[4], st);
-    if (use_fused(h)) {
-        launch_fused<T, Acc>(h, P, st, pre);
-        launch_con_aprod1<Acc, Acc, Acc, A1_LSQR>(h, (const Acc*)P.vp, P.u + h->sv.m, nullptr,
-                                                  h->sc, h->part1 + h->nb2, st);
+    if (gated) {
+        if (mode == kOnePass)
+            launch_one_pass<T, Acc, false>(h, (const Acc*)P.vp, (const Acc*)P.vp3, P.u, P.q,
+                                           P.gpart, gate, st);
+        else
+            launch_fused<T, Acc>(h, P, mode == 1 ? gate : none, st, mode >= 2);
         if (ev) (void)hipEventRecord(ev[1], st);
-        hipLaunchKernelGGL(k_scalar_beta, dim3(1), dim3(kBlock), 0, st, h->part1,
-                           n_part(h, h->nb2), h->sc);
         if (ev) (void)hipEventRecord(ev[2], st);
-        hipLaunchKernelGGL((k_glob_sum<Acc>), dim3(1), dim3(kBlock), 0, st, P.gpart, h->nb2,
-                           P.q + h->sv.glob_base, h->sc);
-        launch_att_pass<T, Acc>(h, P.u, P.q, h->sc, st,
-                                star_order_u(h) ? (const int32_t*)h->perm : nullptr);
-        launch_con_aprod2<Acc, Acc>(h, P.u + h->sv.m, P.q, h->sc, st);
+        if (h->nc > 0) {
+            hipLaunchKernelGGL((k_con_step<Acc>), dim3(h->con_grid), dim3(kBlock), 0, st, h->nc,
+                               h->con_rowptr, h->con_col, h->con_val, (const Acc*)P.vp, P.u + m,
+                               P.q, (const Scalars*)h->sc, h->con_ssq);
+            if (h->nc <= kConDirect) {
+                beta.ncon = (int32_t)h->nc;
+            } else {
+                hipLaunchKernelGGL(k_con_ssq, dim3(1), dim3(kBlock), 0, st, h->nc,
+                                   (const double*)h->con_ssq, h->part1 + h->nb2);
+                beta.npart += 1;
+            }
+        }
+        if (mode == kOnePass) {
+            att = one_pass_att(h);
+            ins = one_pass_instr(h);
+        } else {
+            launch_att_pass<T, Acc>(h, P.u, h->sc, st, mode == 3 ? (const int32_t*)h->perm : nullptr);
+            att = att_slice_view(h, h->S2);
+        }
     } else {
-        launch_aprod1<T, Acc, Acc, Acc, A1_LSQR>(h, (const Acc*)P.vp, P.u, nullptr, h->sc,
-                                                h->part1, st, row_map(h),
-                                                il ? (const Acc*)P.vp3 : nullptr);
+        launch_aprod1<T, Acc, Acc, Acc, A1_LSQR>(
+            h, (const Acc*)P.vp, P.u, nullptr, h->sc, h->part1, st, row_map(h),
+            h->att_il && h->sv.natt > 0 ? (const Acc*)P.vp3 : nullptr);
+        beta.npart = n_part(h, h->nb1);
         if (ev) (void)hipEventRecord(ev[1], st);
-        hipLaunchKernelGGL(k_scalar_beta, dim3(1), dim3(kBlock), 0, st, h->part1,
-                           n_part(h, h->nb1), h->sc);
         if (ev) (void)hipEventRecord(ev[2], st);
         launch_aprod2<T, Acc>(h, P.u, row_map(h), P.q, P.gpart, P.hcols, h->sc, st, P.u,
                               nullptr);
+        glob.ng = 0;
     }
     if (ev) (void)hipEventRecord(ev[3], st);
-    hipLaunchKernelGGL((k_col_a<Acc>), dim3(h->nbc), dim3(kBlock), 0, st, n, h->p, P.q, h->v,
-                       h->sc, h->partc);
-    hipLaunchKernelGGL(k_scalar_alpha, dim3(1), dim3(kBlock), 0, st, h->partc, h->nbc, h->sc);
-    hipLaunchKernelGGL((k_col_b<Acc>), dim3(h->nbc), dim3(kBlock), 0, st, n, h->p, h->v, h->w,
-                       h->y, P.vp, h->sc, h->partdd, h->partxx,
-                       (std::is_same<Acc, double>::value && h->var_on) ? h->var : nullptr);
-    hipLaunchKernelGGL(k_scalar_stop, dim3(1), dim3(kBlock), 0, st, h->partdd, h->partxx, h->nbc,
-                       h->sc);
+    launch_columns<Acc>(h, P, beta, att, ins, glob, st);
+    if (!gated) hipLaunchKernelGGL(k_scalar_stop, dim3(1), dim3(kBlock), 0, st, gate_of(h, true));
+}
+
+// A chunk of iterations, the state current before and after it.
+template <typename T, typename Acc>
+void launch_chunk(lsqr_handle* h, Path<Acc>& P, hipStream_t st, hipEvent_t* ev, int chunk)
+{
+    for (int k = 0; k < chunk; ++k)
+        launch_iteration<T, Acc>(h, P, st, ev ? ev + kEvIter * k : nullptr, k > 0);
+    if (fused_mode(h) != 0)
+        hipLaunchKernelGGL(k_scalar_stop, dim3(1), dim3(kBlock), 0, st, gate_of(h, true));
 }
 
 // Initialisation given u~ (already written, placed by row_map) and ||u~||^2
@@ -679,11 +859,15 @@ void launch_init(lsqr_handle* h, Path<Acc>& P, hipStream_t st)
     hipLaunchKernelGGL((k_fill<double>), dim3(h->nbc), dim3(kBlock), 0, st, n, h->v, 0.0);
     launch_aprod2<T, Acc>(h, P.u, row_map(h), P.q, P.gpart, P.hcols, h->sc, st, P.u,
                           star_order_u(h) ? (const int32_t*)h->perm : nullptr);
-    hipLaunchKernelGGL((k_col_a<Acc>), dim3(h->nbc), dim3(kBlock), 0, st, n, h->p, P.q, h->v,
-                       h->sc, h->partc);
-    hipLaunchKernelGGL(k_scalar_init_alpha, dim3(1), dim3(kBlock), 0, st, h->partc, h->nbc, h->sc);
+    GlobView glob = glob_view(h, P.gpart, 0, 1);
+    glob.ng = 0;  // launch_aprod2 has added every section
+    const int grid = column_grid(h, n, kNoSlices, kNoSlices);
+    hipLaunchKernelGGL((k_col_a<Acc>), dim3(grid), dim3(kBlock), 0, st, n, h->p, P.q, h->v, h->sc,
+                       BetaView{}, kNoSlices, kNoSlices, glob, h->partc);
+    hipLaunchKernelGGL(k_scalar_init_alpha, dim3(1), dim3(kBlock), 0, st, h->partc, grid, h->sc);
     hipLaunchKernelGGL((k_col_init<Acc>), dim3(h->nbc), dim3(kBlock), 0, st, n, h->p, h->v, h->w,
-                       h->y, P.vp, h->sc);
+                       h->y, P.vp, h->sv.natt > 0 ? P.vp3 : nullptr, h->sv.att_base, h->sv.n_dfa,
+                       h->sc);
 }
 
 void batch_free(lsqr_handle* h);
@@ -740,7 +924,7 @@ lsqr_status prepare_path(lsqr_handle* h, Path<Acc>& P)
     // a fused pass that places u~ through the permutation and leaves
     // instrumental tail windows: a star-order copy of u~ for the tails (an
     // optimisation only: without the memory they read u~ through invperm)
-    if (!P.ustar && !P.ustar_tried && use_fused(h) && row_map(h) &&
+    if (!P.ustar && !P.ustar_tried && fused_mode(h) > 0 && row_map(h) && h->sv.ni > 0 &&
         P.f_hcols < h->sv.n_instr_cols) {
         P.ustar_tried = true;
         if (dalloc(&P.ustar, h->sv.m) != LSQR_OK) g_last_error.clear();
@@ -843,7 +1027,24 @@ lsqr_status prepare_att_sorted(lsqr_handle* h)
 lsqr_status ensure_att(lsqr_handle* h)
 {
     if (!att_pass_on(h)) return LSQR_OK;
-    return h->value_type == LSQR_F64 ? prepare_att_sorted<double>(h) : prepare_att_sorted<float>(h);
+    LSQR_TRY(h->value_type == LSQR_F64 ? prepare_att_sorted<double>(h)
+                                       : prepare_att_sorted<float>(h));
+    h->att_locked = true;
+    return LSQR_OK;
+}
+
+// What the single-RHS row passes need: the attitude bucket order, or the
+// slices of the one-pass form.
+lsqr_status ensure_row_order(lsqr_handle* h)
+{
+    if (fused_mode(h) != kOnePass) return ensure_att(h);
+    if (!h->S1) {
+        const int64_t ninst = h->sv.ni > 0 ? h->sv.n_instr_cols : 0;
+        const int64_t natt = h->sv.natt > 0 ? kAxes * h->sv.n_dfa : 0;
+        LSQR_TRY(dalloc(&h->S1, (natt + ninst) * h->nb2));
+    }
+    if (att_pass_on(h)) h->att_locked = true;
+    return LSQR_OK;
 }
 
 // Captured iteration graphs bake in the kernel choices: drop them all (single
@@ -941,7 +1142,7 @@ lsqr_status read_scalars(lsqr_handle* h)
 template <typename T, typename Acc>
 lsqr_status run_iterations(lsqr_handle* h, Path<Acc>& P)
 {
-    h->last_mode = fused_mode(h);
+    h->last_mode = fused_mode(h) == kOnePass ? 2 : fused_mode(h);  // the option's mode
     const int chunk = std::max(1, h->chunk);
     const bool graph = h->use_graph && !h->profile;
     if (graph && (P.graph == nullptr || P.graph_chunk != chunk)) {
@@ -949,7 +1150,7 @@ lsqr_status run_iterations(lsqr_handle* h, Path<Acc>& P)
         P.graph = nullptr;
         hipGraph_t g = nullptr;
         HIP_TRY(hipStreamBeginCapture(h->stream, hipStreamCaptureModeThreadLocal));
-        for (int k = 0; k < chunk; ++k) launch_iteration<T, Acc>(h, P, h->stream, nullptr);
+        launch_chunk<T, Acc>(h, P, h->stream, nullptr, chunk);
         hipError_t e = hipStreamEndCapture(h->stream, &g);
         if (e != hipSuccess) return fail(LSQR_E_HIP, "graph capture: %s", hipGetErrorString(e));
         e = hipGraphInstantiate(&P.graph, g, nullptr, nullptr, 0);
@@ -972,9 +1173,7 @@ lsqr_status run_iterations(lsqr_handle* h, Path<Acc>& P)
         if (graph) {
             HIP_TRY(hipGraphLaunch(P.graph, h->stream));
         } else {
-            for (int k = 0; k < chunk; ++k)
-                launch_iteration<T, Acc>(h, P, h->stream,
-                                         h->profile ? &h->events[kEvIter * k] : nullptr);
+            launch_chunk<T, Acc>(h, P, h->stream, h->profile ? h->events.data() : nullptr, chunk);
             HIP_TRY(hipGetLastError());
         }
         LSQR_TRY(read_scalars(h));
@@ -1022,7 +1221,7 @@ template <typename T>
 lsqr_status solve_fp64(lsqr_handle* h, const double* b, double* x, int32_t itn_limit, double atol,
                        double btol, lsqr_info* info)
 {
-    LSQR_TRY(ensure_att(h));
+    LSQR_TRY(ensure_row_order(h));
     LSQR_TRY(ensure_compact(h));
     LSQR_TRY((prepare_path<T, double>(h, h->p64)));
     Path<double>& P = h->p64;
@@ -1950,14 +2149,14 @@ lsqr_status lsqr_create(const lsqr_system* sys, lsqr_handle** out)
     if ((st = dalloc(&h->w, n)) != LSQR_OK) return bail(st);
     if ((st = dalloc(&h->y, n)) != LSQR_OK) return bail(st);
     if ((st = dalloc(&h->part1, std::max(h->nb1, h->nb2) + 1)) != LSQR_OK) return bail(st);
-    if ((st = dalloc(&h->partc, h->nbc)) != LSQR_OK) return bail(st);
+    if ((st = dalloc(&h->partc, (int64_t)h->num_cu * 4)) != LSQR_OK) return bail(st);
     if ((st = dalloc(&h->partdd, h->nbc)) != LSQR_OK) return bail(st);
     if ((st = dalloc(&h->partxx, h->nbc)) != LSQR_OK) return bail(st);
     if ((st = dalloc(&h->gpart_raw, std::max<int64_t>(h->nb2, (int64_t)h->nba * kGlobMax))) !=
         LSQR_OK)
         return bail(st);
     if ((st = dalloc(&h->flag, 1)) != LSQR_OK) return bail(st);
-    if ((st = dalloc(&h->sc, 1)) != LSQR_OK) return bail(st);
+    if ((st = dalloc(&h->sc, 2)) != LSQR_OK) return bail(st);
     e = hipHostMalloc(reinterpret_cast<void**>(&h->sc_host), sizeof(Scalars), hipHostMallocDefault);
     if (e != hipSuccess) return bail(fail(LSQR_E_NOMEM, "pinned scalars: %s", hipGetErrorString(e)));
     memset(h->sc_host, 0, sizeof(Scalars));
@@ -2034,8 +2233,6 @@ lsqr_status lsqr_create(const lsqr_system* sys, lsqr_handle** out)
                                h->gpart_raw, hc, (const Scalars*)nullptr, (const int32_t*)nullptr);
             launch_instr_tail<float, double, 1, true>(h, nullptr, nullptr, ssq, hc, nullptr, st0);
         }
-        hipLaunchKernelGGL((k_gen_glob_sum<double>), dim3(1), dim3(kBlock), 0, st0, h->gpart_raw,
-                           h->nba, s.ng, ssq + s.glob_base, (const Scalars*)nullptr);
     } else if (h->value_type == LSQR_F64) {
         hipLaunchKernelGGL((k_aprod2<double, double, double, true, true, true, kBlock2>),
                            dim3(h->nb2), dim3(kBlock2), lds, st0, s, (const double*)nullptr, ssq,
@@ -2047,9 +2244,10 @@ lsqr_status lsqr_create(const lsqr_system* sys, lsqr_handle** out)
                            h->wb, h->gpart_raw, hc, (const Scalars*)nullptr);
         launch_instr_tail<float, double, 1, true>(h, nullptr, nullptr, ssq, hc, nullptr, st0);
     }
-    if (!h->generic)
-        hipLaunchKernelGGL((k_glob_sum<double>), dim3(1), dim3(kBlock), 0, st0, h->gpart_raw,
-                           h->nb2, ssq + s.glob_base, (const Scalars*)nullptr);
+    launch_section_sums<double>(h, kNoSlices, kNoSlices,
+                                glob_view(h, h->gpart_raw, h->generic ? h->nba : h->nb2,
+                                          h->generic ? kGlobMax : 1),
+                                ssq, nullptr, st0);
     if (h->nc > 0)
         hipLaunchKernelGGL((k_con_aprod2<double, double, true>), dim3(h->con_grid), dim3(kBlock), 0,
                            st0, h->nc, h->con_rowptr, h->con_col, h->con_val,
@@ -2078,6 +2276,7 @@ lsqr_status lsqr_destroy(lsqr_handle* h)
     dfree(h->invperm);
     dfree(h->bstart);
     dfree(h->S2);
+    dfree(h->S1);
     dfree(h->var);
     dfree(h->x3_raw);
     dfree(h->x3_raw32);
@@ -2158,14 +2357,14 @@ lsqr_status lsqr_set_option(lsqr_handle* h, int32_t option, double value)
         h->ktile = (int)value;
         return LSQR_OK;
     case LSQR_OPT_ATT_RHS:
-        if (h->att_ready)
+        if (h->att_locked)
             return fail(LSQR_E_STATE, "attitude sweep width must be set before the first solve");
         if (!(value == 1.0 || value == 2.0 || value == 4.0 || value == 8.0))
             return fail(LSQR_E_INVALID, "attitude sweep width must be 1, 2, 4 or 8");
         h->att_rhs = (int)value;
         return LSQR_OK;
     case LSQR_OPT_ATT_BUCKETS: {
-        if (h->att_ready)
+        if (h->att_locked)
             return fail(LSQR_E_STATE, "attitude buckets must be set before the first solve");
         if (!(value >= 0.0 && value <= 2147483647.0))
             return fail(LSQR_E_INVALID, "attitude bucket count must be in [0, 2^31)");
@@ -2269,7 +2468,7 @@ lsqr_status lsqr_aprod2(lsqr_handle* h, double* x, const double* y)
 {
     LSQR_TRY(check_handle(h));
     if (!x || !y) return fail(LSQR_E_INVALID, "null vector");
-    LSQR_TRY(ensure_att(h));
+    LSQR_TRY(ensure_row_order(h));
     const int64_t hc = instr_hcols(h, 1);
     // y in row order: the attitude pass (where the bucket order exists:
     // attitude section present, mode 1) reads it through the permutation
@@ -2308,7 +2507,7 @@ lsqr_status lsqr_aprod2_f32(lsqr_handle* h, float* x, const float* y)
     if (!x || !y) return fail(LSQR_E_INVALID, "null vector");
     if (h->value_type != LSQR_F32)
         return fail(LSQR_E_STATE, "lsqr_aprod2_f32 needs an LSQR_F32 system");
-    LSQR_TRY(ensure_att(h));
+    LSQR_TRY(ensure_row_order(h));
     if (!h->gpart_raw32)
         LSQR_TRY(dalloc(&h->gpart_raw32, std::max<int64_t>(h->nb2, (int64_t)h->nba * kGlobMax)));
     const int64_t hc = instr_hcols(h, 1);
@@ -2375,7 +2574,7 @@ lsqr_status lsqr_solve_refined(lsqr_handle* h, const double* b, double* x, int32
     if (!(atol >= 0.0) || !(btol >= 0.0)) return fail(LSQR_E_INVALID, "atol, btol must be >= 0");
     HIP_TRY(hipStreamSynchronize(h->user_stream));
     h->var_valid = 0;
-    LSQR_TRY(ensure_att(h));
+    LSQR_TRY(ensure_row_order(h));
     LSQR_TRY(ensure_compact(h));
     LSQR_TRY((prepare_path<float, float>(h, h->p32)));
     Path<float>& P = h->p32;

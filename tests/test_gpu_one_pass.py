@@ -1,0 +1,139 @@
+"""GPU parity of the one-pass row form (attitude and instrumental histograms
+both in LDS, one sweep over A): Eq. (3) element by element and fixed-iteration
+solves against the oracle, at the edges of its LDS plan, where it gives way to
+the bucket order, and on general layouts. Tolerances as in the full-layout
+parity tests: c eps sum |terms| for the operator, 1e-10 for the iterates.
+"""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+
+EPS = np.finfo(np.float64).eps
+
+# 19,456 FP64 columns fit in the histograms (3 n_dfa + n_instr_cols)
+SPECS = {
+    # everything of the vector in LDS too; fewer rows than one wave
+    "tiny": dict(n_stars=2, obs=(10, 20), n_dfa=5, n_instr_cols=7),
+    "small": dict(n_stars=400, obs=(10, 70), n_dfa=60, n_instr_cols=30),
+    # the vector's instrumental slice beside the histograms, not its attitude
+    "instr_slice": dict(n_stars=400, obs=(40, 90), n_dfa=3500, n_instr_cols=500),
+    # neither
+    "no_slice": dict(n_stars=400, obs=(40, 90), n_dfa=3000, n_instr_cols=10000),
+    # exactly full, and one attitude start more (bucket order, two buckets)
+    "full": dict(n_stars=400, obs=(40, 90), n_dfa=6000, n_instr_cols=1456),
+    "past_full": dict(n_stars=400, obs=(40, 90), n_dfa=6499, n_instr_cols=1456),
+    "no_slice_f32": dict(n_stars=400, obs=(40, 90), n_dfa=3000, n_instr_cols=10000,
+                         value_dtype="f32"),
+    "small_f32": dict(n_stars=400, obs=(10, 70), n_dfa=60, n_instr_cols=30, value_dtype="f32"),
+    # general layouts: no attitude, no global, several globals, one section
+    "no_att": dict(n_stars=300, obs=(10, 70), n_axes=0, n_glob=5),
+    "no_glob": dict(n_stars=300, obs=(10, 70), n_dfa=120, n_instr_cols=23, n_glob=0),
+    "mixed": dict(n_stars=300, obs=(10, 70), n_dfa=120, n_instr_cols=23, n_astro=3, n_instr=2,
+                  n_glob=3),
+    "mixed_f32": dict(n_stars=300, obs=(10, 70), n_dfa=120, n_instr_cols=23, n_astro=4, n_instr=5,
+                      n_glob=1, value_dtype="f32"),
+    "astro_only": dict(n_stars=300, obs=(10, 70), n_axes=0, n_instr=0, n_glob=0),
+    "att_only": dict(n_stars=300, obs=(10, 70), n_dfa=4000, n_astro=0, n_instr=0, n_glob=0),
+    # general layout in bucket order (four buckets)
+    "no_glob_buckets": dict(n_stars=900, obs=(60, 90), n_dfa=20011, n_instr_cols=203, n_glob=0),
+    "mixed_buckets": dict(n_stars=900, obs=(60, 90), n_dfa=7001, n_instr_cols=203, n_astro=3,
+                          n_instr=2, n_glob=3),
+}
+
+_SYS = {}
+
+
+def say(*a):
+    print(*a, flush=True)
+
+
+@pytest.fixture(scope="module")
+def torch_cuda():
+    import torch
+
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch
+
+
+def system(name):
+    if name not in _SYS:
+        S = synth.make_system(synth.tiny(seed=81 + list(SPECS).index(name), **SPECS[name]))
+        _SYS[name] = (S, oracle.OracleSystem.from_synth(S))
+    return _SYS[name]
+
+
+def abs_system(S):
+    sp = S.spec
+    return oracle.OracleSystem(np.abs(S.values.astype(np.float64)), S.star_of_row, S.att_start,
+                               S.instr_idx, n_stars=sp.n_stars, n_dfa=sp.n_dfa,
+                               n_instr_cols=sp.n_instr_cols, n_astro=sp.n_astro,
+                               n_axes=sp.n_axes, n_par_axis=sp.n_par_axis, n_instr=sp.n_instr,
+                               n_glob=sp.n_glob)
+
+
+def gpu_system(S):
+    from paper_2308_00778_amd import LsqrSystem
+
+    return LsqrSystem.from_host(S, "cuda:0")
+
+
+def rel_inf(a, b):
+    return float(np.max(np.abs(a - b)) / np.max(np.abs(b)))
+
+
+@pytest.mark.parametrize("name", list(SPECS))
+def test_one_pass_operators(torch_cuda, name):
+    torch = torch_cuda
+    S, o = system(name)
+    say(f"one-pass operators: {name} m={S.m} n={o.n}")
+    rng = np.random.default_rng(16)
+    y, x0 = rng.standard_normal(o.m), rng.standard_normal(o.n)
+    x, y0 = rng.standard_normal(o.n), rng.standard_normal(o.m)
+    ab = abs_system(S)
+    g = gpu_system(S)
+    yd, xd = torch.from_numpy(y0).cuda(), torch.from_numpy(x0).cuda()
+    g.aprod1(torch.from_numpy(x).cuda(), yd)
+    g.aprod2(xd, torch.from_numpy(y).cuda())
+    torch.cuda.synchronize()
+    got1, got2 = yd.cpu().numpy(), xd.cpu().numpy()
+    g.close()
+    c = 2.0 * np.sqrt(S.m) + 32
+    assert np.all(np.abs(got1 - o.aprod1(x, y0))
+                  <= 32 * EPS * ab.aprod1(np.abs(x), np.abs(y0)) + 1e-300)
+    assert np.all(np.abs(got2 - o.aprod2(y, x0))
+                  <= c * EPS * ab.aprod2(np.abs(y), np.abs(x0)) + 1e-300)
+
+
+# 10 iterations: below the unknown count of every system; graph launches of 4
+# (an iteration's stopping tests inside the next one, and after the last), and
+# single launches
+@pytest.mark.parametrize("graph", [1, 0])
+@pytest.mark.parametrize("name", list(SPECS))
+def test_one_pass_solve(torch_cuda, name, graph):
+    torch = torch_cuda
+    S, o = system(name)
+    itn = 10
+    b = o.aprod1(synth.x_true(S.spec), synth.noise(S.spec, S.m))
+    x_ref, i_ref = o.lsqr(b, itn, atol=0.0, btol=0.0, conlim=0.0, tests=False)
+    say(f"one-pass solve: {name} m={S.m} n={o.n} graph={graph}")
+    g = gpu_system(S)
+    g.set_option("tests", 0)
+    g.set_option("graph", graph)
+    g.set_option("chunk", 4)
+    bd = torch.from_numpy(b).cuda()
+    xs = []
+    for _ in range(2):  # a second solve on the handle's state
+        x, info = g.solve(bd, itn, atol=0.0, btol=0.0)
+        xs.append(x.cpu().numpy())
+        assert info.itn == i_ref.itn == itn and info.istop == 7
+        for k in ("rnorm", "anorm", "acond", "xnorm", "bnorm"):
+            a, r = getattr(info, k), getattr(i_ref, k)
+            assert abs(a - r) <= 1e-8 * abs(r), (k, a, r)
+    g.close()
+    for x in xs:
+        assert rel_inf(x, x_ref) <= 1e-10
