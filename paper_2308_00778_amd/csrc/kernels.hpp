@@ -1083,10 +1083,27 @@ __global__ __launch_bounds__(NT) void k_fused(SysView s, const Acc* __restrict__
         for (int64_t j = threadIdx.x; j < hatt; j += NT) satt[blockIdx.x * hatt + j] = ahist[j];
 }
 
-// Instrumental columns [c0, c1) of Eq. (3) (or of the squared column norms,
-// SQUARE) when the row passes keep only the first columns in LDS: workgroup b
-// sweeps rows [b m / G, (b+1) m / G) with an FP64 LDS histogram of the
-// window, then flushes it with one device atomic per column. U holds K
+// Workgroups that read the same rows (the windows of a section, the sweeps of
+// a k-tile) side by side: block b's part of the rows and its window or sweep
+// (of n), the n of a part next to each other on one accelerator die (block b
+// runs on die b mod 8), where a row read by one of them is found in L2 by the
+// others. One after the other, each reads all rows from memory again.
+constexpr int kDies = 8;
+struct SideBySide {
+    int64_t part;
+    int side;
+};
+__device__ __forceinline__ SideBySide side_by_side(int64_t block, int n)
+{
+    const int64_t k = block / kDies;
+    return {k / n * kDies + block % kDies, (int)(k % n)};
+}
+
+// Instrumental columns [c0, ninst) of Eq. (3) (or of the squared column norms,
+// SQUARE) when the row passes keep only the first columns in LDS, in nw
+// windows of tw columns: a workgroup sweeps one of P parts of the rows with an
+// FP64 LDS histogram of one window (the windows of a part side by side), then
+// flushes it with one device atomic per column. U holds K
 // values per row, row i at U[inv[i] K + r] (U[i K + r] without inv); frozen
 // RHS (done or beta_zero) are skipped.
 // GEN: section sizes from the system view (general layouts); otherwise the
@@ -1094,9 +1111,13 @@ __global__ __launch_bounds__(NT) void k_fused(SysView s, const Acc* __restrict__
 template <typename T, typename Acc, int K, bool SQUARE, int NT, bool GEN, bool PLAIN = false>
 __global__ __launch_bounds__(NT) void k_instr_tail(SysView s, const Acc* __restrict__ U,
                                                     const int32_t* __restrict__ inv,
-                                                    Acc* __restrict__ Q, int64_t c0, int64_t c1,
-                                                    const Scalars* __restrict__ sc)
+                                                    Acc* __restrict__ Q, int64_t cfirst, int64_t tw,
+                                                    int nw, const Scalars* __restrict__ sc)
 {
+    const SideBySide sb = side_by_side(blockIdx.x, nw);
+    const int64_t P = gridDim.x / nw;
+    const int64_t c0 = cfirst + sb.side * tw;
+    const int64_t c1 = c0 + tw < s.n_instr_cols ? c0 + tw : s.n_instr_cols;
     const int ni = GEN ? s.ni : kInstr, oins = GEN ? s.off_instr : kOffInstr;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     double* hist = reinterpret_cast<double*>(smem_raw);
@@ -1115,7 +1136,7 @@ __global__ __launch_bounds__(NT) void k_instr_tail(SysView s, const Acc* __restr
     // (which fetches it twice; also where the caller's columns are not
     // line-aligned)
     static_assert(NT % kWave == 0, "whole waves");
-    const int64_t r0 = blockIdx.x * m / gridDim.x, r1 = (blockIdx.x + 1) * m / gridDim.x;
+    const int64_t r0 = sb.part * m / P, r1 = (sb.part + 1) * m / P;
     constexpr int kW = NT / kWave;
     const int wv = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
     const int64_t rb = r0 + (r1 - r0) * wv / kW, re = r0 + (r1 - r0) * (wv + 1) / kW;
@@ -1922,7 +1943,7 @@ __global__ __launch_bounds__(NT) void k_att_dot(int64_t ld, const T* __restrict_
                                                  const int64_t* __restrict__ bstart,
                                                  int64_t width, int G, int64_t n_dfa,
                                                  const Acc* __restrict__ x3, Acc* __restrict__ u,
-                                                 const Scalars* __restrict__ sc,
+                                                 int64_t slices, const Scalars* __restrict__ sc,
                                                  Gate gate = Gate{})
 {
     static_assert(K % KS == 0, "sweeps of KS right-hand sides cover the tile");
@@ -1931,13 +1952,16 @@ __global__ __launch_bounds__(NT) void k_att_dot(int64_t ld, const T* __restrict_
     __shared__ int32_t gflag;
     Acc* win = reinterpret_cast<Acc*>(smem_raw);
     const int64_t span = width + kParAxis - 1;
-    const int64_t bk = blockIdx.x / G, g = blockIdx.x - bk * G;
+    const SideBySide sb = side_by_side(blockIdx.x, K / KS);
+    if (sb.part >= slices) return;
+    const int64_t bk = sb.part / G, g = sb.part - bk * G;
     const int64_t c0 = bk * width;
     // columns past n_dfa - 1 are never referenced (t + 3 <= n_dfa - 1)
     const int64_t ncol = span < n_dfa - c0 ? span : n_dfa - c0;
     const int64_t b0 = bstart[bk], r1 = bstart[bk + 1];
     const int64_t a0 = b0 & ~(int64_t)(kWave - 1);
-    for (int s0 = 0; s0 < K; s0 += KS) {
+    {
+        const int s0 = sb.side * KS;
         uint32_t live = 0;
         Acc coef[KS];
         if constexpr (!GATED) {
@@ -1946,7 +1970,7 @@ __global__ __launch_bounds__(NT) void k_att_dot(int64_t ld, const T* __restrict_
                 live |= (sc[s0 + j].done ? 0u : 1u) << j;
                 coef[j] = (Acc)sc[s0 + j].coef_u;
             }
-            if (live == 0) continue;  // uniform over the grid
+            if (live == 0) return;  // uniform over the workgroup
         }
         if (KS == K) {
             for (int64_t e = threadIdx.x; e < kAxes * ncol * K; e += NT)
@@ -2057,7 +2081,6 @@ __global__ __launch_bounds__(NT) void k_att_dot(int64_t ld, const T* __restrict_
                 }
             }
         }
-        __syncthreads();  // the next sweep restages the window
     }
 }
 
@@ -2070,8 +2093,9 @@ __global__ __launch_bounds__(NT) void k_att_dot(int64_t ld, const T* __restrict_
 // histogram and S2 are FP64 whatever Acc is: gfx950's LDS FP64 atomic add
 // runs at 7.6x the rate of the FP32 one (measured, random addresses over
 // 150 KB: 1550 vs 204 G/s), and the sums are more accurate. U is in bucket
-// order ([m][K]); K / KS sweeps cover the tile. Frozen RHS (done or
-// beta_zero) are skipped. GATHER: U is in star order instead, and the row at
+// order ([m][K]); the K / KS sweeps of a tile are workgroups side by side (one sweep
+// after the other read every row from memory K / KS times; slices = nbk G).
+// Frozen RHS (done or beta_zero) are skipped. GATHER: U is in star order instead, and the row at
 // bucket position k is read at U[perm[k]] (a read through the permutation,
 // whose targets form one increasing run per bucket).
 // PIPE: each thread issues the loads of its next row before the atomics of
@@ -2085,7 +2109,7 @@ __global__ __launch_bounds__(NT) void k_att_hist(int64_t ld, const T* __restrict
                                                   const int32_t* __restrict__ tloc,
                                                   const int64_t* __restrict__ bstart,
                                                   int64_t width, int G, const Acc* __restrict__ U,
-                                                  double* __restrict__ S2,
+                                                  double* __restrict__ S2, int64_t slices,
                                                   const Scalars* __restrict__ sc,
                                                   const int32_t* __restrict__ perm = nullptr)
 {
@@ -2093,15 +2117,18 @@ __global__ __launch_bounds__(NT) void k_att_hist(int64_t ld, const T* __restrict
     extern __shared__ __align__(16) unsigned char smem_raw[];
     double* hist = reinterpret_cast<double*>(smem_raw);
     const int64_t span = width + kParAxis - 1;
-    const int64_t bk = blockIdx.x / G, g = blockIdx.x - bk * G;
+    const SideBySide sb = side_by_side(blockIdx.x, K / KS);
+    if (sb.part >= slices) return;
+    const int64_t bk = sb.part / G, g = sb.part - bk * G;
     const int64_t b0 = bstart[bk], r1 = bstart[bk + 1];
     const int64_t a0 = b0 & ~(int64_t)(kWave - 1);
-    for (int s0 = 0; s0 < K; s0 += KS) {
+    {
+        const int s0 = sb.side * KS;
         uint32_t live = 0;
 #pragma unroll
         for (int j = 0; j < KS; ++j)
             live |= (sc != nullptr && (sc[s0 + j].done || sc[s0 + j].beta_zero) ? 0u : 1u) << j;
-        if (live == 0) continue;  // uniform over the grid
+        if (live == 0) return;  // uniform over the workgroup
         for (int64_t e = threadIdx.x; e < kAxes * span * KS; e += NT) hist[e] = 0.0;
         __syncthreads();
         constexpr int kAtt = kAxes * kParAxis;
@@ -2194,10 +2221,9 @@ __global__ __launch_bounds__(NT) void k_att_hist(int64_t ld, const T* __restrict
         __syncthreads();
         for (int j = 0; j < KS; ++j) {
             if (!((live >> j) & 1u)) continue;
-            double* out = S2 + ((int64_t)blockIdx.x * K + s0 + j) * kAxes * span;
+            double* out = S2 + (sb.part * K + s0 + j) * kAxes * span;
             for (int64_t e = threadIdx.x; e < kAxes * span; e += NT) out[e] = hist[e * KS + j];
         }
-        __syncthreads();
     }
 }
 

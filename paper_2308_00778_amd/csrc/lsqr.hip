@@ -367,6 +367,17 @@ constexpr int kEvIter = 5;  // profile events per single-RHS iteration
 inline int64_t att_slices(const lsqr_handle* h) { return h->nbk * h->att_g; }
 
 // ------------------------------------------------------------ launch helpers
+// Calls f with std::true_type or std::false_type for the flag.
+template <typename F>
+void by_flag(bool a, F&& f)
+{
+    if (a) f(std::true_type());
+    else f(std::false_type());
+}
+
+// Blocks of a kernel whose n workgroups per part run side by side.
+inline int64_t side_grid(int64_t parts, int n) { return cdiv(parts, kDies) * kDies * n; }
+
 // Instrumental columns a row pass keeps in its FP64 LDS histogram for K
 // right-hand sides; the remaining columns go to k_instr_tail windows.
 inline int64_t instr_hcols(const lsqr_handle* h, int64_t K)
@@ -375,8 +386,8 @@ inline int64_t instr_hcols(const lsqr_handle* h, int64_t K)
     return std::min<int64_t>(h->sv.n_instr_cols, kLdsInstrBudget / (8 * K));
 }
 
-// Tail windows [hcols, n_instr_cols) of the instrumental part of Eq. (3), one
-// launch per window of kLdsInstrBudget bytes (nothing when hcols covers all).
+// Tail windows of kLdsInstrBudget bytes over [hcols, n_instr_cols) of the
+// instrumental part of Eq. (3), in one launch (nothing when hcols covers all).
 template <typename T, typename Acc, int K, bool SQUARE>
 void launch_instr_tail(const lsqr_handle* h, const Acc* U, const int32_t* inv, Acc* Q,
                        int64_t hcols, const Scalars* sc, hipStream_t st)
@@ -387,24 +398,17 @@ void launch_instr_tail(const lsqr_handle* h, const Acc* U, const int32_t* inv, A
     const uintptr_t vb = (uintptr_t)h->sv.val, ib = (uintptr_t)h->sv.instr;
     const bool lined = vb % 128 == 0 && ib % 128 == 0 &&
                        (h->sv.m * (int64_t)sizeof(T)) % 128 == 0 && (h->sv.m * 4) % 128 == 0;
-    for (int64_t c0 = hcols; c0 < ninst; c0 += tw) {
-        const int64_t c1 = std::min(ninst, c0 + tw);
-        auto go = [&](auto gen, auto plain) {
-            hipLaunchKernelGGL((k_instr_tail<T, Acc, K, SQUARE, kAttBlock, decltype(gen)::value,
-                                             decltype(plain)::value>),
-                               dim3(h->num_cu), dim3(kAttBlock), (size_t)((c1 - c0) * K * 8), st,
-                               h->sv, U, inv, Q, c0, c1, sc);
-        };
-        using Y = std::true_type;
-        using N = std::false_type;
-        if (h->generic) {
-            if (lined) go(Y(), N());
-            else go(Y(), Y());
-        } else {
-            if (lined) go(N(), N());
-            else go(N(), Y());
-        }
-    }
+    if (hcols >= ninst) return;
+    const int64_t nw = cdiv(ninst - hcols, tw), wide = std::min(tw, ninst - hcols);
+    // parts of the rows: one workgroup (a window of one part) per compute unit
+    const int64_t parts = std::max<int64_t>(1, h->num_cu / (nw * kDies)) * kDies;
+    auto go = [&](auto gen, auto plain) {
+        hipLaunchKernelGGL((k_instr_tail<T, Acc, K, SQUARE, kAttBlock, decltype(gen)::value,
+                                         decltype(plain)::value>),
+                           dim3(parts * nw), dim3(kAttBlock), (size_t)(wide * K * 8), st, h->sv, U,
+                           inv, Q, hcols, tw, (int)nw, sc);
+    };
+    by_flag(h->generic, [&](auto gen) { by_flag(!lined, [&](auto plain) { go(gen, plain); }); });
 }
 
 // LDS of a fused pass over K right-hand sides: the FP64 histogram of the
@@ -508,14 +512,6 @@ inline Gate gate_of(const lsqr_handle* h, bool pending)
     return {pending ? h->sc + 1 : nullptr, h->sc, h->partdd, h->partxx, h->nbc};
 }
 
-// Calls f with std::true_type or std::false_type for each flag.
-template <typename F>
-void by_flag(bool a, F&& f)
-{
-    if (a) f(std::true_type());
-    else f(std::false_type());
-}
-
 // The fused pass (aprod1 and the astrometric, instrumental and global part of
 // aprod2 in one sweep) over the main-pass grid.
 template <typename T, typename Acc, bool LDSX, int AM, int GEN = 0>
@@ -577,10 +573,12 @@ template <typename T, typename Acc, bool SEP, bool PIPE>
 void launch_att_dot_as(const lsqr_handle* h, Path<Acc>& P, const Gate& gate, hipStream_t st)
 {
     const size_t lds = (size_t)(kAxes * att_span(h)) * sizeof(Acc);
-    hipLaunchKernelGGL((k_att_dot<T, Acc, 1, 1, kAttBlock, SEP, PIPE, true>), dim3(att_slices(h)),
+    hipLaunchKernelGGL((k_att_dot<T, Acc, 1, 1, kAttBlock, SEP, PIPE, true>),
+                       dim3(side_grid(att_slices(h), 1)),
                        dim3(kAttBlock), lds, st, h->att_ld, (const T*)h->att_sorted,
                        (const int32_t*)h->tloc, (const int64_t*)h->bstart, h->bwidth, h->att_g,
-                       h->sv.n_dfa, (const Acc*)P.vp3, SEP ? P.datt : P.u, (const Scalars*)nullptr,
+                       h->sv.n_dfa, (const Acc*)P.vp3, SEP ? P.datt : P.u, att_slices(h),
+                       (const Scalars*)nullptr,
                        gate);
 }
 
@@ -718,9 +716,10 @@ void launch_att_pass(lsqr_handle* h, const Acc* ub, const Scalars* sc, hipStream
     auto go = [&](auto gather, auto pipe) {
         hipLaunchKernelGGL((k_att_hist<T, Acc, 1, 1, kAttBlock, decltype(gather)::value,
                                        decltype(pipe)::value>),
-                           dim3(att_slices(h)), dim3(kAttBlock), lds, st, h->att_ld,
+                           dim3(side_grid(att_slices(h), 1)), dim3(kAttBlock), lds, st, h->att_ld,
                            (const T*)h->att_sorted, (const int32_t*)h->tloc,
-                           (const int64_t*)h->bstart, h->bwidth, h->att_g, ub, h->S2, sc, gperm);
+                           (const int64_t*)h->bstart, h->bwidth, h->att_g, ub, h->S2,
+                           att_slices(h), sc, gperm);
     };
     using Y = std::true_type;
     using N = std::false_type;
@@ -1442,11 +1441,12 @@ void batch_att_pass(lsqr_handle* h, hipStream_t st)
     // buckets: one 4-RHS sweep 6.3 ms, two 2-RHS sweeps 2 x 2.15 ms)
     const int ks = std::min(2, att_sweep<K>(h));
     by_sweep<K>(ks, [&](auto KS) {
-        hipLaunchKernelGGL((k_att_hist<T, Acc, K, KS(), kAttBlock>), dim3(att_slices(h)),
+        hipLaunchKernelGGL((k_att_hist<T, Acc, K, KS(), kAttBlock>),
+                           dim3(side_grid(att_slices(h), K / KS())),
                            dim3(kAttBlock), (size_t)(kAxes * att_span(h) * 8 * ks), st, h->att_ld,
                            (const T*)h->att_sorted, (const int32_t*)h->tloc,
                            (const int64_t*)h->bstart, h->bwidth, h->att_g, (const Acc*)tb.U,
-                           B.S2, B.sc, (const int32_t*)nullptr);
+                           B.S2, att_slices(h), B.sc, (const int32_t*)nullptr);
     });
     launch_slice_reduce<Acc, K>(h, att_slice_view(h, B.S2), tb.Q, B.sc, st);
 }
@@ -1553,11 +1553,12 @@ void batch_fused(lsqr_handle* h, hipStream_t st)
     if (pre) {
         const int ks = att_sweep<K>(h, (int64_t)sizeof(Acc));
         by_sweep<K>(ks, [&](auto KS) {
-            hipLaunchKernelGGL((k_att_dot<T, Acc, K, KS(), kAttBlock>), dim3(att_slices(h)),
+            hipLaunchKernelGGL((k_att_dot<T, Acc, K, KS(), kAttBlock>),
+                               dim3(side_grid(att_slices(h), K / KS())),
                                dim3(kAttBlock), (size_t)(kAxes * att_span(h) * sizeof(Acc) * ks),
                                st, h->att_ld, (const T*)h->att_sorted, (const int32_t*)h->tloc,
                                (const int64_t*)h->bstart, h->bwidth, h->att_g, h->sv.n_dfa, X3,
-                               tb.U, (const Scalars*)B.sc);
+                               tb.U, att_slices(h), (const Scalars*)B.sc);
         });
         if (ldsx) batch_fused_as<T, Acc, K, true, kAttPre>(h, nullptr, hc, lds, st);
         else batch_fused_as<T, Acc, K, false, kAttPre>(h, nullptr, hc, lds, st);
