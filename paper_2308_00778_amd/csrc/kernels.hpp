@@ -944,10 +944,18 @@ __global__ __launch_bounds__(NT) void k_fused(SysView s, const Acc* __restrict__
 #pragma unroll
     for (int g = 0; g < NG; ++g) gsum[g] = (Acc)0;
     SegAcc<Acc, kAstro> seg;
+    // A star's rows belong to one wave and its columns of q are zero here (the
+    // column kernel leaves them so), so a step stores its sums; an addition
+    // would make the wave wait for its loads, and with them for every load
+    // issued before (loads return in issue order), at each end of a star.
     auto astro_emit = [=](int64_t star, const Acc (&tot)[kAstro]) {
 #pragma unroll
         for (int j = 0; j < kAstro; ++j)
-            if (!GEN || j < na) q[(int64_t)na * star + j] += tot[j];
+            if (!GEN || j < na) {
+                Acc* dst = &q[(int64_t)na * star + j];
+                if (A2) *dst += tot[j];
+                else *dst = tot[j];
+            }
     };
 
     // 64-row aligned chunks, as in k_aprod2; lanes outside [rb, re) compute on
@@ -2715,7 +2723,10 @@ __global__ __launch_bounds__(NT) void k_fused(SysView s, const Acc* __restrict__
     auto astro_emit = [Q](int64_t star, const Acc (&tot)[kAstro * K]) {
         Acc* dst = Q + kAstro * star * K;
 #pragma unroll
-        for (int j = 0; j < kAstro * K; ++j) dst[j] += tot[j];
+        for (int j = 0; j < kAstro * K; ++j) {
+            if (kChunkFlush) dst[j] += tot[j];  // a star in several pieces
+            else dst[j] = tot[j];
+        }
     };
     for (int64_t r0 = rb < re ? (rb & ~(int64_t)(kWave - 1)) : re; r0 < re; r0 += kWave) {
         const int64_t i = r0 + lane;
@@ -3059,7 +3070,10 @@ __global__ __launch_bounds__(NT) void k_fused_rl(SysView s, const Acc* __restric
     auto astro_emit = [Q, lane](int64_t star, const Acc (&tot)[kAstro]) {
         Acc* dst = Q + kAstro * star * K + lane;
 #pragma unroll
-        for (int j = 0; j < kAstro; ++j) dst[j * K] += tot[j];
+        for (int j = 0; j < kAstro; ++j) {
+            if (A2) dst[j * K] += tot[j];
+            else dst[j * K] = tot[j];  // as in the single-RHS pass
+        }
     };
     // one R-row step: the row of slot `slot` (clamped), its coefficients,
     // indices, star and place in U already loaded
