@@ -129,6 +129,23 @@ __device__ __forceinline__ T ld_stream(const T* p)
         return ldnt(p);
 }
 
+// base[i], i small and per lane, base the same over the wave (in scalar
+// registers): the address takes one vector register, not two per column.
+template <bool PLAIN = false, typename T>
+__device__ __forceinline__ T ld_off(const T* base, uint32_t i)
+{
+    return ld_stream<PLAIN>(reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) +
+                                                       (uint32_t)(i * sizeof(T))));
+}
+
+// A value that is the same over the wave, moved to scalar registers.
+__device__ __forceinline__ int32_t uniform(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ int64_t uniform(int64_t v)
+{
+    const int32_t lo = uniform((int32_t)v), hi = uniform((int32_t)(v >> 32));
+    return (int64_t)(uint32_t)lo | ((int64_t)hi << 32);
+}
+
 // ---------------------------------------------------------------- reductions
 // Deterministic block sum of one double per thread; result valid on thread 0.
 __device__ __forceinline__ double block_sum(double v, double* lds /* >= kWavesPerBlock */)
@@ -1147,33 +1164,88 @@ __global__ __launch_bounds__(NT) void k_instr_tail(SysView s, const Acc* __restr
     const int64_t r0 = sb.part * m / P, r1 = (sb.part + 1) * m / P;
     constexpr int kW = NT / kWave;
     const int wv = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
-    const int64_t rb = r0 + (r1 - r0) * wv / kW, re = r0 + (r1 - r0) * (wv + 1) / kW;
-    for (int64_t i0 = rb & ~(int64_t)(kWave - 1); i0 < re; i0 += kWave) {
-        const int64_t i = i0 + lane;
-        if (i < rb || i >= re) continue;
+    const int64_t rb = uniform(r0 + (r1 - r0) * wv / kW);
+    const int64_t re = uniform(r0 + (r1 - r0) * (wv + 1) / kW);
+    // Steps in flight: the streams of the step two ahead are loaded after the
+    // current step's values of U have been asked for (one step before they are
+    // used), so a step waits neither for memory nor for the permuted read it
+    // addresses. Lanes outside [rb, re) repeat a row of the range with weight 0.
+    struct Step {
         int32_t ix[kInstr];
         T a[kInstr];
+        int32_t pu;
+    };
+    auto load = [&](Step& st, int64_t i0) {
+        // the step's first row (of the range, once past its end) and the lane's
+        // row from there
+        const int64_t base = i0 < re ? i0 : re - 1;
+        const int64_t k = base + lane;
+        const uint32_t o = (uint32_t)((k < rb ? rb : (k < re ? k : re - 1)) - base);
 #pragma unroll
         for (int j = 0; j < kInstr; ++j) {
-            ix[j] = j < ni ? ld_stream<PLAIN>(&s.instr[j * m + i]) : -1;
-            a[j] = j < ni ? ld_stream<PLAIN>(&val[(oins + j) * m + i]) : (T)0;
+            st.ix[j] = j < ni ? ld_off<PLAIN>(&s.instr[j * m + base], o) : -1;
+            st.a[j] = j < ni ? ld_off<PLAIN>(&val[(oins + j) * m + base], o) : (T)0;
         }
-        double u[K];
-        if (!SQUARE) {
-            const int64_t pu = inv ? (int64_t)ldnt(&inv[i]) : i;
+        st.pu = inv ? ld_off(&inv[base], o) : (int32_t)(base + o - rb);
+    };
+    auto value = [&](const Step& st, Acc (&u)[K]) {
+        if (SQUARE) return;
+        const Acc* up = U + (inv ? (int64_t)st.pu : rb + st.pu) * K;
 #pragma unroll
-            for (int r = 0; r < K; ++r) u[r] = ((live >> r) & 1u) ? (double)U[pu * K + r] : 0.0;
-        }
+        for (int r = 0; r < K; ++r) u[r] = up[r];
+    };
+    auto scatter = [&](const Step& st, const Acc (&u)[K], int64_t i0) {
+        const int64_t k = i0 + lane;
+        if (k < rb || k >= re) return;
 #pragma unroll
         for (int j = 0; j < kInstr; ++j) {
-            const int64_t c = (int64_t)ix[j] - c0;
-            if (c < 0 || c >= w) continue;
+            const uint32_t c = (uint32_t)(st.ix[j] - (int32_t)c0);  // < 2^31: n_instr_cols
+            if (c >= (uint32_t)w) continue;
 #pragma unroll
             for (int r = 0; r < K; ++r) {
                 if (!((live >> r) & 1u)) continue;
-                const double av = (double)(Acc)a[j];
-                atomicAdd(&hist[c * K + r], SQUARE ? av * av : (double)((Acc)a[j] * (Acc)u[r]));
+                const double av = (double)(Acc)st.a[j];
+                atomicAdd(&hist[c * K + r], SQUARE ? av * av : (double)((Acc)st.a[j] * u[r]));
             }
+        }
+    };
+    const int64_t istart = rb & ~(int64_t)(kWave - 1);
+    if constexpr (K <= 4) {
+        if (rb < re) {
+            Step A, B, C;
+            Acc ua[K], ub[K];
+            int64_t i0 = istart;
+            load(A, i0);
+            load(B, i0 + kWave);
+            value(A, ua);
+            // step(cur, its U, next, next's U, the buffer two ahead)
+            auto step = [&](const Step& cur, const Acc (&uc)[K], const Step& nxt, Acc (&un)[K],
+                            Step& far) {
+                value(nxt, un);
+                __builtin_amdgcn_sched_barrier(0);
+                load(far, i0 + 2 * kWave);
+                __builtin_amdgcn_sched_barrier(0);
+                scatter(cur, uc, i0);
+                __builtin_amdgcn_sched_barrier(0);
+                i0 += kWave;
+                return i0 < re;
+            };
+            for (;;) {  // six steps: three buffers of rows, two of U
+                if (!step(A, ua, B, ub, C)) break;
+                if (!step(B, ub, C, ua, A)) break;
+                if (!step(C, ua, A, ub, B)) break;
+                if (!step(A, ub, B, ua, C)) break;
+                if (!step(B, ua, C, ub, A)) break;
+                if (!step(C, ub, A, ua, B)) break;
+            }
+        }
+    } else {  // more right-hand sides: their registers leave no room for it
+        for (int64_t i0 = istart; i0 < re; i0 += kWave) {
+            Step A;
+            Acc ua[K];
+            load(A, i0);
+            value(A, ua);
+            scatter(A, ua, i0);
         }
     }
     __syncthreads();
@@ -1944,8 +2016,8 @@ __global__ __launch_bounds__(kBlock) void k_att_gather(const T* __restrict__ val
 // not.
 // GATED (single right-hand side): the pass makes the previous iteration's
 // stopping tests first (Gate); otherwise sc holds the K current states.
-template <typename T, typename Acc, int K, int KS, int NT, bool SEP = false, bool PIPE = (K == 1),
-          bool GATED = false>
+template <typename T, typename Acc, int K, int KS, int NT, bool SEP = false,
+          bool PIPE = (KS * sizeof(Acc) <= 8), bool GATED = false>
 __global__ __launch_bounds__(NT) void k_att_dot(int64_t ld, const T* __restrict__ att_sorted,
                                                  const int32_t* __restrict__ tloc,
                                                  const int64_t* __restrict__ bstart,
@@ -2112,7 +2184,7 @@ __global__ __launch_bounds__(NT) void k_att_dot(int64_t ld, const T* __restrict_
 // att_sorted and the row blocks as in k_att_dot (64-row aligned; lanes below
 // the bucket's first row load that row with a zero weight).
 template <typename T, typename Acc, int K, int KS, int NT, bool GATHER = false,
-          bool PIPE = (K == 1)>
+          bool PIPE = (KS <= 2)>
 __global__ __launch_bounds__(NT) void k_att_hist(int64_t ld, const T* __restrict__ att_sorted,
                                                   const int32_t* __restrict__ tloc,
                                                   const int64_t* __restrict__ bstart,
