@@ -80,20 +80,6 @@ struct SysView {
     const uint16_t* instr16;  // [kInstr][m]
 };
 
-// Star and instrumental index of row ic, from the compact copies when CIDX.
-template <bool CIDX>
-__device__ __forceinline__ int64_t star_of(const SysView& s, int64_t ic)
-{
-    return CIDX ? (int64_t)__builtin_nontemporal_load(&s.star32[ic])
-                : __builtin_nontemporal_load(&s.star[ic]);
-}
-template <bool CIDX>
-__device__ __forceinline__ int32_t instr_of(const SysView& s, int j, int64_t ic)
-{
-    return CIDX ? (int32_t)__builtin_nontemporal_load(&s.instr16[j * s.m + ic])
-                : __builtin_nontemporal_load(&s.instr[j * s.m + ic]);
-}
-
 // LSQR state kept on the device so that a whole iteration runs without a
 // host round trip (and can be captured into a graph).
 struct Scalars {
@@ -144,6 +130,19 @@ __device__ __forceinline__ int64_t uniform(int64_t v)
 {
     const int32_t lo = uniform((int32_t)v), hi = uniform((int32_t)(v >> 32));
     return (int64_t)(uint32_t)lo | ((int64_t)hi << 32);
+}
+
+// Star and instrumental index of row ic, from the compact copies when CIDX.
+template <bool CIDX, bool PLAIN = false>
+__device__ __forceinline__ int64_t star_of(const SysView& s, int64_t ic)
+{
+    return CIDX ? (int64_t)ld_stream<PLAIN>(&s.star32[ic]) : ld_stream<PLAIN>(&s.star[ic]);
+}
+template <bool CIDX, bool PLAIN = false>
+__device__ __forceinline__ int32_t instr_of(const SysView& s, int j, int64_t ic)
+{
+    return CIDX ? (int32_t)ld_stream<PLAIN>(&s.instr16[j * s.m + ic])
+                : ld_stream<PLAIN>(&s.instr[j * s.m + ic]);
 }
 
 // ---------------------------------------------------------------- reductions
@@ -906,6 +905,7 @@ __global__ __launch_bounds__(NT) void k_fused(SysView s, const Acc* __restrict__
                                                double* __restrict__ sins = nullptr)
 {
     constexpr bool kNoAtt = AM == kAttPre || AM == kAttGather;
+    constexpr bool kPlain = AM == kAttAll;
     constexpr int kAtt = kAxes * kParAxis;
     constexpr int NG = GEN ? GEN : 1;
     constexpr int W = NT / kWave;
@@ -981,28 +981,28 @@ __global__ __launch_bounds__(NT) void k_fused(SysView s, const Acc* __restrict__
         const int64_t i = r0 + lane;
         const bool ok = i >= rb && i < re;
         const int64_t ic = i < rb ? rb : (i < re ? i : re - 1);
-        const int64_t stc = star_of<CIDX>(s, ic);
+        const int64_t stc = star_of<CIDX, kPlain>(s, ic);
         const int64_t st = i < re ? stc : kNoStar;
-        const int64_t t = att ? ldnt(&s.att[ic]) : 0;
+        const int64_t t = att ? ld_stream<kPlain>(&s.att[ic]) : 0;
         T aa[kAstro], at[kAtt], ai[kInstr], ag[NG];
         int32_t ix[kInstr];
 #pragma unroll
         for (int j = 0; j < kAstro; ++j)
-            aa[j] = !GEN || j < na ? ldnt(&val[j * m + ic]) : (T)0;
+            aa[j] = !GEN || j < na ? ld_stream<kPlain>(&val[j * m + ic]) : (T)0;
         if (!kNoAtt) {
             if (att) {
 #pragma unroll
-                for (int c = 0; c < kAtt; ++c) at[c] = ldnt(&val[(oatt + c) * m + ic]);
+                for (int c = 0; c < kAtt; ++c) at[c] = ld_stream<kPlain>(&val[(oatt + c) * m + ic]);
             }
         }
 #pragma unroll
         for (int j = 0; j < kInstr; ++j)
-            ai[j] = !GEN || j < ni ? ldnt(&val[(oins + j) * m + ic]) : (T)0;
+            ai[j] = !GEN || j < ni ? ld_stream<kPlain>(&val[(oins + j) * m + ic]) : (T)0;
 #pragma unroll
         for (int g = 0; g < NG; ++g)
-            ag[g] = !GEN || g < ng ? ldnt(&val[(oglob + g) * m + ic]) : (T)0;
+            ag[g] = !GEN || g < ng ? ld_stream<kPlain>(&val[(oglob + g) * m + ic]) : (T)0;
 #pragma unroll
-        for (int j = 0; j < kInstr; ++j) ix[j] = !GEN || j < ni ? instr_of<CIDX>(s, j, ic) : 0;
+        for (int j = 0; j < kInstr; ++j) ix[j] = !GEN || j < ni ? instr_of<CIDX, kPlain>(s, j, ic) : 0;
         const int64_t pu = (AM != kAttGather && inv) ? (int64_t)ldnt(&inv[ic]) : ic;
         const Acc dg = AM == kAttGather ? datt[ldnt(&inv[ic])] : (Acc)0;
         const Acc uo = u[pu];
