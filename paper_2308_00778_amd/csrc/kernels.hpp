@@ -1205,7 +1205,8 @@ __global__ __launch_bounds__(NT) void k_instr_tail(SysView s, const Acc* __restr
             for (int r = 0; r < K; ++r) {
                 if (!((live >> r) & 1u)) continue;
                 const double av = (double)(Acc)st.a[j];
-                atomicAdd(&hist[c * K + r], SQUARE ? av * av : (double)((Acc)st.a[j] * u[r]));
+                atomicAdd(&hist[r * (uint32_t)w + c],
+                          SQUARE ? av * av : (double)((Acc)st.a[j] * u[r]));
             }
         }
     };
@@ -1250,8 +1251,9 @@ __global__ __launch_bounds__(NT) void k_instr_tail(SysView s, const Acc* __restr
     }
     __syncthreads();
     Acc* __restrict__ qins = Q + (s.instr_base + c0) * K;
-    for (int64_t e = threadIdx.x; e < w * K; e += NT) {
-        const double v = hist[e];
+    for (int32_t e = threadIdx.x; e < (int32_t)w * K; e += NT) {
+        const int32_t c = e / K, r = e - c * K;  // one plane per right-hand side (k_att_dot)
+        const double v = hist[r * (int32_t)w + c];
         if (v != 0.0) atomicAdd(&qins[e], (Acc)v);
     }
 }
@@ -1997,8 +1999,10 @@ __global__ __launch_bounds__(kBlock) void k_att_gather(const T* __restrict__ val
 // sides (u~ [m][K] row-interleaved, x3 [3 n_dfa][K]). The G workgroups of a
 // bucket share its rows as in k_att_hist; the bucket's attitude columns
 // [b W, b W + W + 3) of the interleaved copy x3 are staged in LDS first
-// (win[(3 c + axis) KS + j], 3 (W + 3) KS Acc), so no row gathers from global
-// memory. KS right-hand sides share one sweep over the rows (one window each);
+// (win[j][3 c + axis], 3 (W + 3) KS Acc), so no row gathers from global
+// memory. One plane per right-hand side: with the KS values of a column
+// together, the random columns of a wave share 1/KS of the LDS banks (1e7 rows,
+// 4 right-hand sides: 84% of the LDS cycles were conflicts). KS right-hand sides share one sweep over the rows (one window each);
 // K / KS sweeps cover the tile. Frozen RHS (done) keep u~. The fused pass
 // (kAttPre) then adds the other sections. SEP: u is a separate bucket-order
 // vector that receives the attitude part alone (u[k] <- sum_c a_c x[col_c],
@@ -2052,14 +2056,10 @@ __global__ __launch_bounds__(NT) void k_att_dot(int64_t ld, const T* __restrict_
             }
             if (live == 0) return;  // uniform over the workgroup
         }
-        if (KS == K) {
-            for (int64_t e = threadIdx.x; e < kAxes * ncol * K; e += NT)
-                win[e] = x3[kAxes * c0 * K + e];
-        } else {
-            for (int64_t e = threadIdx.x; e < kAxes * ncol * KS; e += NT) {
-                const int64_t col = e / KS;
-                win[e] = x3[(kAxes * c0 + col) * K + s0 + (e - col * KS)];
-            }
+        const int32_t plane = (int32_t)(kAxes * span);
+        for (int32_t e = threadIdx.x; e < (int32_t)(kAxes * ncol) * KS; e += NT) {
+            const int32_t col = e / KS, j = e - col * KS;
+            win[j * plane + col] = x3[(kAxes * c0 + col) * K + s0 + j];
         }
         if constexpr (GATED) {  // beside the window's loads
             double cf = 0.0;
@@ -2078,9 +2078,9 @@ __global__ __launch_bounds__(NT) void k_att_dot(int64_t ld, const T* __restrict_
 #pragma unroll
                 for (int qq = 0; qq < kParAxis; ++qq) {
                     const Acc av = (Acc)a[ax * kParAxis + qq];
-                    const Acc* w = win + (kAxes * (tl + qq) + ax) * KS;
+                    const Acc* w = win + (kAxes * ((int32_t)tl + qq) + ax);
 #pragma unroll
-                    for (int j = 0; j < KS; ++j) d[j] += av * w[j];
+                    for (int j = 0; j < KS; ++j) d[j] += av * w[j * plane];
                 }
         };
         const int64_t stride = (int64_t)G * NT;
@@ -2167,7 +2167,7 @@ __global__ __launch_bounds__(NT) void k_att_dot(int64_t ld, const T* __restrict_
 // Attitude part of Eq. (3) over the rows in bucket order. The G workgroups
 // of bucket b share its rows in interleaved blocks of NT (workgroup w = b G +
 // g takes blocks g, g + G, ..., so the G streams advance through memory
-// together): an LDS histogram hist[axis][W + 3][KS] gets a * u for the 12
+// together): an LDS histogram hist[KS][axis][W + 3] gets a * u for the 12
 // coefficients of each of its rows and the KS right-hand sides of one sweep,
 // then is stored as S2[w][r][axis][W + 3]; k_slice_reduce adds the slices. The
 // histogram and S2 are FP64 whatever Acc is: gfx950's LDS FP64 atomic add
@@ -2220,7 +2220,7 @@ __global__ __launch_bounds__(NT) void k_att_hist(int64_t ld, const T* __restrict
 #pragma unroll
                     for (int j = 0; j < KS; ++j)
                         if ((live >> j) & 1u)
-                            atomicAdd(&hist[(ax * span + tl + qq) * KS + j],
+                            atomicAdd(&hist[(j * kAxes + ax) * (int32_t)span + (int32_t)tl + qq],
                                       (double)a[ax * kParAxis + qq] * uk[j]);
         };
         const int64_t stride = (int64_t)G * NT;
@@ -2302,7 +2302,7 @@ __global__ __launch_bounds__(NT) void k_att_hist(int64_t ld, const T* __restrict
         for (int j = 0; j < KS; ++j) {
             if (!((live >> j) & 1u)) continue;
             double* out = S2 + (sb.part * K + s0 + j) * kAxes * span;
-            for (int64_t e = threadIdx.x; e < kAxes * span; e += NT) out[e] = hist[e * KS + j];
+            for (int64_t e = threadIdx.x; e < kAxes * span; e += NT) out[e] = hist[j * kAxes * span + e];
         }
     }
 }
