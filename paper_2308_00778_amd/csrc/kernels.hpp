@@ -429,6 +429,7 @@ template <int NT>
 __device__ __forceinline__ bool gate_open(const Gate& G, double* red, int32_t* flag, double* coef)
 {
     if (G.B == nullptr) {
+        if (G.A == nullptr) return true;  // an operator, outside a solve
         *coef = G.A->coef_u;
         return G.A->done == 0;
     }
@@ -464,53 +465,7 @@ __global__ __launch_bounds__(kBlock) void k_scalar_stop(Gate gate)
 }
 
 // ------------------------------------------------------------------- aprod 1
-// Eq. (2) for one row: sum over the 24 coefficients in section order.
-// xi: the instrumental slice of x (x + instr_base, or its copy in LDS).
-// x3 (ATTI): the attitude section interleaved by axis,
-// x3[3 c + axis] = x[att_base + axis * n_dfa + c], so that the 12 attitude
-// values of a row (columns t..t+3 of the three axes) are 12 consecutive
-// elements: about 1.7 cache lines per row instead of 3.6 for three separate
-// 4-value windows, with the same footprint.
-template <typename T, typename Acc, typename VX, bool ATTI = false>
-__device__ __forceinline__ Acc row_dot(const SysView& s, const VX* __restrict__ x,
-                                       const VX* __restrict__ xi, int64_t i,
-                                       const VX* __restrict__ x3 = nullptr)
-{
-    const T* __restrict__ val = static_cast<const T*>(s.val);
-    const int64_t m = s.m;
-    const int64_t st = ldnt(&s.star[i]);
-    const int64_t t = ldnt(&s.att[i]);
-    T a[kPar];
-#pragma unroll
-    for (int c = 0; c < kPar; ++c) a[c] = ldnt(&val[c * m + i]);
-    int32_t ic[kInstr];
-#pragma unroll
-    for (int j = 0; j < kInstr; ++j) ic[j] = ldnt(&s.instr[j * m + i]);
-
-    Acc sum = 0;
-    const VX* xa = x + kAstro * st;
-#pragma unroll
-    for (int j = 0; j < kAstro; ++j) sum += (Acc)a[j] * (Acc)xa[j];
-#pragma unroll
-    for (int ax = 0; ax < kAxes; ++ax) {
-        VX xv[kParAxis];
-        if (ATTI) {
-            const VX* xt = x3 + kAxes * t + ax;
-#pragma unroll
-            for (int q = 0; q < kParAxis; ++q) xv[q] = xt[kAxes * q];
-        } else {
-            const VX* xt = x + s.att_base + ax * s.n_dfa + t;
-#pragma unroll
-            for (int q = 0; q < kParAxis; ++q) xv[q] = xt[q];
-        }
-#pragma unroll
-        for (int q = 0; q < kParAxis; ++q) sum += (Acc)a[kOffAtt + ax * kParAxis + q] * (Acc)xv[q];
-    }
-#pragma unroll
-    for (int j = 0; j < kInstr; ++j) sum += (Acc)a[kOffInstr + j] * (Acc)xi[ic[j]];
-    sum += (Acc)a[kOffGlob] * (Acc)x[s.glob_base];
-    return sum;
-}
+constexpr int kGlobMax = 5;  // global columns of a general layout
 
 enum Aprod1Mode : int {
     A1_ACCUM = 0,  // y += A x
@@ -518,56 +473,165 @@ enum Aprod1Mode : int {
     A1_RESID = 2,  // y = b - A x
 };
 
-// part[blockIdx.x] receives the FP64 sum of squares of the stored y (LSQR,
-// RESID modes). NT threads per block. LDSX: the instrumental slice of x
-// (n_instr_cols values) is first copied into LDS, so that the six random
-// instrumental gathers per row hit LDS instead of L2.
+// Where Eq. (2) reads the attitude values of a row (columns t..t+3 of the three
+// axes): three windows of x; 12 consecutive elements of x3, the section
+// interleaved by axis (x3[3 c + axis] = x[att_base + axis n_dfa + c]: about 1.7
+// cache lines per row instead of 3.6); such a copy that the workgroup makes
+// in LDS; or nowhere: k_att_dot has left every row's attitude part in datt, in
+// bucket order (row i at datt[place[i]]).
+enum Aprod1Att : int { kWindows = 0, kInterleaved = 1, kStaged = 2, kPrepass = 3 };
+
+// Eq. (2): 64-row steps over the grid's waves, one row per lane; part[blockIdx.x]
+// receives the FP64 sum of squares of the stored y (LSQR, RESID). LDSX: the
+// instrumental slice of x (n_instr_cols values) is first copied into LDS, so
+// that the six random instrumental gathers per row hit LDS instead of L2.
 // inv (optional, LSQR and RESID modes): placement of the row vector, the value
 // of row i lives at y[inv[i]] (the attitude-bucket order of the solver's work
-// vector); nullptr: y[i].
-template <typename T, typename Acc, typename VX, typename VY, int MODE, int NT = kBlock,
-          bool LDSX = false, bool ATTI = false>
+// vector); nullptr: y[i]. GEN: section sizes from the system view.
+// A step's coefficients, then the gathers that its indices address, then the
+// next step's indices go out together, one round trip a step at 16 waves a
+// compute unit. What bounds it with attitude gathers is their requests (12
+// values at a random place per row, 1.7 lines; 1.5e7 rows, 1e5 starts: 1.05 ms,
+// 3.5 TB/s, whatever the schedule), hence the pre-pass form.
+template <typename T, typename Acc, typename VX, typename VY, int MODE, int NT, bool LDSX, int XA,
+          bool GEN = false>
 __global__ __launch_bounds__(NT) void k_aprod1(SysView s, const VX* __restrict__ x,
                                                 VY* __restrict__ y, const double* __restrict__ b,
                                                 const Scalars* __restrict__ sc,
                                                 double* __restrict__ part,
-                                                const int32_t* __restrict__ inv = nullptr,
-                                                const VX* __restrict__ x3 = nullptr)
+                                                const int32_t* __restrict__ inv,
+                                                const VX* __restrict__ x3,
+                                                const Acc* __restrict__ datt,
+                                                const int32_t* __restrict__ place)
 {
+    constexpr int kAtt = kAxes * kParAxis, W = NT / kWave, NG = GEN ? kGlobMax : 1;
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    __shared__ double red[NT / kWave];
+    __shared__ double red[W];
     if (MODE == A1_LSQR && sc->done) return;
+    const T* __restrict__ val = static_cast<const T*>(s.val);
+    const int64_t m = s.m;
+    const int na = GEN ? s.na : kAstro, ni = GEN ? s.ni : kInstr, ng = GEN ? s.ng : 1;
+    const bool att = XA != kPrepass && (!GEN || s.natt > 0);
+    const int oatt = GEN ? s.off_att : kOffAtt, oins = GEN ? s.off_instr : kOffInstr,
+              oglob = GEN ? s.off_glob : kOffGlob;
+    // inv, if given, is place in the pre-pass form
+    const int32_t* __restrict__ pl = XA == kPrepass ? place : (MODE != A1_ACCUM ? inv : nullptr);
+
+    const int lane = threadIdx.x & (kWave - 1);
+    const int32_t wave = uniform((int32_t)(blockIdx.x * W + threadIdx.x / kWave));
+    const int64_t stride = (int64_t)gridDim.x * NT;
+    struct Idx {
+        int64_t star;
+        int32_t t, place, ix[kInstr];
+    };
+    auto lane_off = [&](int64_t r0) {  // the lane's row, the last one past the end
+        return (uint32_t)(lane < m - r0 ? lane : m - 1 - r0);
+    };
+    auto load_idx = [&](Idx& w, int64_t r0) {
+        const int64_t base = r0 < m ? r0 : m - 1;
+        const uint32_t o = r0 < m ? lane_off(r0) : 0u;
+        w.star = na > 0 ? ld_off(&s.star[base], o) : 0;
+        if (att) w.t = ld_off(reinterpret_cast<const int32_t*>(&s.att[base]), 2 * o);
+        if (pl) w.place = ld_off(&pl[base], o);
+#pragma unroll
+        for (int j = 0; j < kInstr; ++j)
+            w.ix[j] = !GEN || j < ni ? ld_off(&s.instr[j * m + base], o) : 0;
+    };
+    Idx nx = {};
+    int64_t r0 = (int64_t)wave * kWave;
+    if (r0 < m) load_idx(nx, r0);
+
     const VX* xi = x + s.instr_base;
+    const VX* xw = x3;
     if (LDSX) {
         VX* xl = reinterpret_cast<VX*>(smem_raw);
         for (int64_t j = threadIdx.x; j < s.n_instr_cols; j += NT) xl[j] = xi[j];
-        __syncthreads();
         xi = xl;
+        if (XA == kStaged) {
+            VX* wl = xl + s.n_instr_cols;
+            const VX* xa = x + s.att_base;
+            for (int ax = 0; ax < kAxes; ++ax)
+                for (int64_t c = threadIdx.x; c < s.n_dfa; c += NT)
+                    wl[kAxes * c + ax] = xa[ax * s.n_dfa + c];
+            xw = wl;
+        }
+        __syncthreads();
     }
     const Acc coef = (MODE == A1_LSQR) ? (Acc)sc->coef_u : (Acc)0;
-    const int64_t stride = (int64_t)gridDim.x * NT;
+    Acc xg[NG];
+#pragma unroll
+    for (int g = 0; g < NG; ++g) xg[g] = g < ng ? (Acc)x[s.glob_base + g] : (Acc)0;
+    auto att_value = [&](int32_t t, int e) {
+        const int ax = e / kParAxis, qq = e % kParAxis;
+        return XA == kWindows  ? x[s.att_base + ax * s.n_dfa + t + qq]
+               : XA == kStaged ? xw[kAxes * (t + qq) + ax]
+                               : xw[kAxes * (int64_t)(t + qq) + ax];
+    };
+
     double ssq = 0.0;
-    for (int64_t i0 = (int64_t)blockIdx.x * NT + threadIdx.x; i0 < s.m; i0 += 2 * stride) {
-        const int64_t i1 = i0 + stride;
-        const bool has1 = i1 < s.m;
-        const int64_t i1c = has1 ? i1 : i0;
-        const Acc d0 = row_dot<T, Acc, VX, ATTI>(s, x, xi, i0, x3);
-        const Acc d1 = row_dot<T, Acc, VX, ATTI>(s, x, xi, i1c, x3);
-        if (MODE == A1_ACCUM) {
-            y[i0] = (VY)((Acc)y[i0] + d0);
-            if (has1) y[i1] = (VY)((Acc)y[i1] + d1);
-        } else {
-            const int64_t p0 = inv ? (int64_t)ldnt(&inv[i0]) : i0;
-            const VY n0 = MODE == A1_LSQR ? (VY)(d0 - coef * (Acc)y[p0]) : (VY)((Acc)b[i0] - d0);
-            y[p0] = n0;
-            ssq += (double)n0 * (double)n0;
-            if (has1) {
-                const int64_t p1 = inv ? (int64_t)ldnt(&inv[i1]) : i1;
-                const VY n1 =
-                    MODE == A1_LSQR ? (VY)(d1 - coef * (Acc)y[p1]) : (VY)((Acc)b[i1] - d1);
-                y[p1] = n1;
-                ssq += (double)n1 * (double)n1;
-            }
+    for (; r0 < m; r0 += stride) {
+        const uint32_t o = lane_off(r0);
+        const bool ok = lane < m - r0;
+        T aa[kAstro], at[kAtt], ai[kInstr], ag[NG];
+#pragma unroll
+        for (int j = 0; j < kAstro; ++j)
+            aa[j] = !GEN || j < na ? ld_off(&val[j * m + r0], o) : (T)0;
+        if (att) {
+#pragma unroll
+            for (int c = 0; c < kAtt; ++c) at[c] = ld_off(&val[(oatt + c) * m + r0], o);
+        }
+#pragma unroll
+        for (int j = 0; j < kInstr; ++j)
+            ai[j] = !GEN || j < ni ? ld_off(&val[(oins + j) * m + r0], o) : (T)0;
+#pragma unroll
+        for (int g = 0; g < NG; ++g)
+            ag[g] = !GEN || g < ng ? ld_off(&val[(oglob + g) * m + r0], o) : (T)0;
+        __builtin_amdgcn_sched_barrier(0);
+        const Idx id = nx;
+        VY* yp = (MODE != A1_ACCUM && inv) ? &y[id.place] : &y[r0 + o];
+        const VY yo = MODE == A1_RESID ? (VY)0 : *yp;
+        const Acc da = XA == kPrepass ? datt[id.place] : (Acc)0;
+        const double bo = MODE == A1_RESID ? b[r0 + o] : 0.0;
+        VX xs[kAstro], xt[kAtt], xv[kInstr];
+        const VX* xa = x + (int64_t)na * id.star;
+#pragma unroll
+        for (int j = 0; j < kAstro; ++j)
+            if (!GEN || j < na) xs[j] = xa[j];
+        if (XA != kStaged && att) {
+#pragma unroll
+            for (int e = 0; e < kAtt; ++e) xt[e] = att_value(id.t, e);
+        }
+        if (!LDSX) {
+#pragma unroll
+            for (int j = 0; j < kInstr; ++j)
+                if (!GEN || j < ni) xv[j] = xi[id.ix[j]];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        load_idx(nx, r0 + stride);
+        __builtin_amdgcn_sched_barrier(0);
+
+        Acc d = (Acc)0;  // in section order
+#pragma unroll
+        for (int j = 0; j < kAstro; ++j)
+            if (!GEN || j < na) d += (Acc)aa[j] * (Acc)xs[j];
+        if (att) {
+#pragma unroll
+            for (int e = 0; e < kAtt; ++e)
+                d += (Acc)at[e] * (Acc)(XA == kStaged ? att_value(id.t, e) : xt[e]);
+        }
+#pragma unroll
+        for (int j = 0; j < kInstr; ++j)
+            if (!GEN || j < ni) d += (Acc)ai[j] * (Acc)(LDSX ? xi[id.ix[j]] : xv[j]);
+#pragma unroll
+        for (int g = 0; g < NG; ++g)
+            if (!GEN || g < ng) d += (Acc)ag[g] * xg[g];
+        if (XA == kPrepass) d += da;
+        const VY nv = MODE == A1_ACCUM  ? (VY)((Acc)yo + d)
+                      : MODE == A1_LSQR ? (VY)(d - coef * (Acc)yo)
+                                        : (VY)((Acc)bo - d);
+        if (ok) {
+            *yp = nv;
+            if (MODE != A1_ACCUM) ssq += (double)nv * (double)nv;
         }
     }
     if (MODE != A1_ACCUM) {
@@ -889,8 +953,6 @@ __global__ __launch_bounds__(NT) void k_aprod2(SysView s, const VU* __restrict__
 // global columns: five of them cost 20 registers more); the loads stay unrolled,
 // each under a uniform test. A2: Eq. (3) alone, u unchanged.
 enum { kAttX = 0, kAttX3 = 1, kAttPre = 2, kAttGather = 3, kAttAll = 4 };
-constexpr int kGlobMax = 5;  // global columns of a general layout
-
 template <typename T, typename Acc, int NT, bool LDSX, int AM, bool CIDX, int GEN = 0,
           bool WIN = false, bool A2 = false>
 __global__ __launch_bounds__(NT) void k_fused(SysView s, const Acc* __restrict__ x,
@@ -1264,57 +1326,6 @@ __global__ __launch_bounds__(NT) void k_instr_tail(SysView s, const Acc* __restr
 // section sizes and value-row offsets come from the system view at run time,
 // aprod1 and aprod2 run as separate passes, and the attitude columns go
 // through the bucket-order pass (or device atomics) as in the full layout.
-
-// Eq. (2) for a general layout; modes, y placement (inv) and part as k_aprod1.
-template <typename T, typename Acc, typename VX, typename VY, int MODE>
-__global__ __launch_bounds__(kBlock) void k_gen_aprod1(SysView s, const VX* __restrict__ x,
-                                                        VY* __restrict__ y,
-                                                        const double* __restrict__ b,
-                                                        const Scalars* __restrict__ sc,
-                                                        double* __restrict__ part,
-                                                        const int32_t* __restrict__ inv)
-{
-    __shared__ double red[kWavesPerBlock];
-    if (MODE == A1_LSQR && sc->done) return;
-    const T* __restrict__ val = static_cast<const T*>(s.val);
-    const int64_t m = s.m;
-    const Acc coef = (MODE == A1_LSQR) ? (Acc)sc->coef_u : (Acc)0;
-    double ssq = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < m;
-         i += (int64_t)gridDim.x * kBlock) {
-        Acc d = (Acc)0;
-        if (s.na > 0) {
-            const VX* xa = x + (int64_t)s.na * ldnt(&s.star[i]);
-            for (int j = 0; j < s.na; ++j) d += (Acc)ldnt(&val[j * m + i]) * (Acc)xa[j];
-        }
-        if (s.natt > 0) {
-            const int64_t t = ldnt(&s.att[i]);
-#pragma unroll
-            for (int ax = 0; ax < kAxes; ++ax)
-#pragma unroll
-                for (int qq = 0; qq < kParAxis; ++qq)
-                    d += (Acc)ldnt(&val[(s.off_att + ax * kParAxis + qq) * m + i]) *
-                         (Acc)x[s.att_base + ax * s.n_dfa + t + qq];
-        }
-        for (int j = 0; j < s.ni; ++j)
-            d += (Acc)ldnt(&val[(s.off_instr + j) * m + i]) *
-                 (Acc)x[s.instr_base + ldnt(&s.instr[j * m + i])];
-        for (int g = 0; g < s.ng; ++g)
-            d += (Acc)ldnt(&val[(s.off_glob + g) * m + i]) * (Acc)x[s.glob_base + g];
-        if (MODE == A1_ACCUM) {
-            y[i] = (VY)((Acc)y[i] + d);
-        } else {
-            const int64_t p = inv ? (int64_t)ldnt(&inv[i]) : i;
-            const VY nv = MODE == A1_LSQR ? (VY)(d - coef * (Acc)y[p]) : (VY)((Acc)b[i] - d);
-            y[p] = nv;
-            ssq += (double)nv * (double)nv;
-        }
-    }
-    if (MODE != A1_ACCUM) {
-        const double r = block_sum(ssq, red);
-        if (threadIdx.x == 0) part[blockIdx.x] = r;
-    }
-}
 
 // Eq. (3) (SQUARE: squared coefficients, the column norms) for a general
 // layout over the star-aligned wave ranges: astrometric per-star segments,

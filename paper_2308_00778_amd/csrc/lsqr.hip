@@ -111,8 +111,7 @@ inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // bytes of LDS for the instrumental histogram of aprod2 (gfx950 allows 160 KB
 // per workgroup; a little is kept for the static arrays)
 constexpr int64_t kLdsInstrBudget = 152 * 1024;
-constexpr int64_t kLdsXBudget = 64 * 1024;      // bytes of LDS for aprod1's instrumental slice
-constexpr int kBlock1 = 512;                    // aprod1 workgroup size
+constexpr int kBlock1 = 512;                    // k-tile workgroups with 256 registers a lane
 constexpr int kBlock2 = 1024;                   // aprod2 main-pass workgroup size
 constexpr int kWavesPerCU = 16;                 // row ranges per compute unit in aprod2
 // Rows per block of the two-level attitude sort: the block's slice of an FP64
@@ -161,6 +160,7 @@ struct lsqr_handle {
     hipStream_t stream = nullptr;       // solves (capturable, owned)
 
     int nb1 = 0;  // aprod1 grid
+    int nbr = 0;  // grid of the other row kernels (256 threads)
     int64_t nw = 0;  // star-aligned row ranges of aprod2, one per wave (multiple of 16)
     int nb2 = 0;     // aprod2 main-pass grid: nw / 16 workgroups of 1024 threads
     int nba = 0;     // reordered attitude pass grid: nw / 4 workgroups of 256 threads
@@ -171,7 +171,7 @@ struct lsqr_handle {
     double* v = nullptr;    // [n]
     double* w = nullptr;    // [n]
     double* y = nullptr;    // [n] iterate in the scaled space
-    double* part1 = nullptr;                    // [max(nb1, nb2) + 1]
+    double* part1 = nullptr;                    // [max(nb1, nb2, nbr) + 1]
     double* partc = nullptr;                    // [4 CUs]
     double* partdd = nullptr;                   // [nbc]
     double* partxx = nullptr;                   // [nbc]
@@ -207,6 +207,8 @@ struct lsqr_handle {
     double* S2 = nullptr;         // [nbk att_g][3][W + 3] slices of the attitude pass
     double* x3_raw = nullptr;     // interleaved attitude section of lsqr_aprod1's x
     float* x3_raw32 = nullptr;    // the same for lsqr_aprod1_f32
+    double* datt_raw = nullptr;   // [m] attitude parts of the operators' rows, bucket order
+    float* datt_raw32 = nullptr;
     float* gpart_raw32 = nullptr; // global-column partials of lsqr_aprod2_f32
     bool att_ready = false;
     bool att_locked = false;      // a solve or aprod2 has run: the bucket options are settled
@@ -464,38 +466,61 @@ void launch_con_aprod2(const lsqr_handle* h, const VU* u, Acc* q, const Scalars*
                        h->nc, h->con_rowptr, h->con_col, h->con_val, u, q, sc);
 }
 
+// aprod1's workgroups stage the attitude section of x in LDS themselves (no
+// interleaved copy is made) where it fits beside the instrumental slice and is
+// no more than 1/4 of the rows' own bytes: every workgroup reads all of it.
+inline bool aprod1_staged(const lsqr_handle* h, int64_t vbytes)
+{
+    if (!h->att_il || h->sv.natt == 0 || h->generic) return false;
+    const int64_t bytes = (h->sv.n_instr_cols + kAxes * h->sv.n_dfa) * vbytes;
+    return bytes <= kLdsInstrBudget && 4 * bytes * h->nb1 <= 200 * h->sv.m;
+}
+
 // aprod1 with the instrumental slice of x staged in LDS when it fits.
 // x3 (optional): interleaved attitude section of x, already written
-// (k_interleave_att).
+// (k_interleave_att). datt (optional): the rows' attitude parts
+// (launch_att_part).
 // inv (optional): placement of y (row i at y[inv[i]]). Constraint rows follow
 // at y[m..] (b[m..]), their ||u||^2 share at part[nb1].
 template <typename T, typename Acc, typename VX, typename VY, int MODE>
 void launch_aprod1(const lsqr_handle* h, const VX* x, VY* y, const double* b, const Scalars* sc,
                    double* part, hipStream_t st, const int32_t* inv = nullptr,
-                   const VX* x3 = nullptr)
+                   const VX* x3 = nullptr, const Acc* datt = nullptr)
 {
     const int64_t m = h->sv.m;
     launch_con_aprod1<Acc, VX, VY, MODE>(h, x, y + m, b ? b + m : nullptr, sc,
                                          part ? part + h->nb1 : nullptr, st);
+    const int64_t xb = h->sv.ni > 0 ? h->sv.n_instr_cols * (int64_t)sizeof(VX) : 0;
+    auto go = [&](auto ldsx, auto xa, auto gen, int64_t lds) {
+        hipLaunchKernelGGL((k_aprod1<T, Acc, VX, VY, MODE, kBlock2, decltype(ldsx)::value,
+                                     decltype(xa)::value, decltype(gen)::value>),
+                           dim3(h->nb1), dim3(kBlock2), (size_t)lds, st, h->sv, x, y, b, sc, part,
+                           inv, x3, datt, (const int32_t*)h->invperm);
+    };
+    using Y = std::true_type;
+    using N = std::false_type;
+    using Win = std::integral_constant<int, kWindows>;
+    using Inter = std::integral_constant<int, kInterleaved>;
+    using Staged = std::integral_constant<int, kStaged>;
+    const bool ldsx = xb <= kLdsInstrBudget;  // one workgroup per compute unit
     if (h->generic) {  // any layout: runtime section sizes
-        hipLaunchKernelGGL((k_gen_aprod1<T, Acc, VX, VY, MODE>), dim3(h->nb1), dim3(kBlock), 0, st,
-                           h->sv, x, y, b, sc, part, inv);
-        return;
+        if (ldsx && h->sv.ni > 0) go(Y(), Win(), Y(), xb);
+        else go(N(), Win(), Y(), 0);
+    } else if (datt) {
+        using Pre = std::integral_constant<int, kPrepass>;
+        if constexpr (MODE != A1_LSQR) {
+            if (ldsx) go(Y(), Pre(), N(), xb);
+            else go(N(), Pre(), N(), 0);
+        }
+    } else if (aprod1_staged(h, (int64_t)sizeof(VX))) {
+        go(Y(), Staged(), N(), xb + kAxes * h->sv.n_dfa * (int64_t)sizeof(VX));
+    } else if (x3) {
+        if (ldsx) go(Y(), Inter(), N(), xb);
+        else go(N(), Inter(), N(), 0);
+    } else {
+        if (ldsx) go(Y(), Win(), N(), xb);
+        else go(N(), Win(), N(), 0);
     }
-    const int64_t bytes = h->sv.n_instr_cols * (int64_t)sizeof(VX);
-    const dim3 g(h->nb1), b1(kBlock1);
-    if (bytes <= kLdsXBudget && x3)
-        hipLaunchKernelGGL((k_aprod1<T, Acc, VX, VY, MODE, kBlock1, true, true>), g, b1,
-                           (size_t)bytes, st, h->sv, x, y, b, sc, part, inv, x3);
-    else if (bytes <= kLdsXBudget)
-        hipLaunchKernelGGL((k_aprod1<T, Acc, VX, VY, MODE, kBlock1, true, false>), g, b1,
-                           (size_t)bytes, st, h->sv, x, y, b, sc, part, inv, x3);
-    else if (x3)
-        hipLaunchKernelGGL((k_aprod1<T, Acc, VX, VY, MODE, kBlock1, false, true>), g, b1, 0, st,
-                           h->sv, x, y, b, sc, part, inv, x3);
-    else
-        hipLaunchKernelGGL((k_aprod1<T, Acc, VX, VY, MODE, kBlock1, false, false>), g, b1, 0, st,
-                           h->sv, x, y, b, sc, part, inv, x3);
 }
 
 template <typename V>
@@ -590,6 +615,18 @@ void launch_att_dot(const lsqr_handle* h, Path<Acc>& P, const Gate& gate, hipStr
             launch_att_dot_as<T, Acc, decltype(sep)::value, decltype(pipe)::value>(h, P, gate, st);
         });
     });
+}
+
+// Attitude part of Eq. (2) outside the iterations, into datt (bucket order).
+template <typename T, typename Acc>
+void launch_att_part(const lsqr_handle* h, const Acc* x3, Acc* datt, hipStream_t st)
+{
+    hipLaunchKernelGGL((k_att_dot<T, Acc, 1, 1, kAttBlock, true, true, true>),
+                       dim3(side_grid(att_slices(h), 1)), dim3(kAttBlock),
+                       (size_t)(kAxes * att_span(h)) * sizeof(Acc), st, h->att_ld,
+                       (const T*)h->att_sorted, (const int32_t*)h->tloc,
+                       (const int64_t*)h->bstart, h->bwidth, h->att_g, h->sv.n_dfa, x3, datt,
+                       att_slices(h), (const Scalars*)nullptr, Gate{});
 }
 
 // pre: the attitude part of the row products is already in u~ (fused mode 2)
@@ -846,14 +883,13 @@ void launch_chunk(lsqr_handle* h, Path<Acc>& P, hipStream_t st, hipEvent_t* ev, 
         hipLaunchKernelGGL(k_scalar_stop, dim3(1), dim3(kBlock), 0, st, gate_of(h, true));
 }
 
-// Initialisation given u~ (already written, placed by row_map) and ||u~||^2
-// partials in part1.
+// Initialisation given u~ (already written, placed by row_map) and npart
+// partials of ||u~||^2 in part1.
 template <typename T, typename Acc>
-void launch_init(lsqr_handle* h, Path<Acc>& P, hipStream_t st)
+void launch_init(lsqr_handle* h, Path<Acc>& P, int npart, hipStream_t st)
 {
     const int64_t n = h->sv.n;
-    hipLaunchKernelGGL(k_scalar_init_beta, dim3(1), dim3(kBlock), 0, st, h->part1,
-                       n_part(h, h->nb1), h->sc);
+    hipLaunchKernelGGL(k_scalar_init_beta, dim3(1), dim3(kBlock), 0, st, h->part1, npart, h->sc);
     hipLaunchKernelGGL((k_fill<Acc>), dim3(h->nbc), dim3(kBlock), 0, st, n, P.q, (Acc)0);
     hipLaunchKernelGGL((k_fill<double>), dim3(h->nbc), dim3(kBlock), 0, st, n, h->v, 0.0);
     launch_aprod2<T, Acc>(h, P.u, row_map(h), P.q, P.gpart, P.hcols, h->sc, st, P.u,
@@ -872,6 +908,13 @@ void launch_init(lsqr_handle* h, Path<Acc>& P, hipStream_t st)
 void batch_free(lsqr_handle* h);
 template <typename Acc>
 void release_path(Path<Acc>& P);
+
+// The operators' scratch (a later operator allocates it again).
+void release_datt(lsqr_handle* h)
+{
+    dfree(h->datt_raw);
+    dfree(h->datt_raw32);
+}
 
 template <typename Acc>
 lsqr_status path_alloc(lsqr_handle* h, Path<Acc>& P)
@@ -897,6 +940,7 @@ lsqr_status prepare_path(lsqr_handle* h, Path<Acc>& P)
         if (rc == LSQR_E_NOMEM) {
             release_path(P);
             batch_free(h);
+            release_datt(h);
             g_last_error.clear();
             rc = path_alloc(h, P);
         }
@@ -1236,12 +1280,12 @@ lsqr_status solve_fp64(lsqr_handle* h, const double* b, double* x, int32_t itn_l
         hipLaunchKernelGGL((k_fill<double>), dim3(h->nbc), dim3(kBlock), 0, h->stream, n, h->var,
                            0.0);
     }
-    hipLaunchKernelGGL((k_copy_ssq<double>), dim3(h->nb1), dim3(kBlock), 0, h->stream, m, b, P.u,
+    hipLaunchKernelGGL((k_copy_ssq<double>), dim3(h->nbr), dim3(kBlock), 0, h->stream, m, b, P.u,
                        h->part1, row_map(h));
     if (h->nc > 0)  // constraint rows: after the observation rows, one partial
         hipLaunchKernelGGL((k_copy_ssq<double>), dim3(1), dim3(kBlock), 0, h->stream, h->nc, b + m,
-                           P.u + m, h->part1 + h->nb1, (const int32_t*)nullptr);
-    launch_init<T, double>(h, P, h->stream);
+                           P.u + m, h->part1 + h->nbr, (const int32_t*)nullptr);
+    launch_init<T, double>(h, P, n_part(h, h->nbr), h->stream);
     HIP_TRY(hipGetLastError());
     LSQR_TRY(read_scalars(h));
     if (!h->sc_host->done && itn_limit > 0) LSQR_TRY((run_iterations<T, double>(h, P)));
@@ -1281,7 +1325,7 @@ lsqr_status batch_alloc_once(lsqr_handle* h, int kmax, bool want64, bool want32)
     LSQR_TRY(dalloc(&B.W, n * kmax));
     LSQR_TRY(dalloc(&B.Y, n * kmax));
     LSQR_TRY(dalloc(&B.gpart, (int64_t)h->nba * kmax));
-    LSQR_TRY(dalloc(&B.part1, (int64_t)std::max(h->nb1, h->nba) * kmax));
+    LSQR_TRY(dalloc(&B.part1, (int64_t)std::max(h->nbr, h->nba) * kmax));
     LSQR_TRY(dalloc(&B.partc, (int64_t)h->nbc * kmax));
     LSQR_TRY(dalloc(&B.partdd, (int64_t)h->nbc * kmax));
     LSQR_TRY(dalloc(&B.partxx, (int64_t)h->nbc * kmax));
@@ -1342,6 +1386,7 @@ lsqr_status batch_alloc(lsqr_handle* h, int kmax, bool fp32)
         batch_free(h);
         release_path(h->p64);
         release_path(h->p32);
+        release_datt(h);
         g_last_error.clear();
         rc = batch_alloc_once(h, kmax, !fp32, fp32);
     }
@@ -1595,11 +1640,11 @@ void batch_iteration(lsqr_handle* h, hipStream_t st, hipEvent_t* ev)
                            tb.Q + h->sv.glob_base * K, B.sc);
         batch_att_pass<T, Acc, K>(h, st);
     } else if constexpr (K <= 8) {
-        hipLaunchKernelGGL((batched::k_aprod1<T, Acc, K>), dim3(h->nb1), dim3(kBlock), 0, st,
+        hipLaunchKernelGGL((batched::k_aprod1<T, Acc, K>), dim3(h->nbr), dim3(kBlock), 0, st,
                            h->sv, (const Acc*)tb.VP, tb.U, B.sc, B.part1, batch_row_map(h));
         if (ev) (void)hipEventRecord(ev[1], st);
         hipLaunchKernelGGL((batched::k_scalar_beta<K>), dim3(1), dim3(kBlock), 0, st, B.part1,
-                           h->nb1, B.sc);
+                           h->nbr, B.sc);
         if (ev) (void)hipEventRecord(ev[2], st);
         batch_aprod2<T, Acc, K>(h, st);
     }
@@ -1638,7 +1683,7 @@ lsqr_status batch_controls(lsqr_handle* h, int32_t itn_limit, double atol, doubl
 }
 
 // Start of a tile's LSQR given U (placed by batch_row_map) and its sums of
-// squares in part1 (h->nb1 partials): beta_1, alpha_1 v_1 = Abar^T u_1, w, y.
+// squares in part1 (h->nbr partials): beta_1, alpha_1 v_1 = Abar^T u_1, w, y.
 template <typename T, typename Acc, int K>
 lsqr_status batch_init(lsqr_handle* h)
 {
@@ -1647,7 +1692,7 @@ lsqr_status batch_init(lsqr_handle* h)
     hipStream_t st = h->stream;
     const int64_t n = h->sv.n;
     hipLaunchKernelGGL((batched::k_scalar_init_beta<K>), dim3(1), dim3(kBlock), 0, st, B.part1,
-                       h->nb1, B.sc);
+                       h->nbr, B.sc);
     hipLaunchKernelGGL((k_fill<Acc>), dim3(h->nbc), dim3(kBlock), 0, st, n * K, tb.Q, (Acc)0);
     hipLaunchKernelGGL((k_fill<double>), dim3(h->nbc), dim3(kBlock), 0, st, n * K, B.V, 0.0);
     batch_aprod2<T, Acc, K>(h, st);
@@ -1759,7 +1804,7 @@ lsqr_status batch_tile(lsqr_handle* h, const double* Bm, int64_t ldb, double* X,
     hipStream_t st = h->stream;
     const int64_t m = h->sv.m, n = h->sv.n;
     LSQR_TRY(batch_controls<K>(h, itn_limit, atol, btol));
-    hipLaunchKernelGGL((batched::k_copy_ssq<double, K>), dim3(h->nb1), dim3(kBlock), 0, st, m, Bm,
+    hipLaunchKernelGGL((batched::k_copy_ssq<double, K>), dim3(h->nbr), dim3(kBlock), 0, st, m, Bm,
                        ldb, B.U, B.part1, batch_row_map(h));
     LSQR_TRY((batch_init<T, double, K>(h)));
     Scalars host[kMaxTile];
@@ -1816,12 +1861,12 @@ lsqr_status batch_refined_tile(lsqr_handle* h, const double* Bm, int64_t ldb, do
         // FP64 residual of the full problem of every live RHS (B itself at the
         // first step, where X = 0 and every RHS is live)
         if (outer == 1) {
-            hipLaunchKernelGGL((batched::k_copy_ssq<float, K>), dim3(h->nb1), dim3(kBlock), 0, st,
+            hipLaunchKernelGGL((batched::k_copy_ssq<float, K>), dim3(h->nbr), dim3(kBlock), 0, st,
                                h->sv.m, Bm, ldb, B.U32, B.part1, batch_row_map(h));
         } else {
             hipLaunchKernelGGL((batched::k_interleave_att<double, K>), dim3(h->nbc), dim3(kBlock),
                                0, st, (const double*)X, ldx, h->sv.att_base, h->sv.n_dfa, B.X3);
-            hipLaunchKernelGGL((batched::k_resid<T, float, K>), dim3(h->nb1), dim3(kBlock), 0, st,
+            hipLaunchKernelGGL((batched::k_resid<T, float, K>), dim3(h->nbr), dim3(kBlock), 0, st,
                                h->sv, (const double*)X, ldx, (const double*)B.X3, Bm, ldb, B.U32,
                                B.part1, batch_row_map(h), live);
         }
@@ -1890,7 +1935,7 @@ lsqr_status batch_probe(lsqr_handle* h, const double* Bm, int64_t ldb, double* m
     auto& B = h->batch;
     const TileBufs<Acc> tb = tile_bufs<Acc>(h);
     LSQR_TRY(batch_controls<K>(h, 1 << 20, 0.0, 0.0));
-    hipLaunchKernelGGL((batched::k_copy_ssq<Acc, K>), dim3(h->nb1), dim3(kBlock), 0, h->stream,
+    hipLaunchKernelGGL((batched::k_copy_ssq<Acc, K>), dim3(h->nbr), dim3(kBlock), 0, h->stream,
                        h->sv.m, Bm, ldb, tb.U, B.part1, batch_row_map(h));
     LSQR_TRY((batch_init<T, Acc, K>(h)));
     Scalars host[kMaxTile];
@@ -1991,6 +2036,45 @@ lsqr_status solve_batched(lsqr_handle* h, bool refined, const double* Bm, double
                                  outer_limit, infos ? infos + j0 : nullptr, 0));
         j0 += kt;
     }
+    return LSQR_OK;
+}
+
+// Scratch for the operators' attitude parts, where it takes at most a quarter
+// of the free memory; without it their rows gather.
+template <typename V>
+void ensure_datt(const lsqr_handle* h, V*& datt)
+{
+    size_t free_b = 0, total_b = 0;
+    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) return;
+    if ((size_t)h->sv.m * sizeof(V) > free_b / 4) return;
+    if (dalloc(&datt, h->sv.m) != LSQR_OK) g_last_error.clear();
+}
+
+// y = A x as MODE says on stream st, for the operators and the refinement's
+// residual: once the attitude bucket order is there (an aprod2 or a solve has
+// built it) the attitude part comes from a pass over it, which gathers nothing
+// from memory: 1.5e7 rows, 1e5 starts 1.05 -> 0.80 ms. x3, datt: the handle's
+// scratch of the vector's type (without memory for datt the rows gather).
+template <typename T, typename V, typename VY, int MODE>
+lsqr_status run_aprod1(lsqr_handle* h, const V* x, VY* y, const double* b, double* part,
+                       const int32_t* inv, V*& x3_raw, V*& datt_raw, hipStream_t st)
+{
+    const V* x3 = nullptr;
+    const V* datt = nullptr;
+    const bool il = h->att_il && h->sv.natt > 0 && !h->generic;
+    const bool pre = il && h->att_ready && att_pass_on(h);
+    if (il && (pre || !aprod1_staged(h, (int64_t)sizeof(V)))) {
+        if (!x3_raw) LSQR_TRY(dalloc(&x3_raw, (int64_t)kAxes * h->sv.n_dfa));
+        launch_interleave_att<V>(h, x, x3_raw, nullptr, st);
+        x3 = x3_raw;
+        if (pre && !datt_raw) ensure_datt(h, datt_raw);
+        if (pre && datt_raw) {
+            launch_att_part<T, V>(h, x3, datt_raw, st);
+            datt = datt_raw;
+        }
+    }
+    launch_aprod1<T, V, V, VY, MODE>(h, x, y, b, nullptr, part, st, inv, x3, datt);
+    HIP_TRY(hipGetLastError());
     return LSQR_OK;
 }
 
@@ -2113,21 +2197,11 @@ lsqr_status lsqr_create(const lsqr_system* sys, lsqr_handle** out)
 
     // grids
     const int64_t m = s.m, n = s.n;
-    {
-        // aprod1 grid: resident workgroups of the LDS-staged kernel
-        const int64_t bytes = s.n_instr_cols * 8;
-        int occ = 0;
-        if (bytes <= kLdsXBudget)
-            e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                &occ, k_aprod1<double, double, double, double, A1_LSQR, kBlock1, true>, kBlock1,
-                (size_t)bytes);
-        else
-            e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                &occ, k_aprod1<double, double, double, double, A1_LSQR, kBlock1, false>, kBlock1, 0);
-        if (e != hipSuccess || occ <= 0) occ = 2;
-        h->nb1 = (int)std::max<int64_t>(
-            1, std::min<int64_t>((int64_t)h->num_cu * occ, cdiv(m, 2 * kBlock1)));
-    }
+    // aprod1: one 1024-thread workgroup per compute unit (the slice of x in its
+    // LDS); the row kernels without LDS (copies, k-tile residuals): 8 of 256
+    // threads (1e8 rows copied into bucket order with 1 per compute unit: 1.2 ms)
+    h->nb1 = (int)std::min<int64_t>(h->num_cu, cdiv(m, kBlock2));
+    h->nbr = (int)std::min<int64_t>((int64_t)h->num_cu * 8, cdiv(m, kBlock));
     {
         // aprod2: a fixed number of row ranges (16 waves per compute unit),
         // run by 1024-thread workgroups in the main pass (one per compute
@@ -2149,7 +2223,7 @@ lsqr_status lsqr_create(const lsqr_system* sys, lsqr_handle** out)
     if ((st = dalloc(&h->v, n)) != LSQR_OK) return bail(st);
     if ((st = dalloc(&h->w, n)) != LSQR_OK) return bail(st);
     if ((st = dalloc(&h->y, n)) != LSQR_OK) return bail(st);
-    if ((st = dalloc(&h->part1, std::max(h->nb1, h->nb2) + 1)) != LSQR_OK) return bail(st);
+    if ((st = dalloc(&h->part1, std::max({h->nb1, h->nb2, h->nbr}) + 1)) != LSQR_OK) return bail(st);
     if ((st = dalloc(&h->partc, (int64_t)h->num_cu * 4)) != LSQR_OK) return bail(st);
     if ((st = dalloc(&h->partdd, h->nbc)) != LSQR_OK) return bail(st);
     if ((st = dalloc(&h->partxx, h->nbc)) != LSQR_OK) return bail(st);
@@ -2281,6 +2355,7 @@ lsqr_status lsqr_destroy(lsqr_handle* h)
     dfree(h->var);
     dfree(h->x3_raw);
     dfree(h->x3_raw32);
+    release_datt(h);
     dfree(h->gpart_raw32);
     if (h->att_sorted) (void)hipFree(h->att_sorted);
     h->att_sorted = nullptr;
@@ -2418,20 +2493,11 @@ lsqr_status lsqr_aprod1(lsqr_handle* h, const double* x, double* y)
 {
     LSQR_TRY(check_handle(h));
     if (!x || !y) return fail(LSQR_E_INVALID, "null vector");
-    const double* x3 = nullptr;
-    if (h->att_il && h->sv.natt > 0 && !h->generic) {
-        if (!h->x3_raw) LSQR_TRY(dalloc(&h->x3_raw, (int64_t)kAxes * h->sv.n_dfa));
-        launch_interleave_att<double>(h, x, h->x3_raw, nullptr, h->user_stream);
-        x3 = h->x3_raw;
-    }
-    if (h->value_type == LSQR_F64)
-        launch_aprod1<double, double, double, double, A1_ACCUM>(h, x, y, nullptr, nullptr, nullptr,
-                                                                h->user_stream, nullptr, x3);
-    else
-        launch_aprod1<float, double, double, double, A1_ACCUM>(h, x, y, nullptr, nullptr, nullptr,
-                                                               h->user_stream, nullptr, x3);
-    HIP_TRY(hipGetLastError());
-    return LSQR_OK;
+    auto go = [&](auto t) {
+        return run_aprod1<decltype(t), double, double, A1_ACCUM>(
+            h, x, y, nullptr, nullptr, nullptr, h->x3_raw, h->datt_raw, h->user_stream);
+    };
+    return h->value_type == LSQR_F64 ? go(double()) : go(float());
 }
 
 lsqr_status lsqr_aprod1_noalloc(lsqr_handle* h, const double* x, double* y)
@@ -2439,7 +2505,7 @@ lsqr_status lsqr_aprod1_noalloc(lsqr_handle* h, const double* x, double* y)
     LSQR_TRY(check_handle(h));
     if (!x || !y) return fail(LSQR_E_INVALID, "null vector");
     const double* x3 = nullptr;
-    if (h->att_il && h->sv.natt > 0 && !h->generic) {
+    if (h->att_il && h->sv.natt > 0 && !h->generic && !aprod1_staged(h, 8)) {
         const int64_t need = (int64_t)kAxes * h->sv.n_dfa;
         if (need > (int64_t)LSQR_NOALLOC_ATT_MAX)
             return fail(LSQR_E_INVALID,
@@ -2490,16 +2556,8 @@ lsqr_status lsqr_aprod1_f32(lsqr_handle* h, const float* x, float* y)
     if (!x || !y) return fail(LSQR_E_INVALID, "null vector");
     if (h->value_type != LSQR_F32)
         return fail(LSQR_E_STATE, "lsqr_aprod1_f32 needs an LSQR_F32 system");
-    const float* x3 = nullptr;
-    if (h->att_il && h->sv.natt > 0 && !h->generic) {
-        if (!h->x3_raw32) LSQR_TRY(dalloc(&h->x3_raw32, (int64_t)kAxes * h->sv.n_dfa));
-        launch_interleave_att<float>(h, x, h->x3_raw32, nullptr, h->user_stream);
-        x3 = h->x3_raw32;
-    }
-    launch_aprod1<float, float, float, float, A1_ACCUM>(h, x, y, nullptr, nullptr, nullptr,
-                                                        h->user_stream, nullptr, x3);
-    HIP_TRY(hipGetLastError());
-    return LSQR_OK;
+    return run_aprod1<float, float, float, A1_ACCUM>(h, x, y, nullptr, nullptr, nullptr,
+                                                     h->x3_raw32, h->datt_raw32, h->user_stream);
 }
 
 lsqr_status lsqr_aprod2_f32(lsqr_handle* h, float* x, const float* y)
@@ -2598,23 +2656,18 @@ lsqr_status lsqr_solve_refined(lsqr_handle* h, const double* b, double* x, int32
         // FP64 residual of the full problem, stored as the FP32 start vector
         // (b itself at the first step, where x = 0)
         if (outer == 1) {
-            hipLaunchKernelGGL((k_copy_ssq<float>), dim3(h->nb1), dim3(kBlock), 0, h->stream,
+            hipLaunchKernelGGL((k_copy_ssq<float>), dim3(h->nbr), dim3(kBlock), 0, h->stream,
                                h->sv.m, b, P.u, h->part1, row_map(h));
             if (h->nc > 0)
                 hipLaunchKernelGGL((k_copy_ssq<float>), dim3(1), dim3(kBlock), 0, h->stream,
-                                   h->nc, b + h->sv.m, P.u + h->sv.m, h->part1 + h->nb1,
+                                   h->nc, b + h->sv.m, P.u + h->sv.m, h->part1 + h->nbr,
                                    (const int32_t*)nullptr);
         } else {
-            const double* x3 = nullptr;
-            if (h->att_il && h->sv.natt > 0 && !h->generic) {
-                if (!h->x3_raw) LSQR_TRY(dalloc(&h->x3_raw, (int64_t)kAxes * h->sv.n_dfa));
-                launch_interleave_att<double>(h, x, h->x3_raw, nullptr, h->stream);
-                x3 = h->x3_raw;
-            }
-            launch_aprod1<float, double, double, float, A1_RESID>(
-                h, (const double*)x, P.u, b, nullptr, h->part1, h->stream, row_map(h), x3);
+            LSQR_TRY((run_aprod1<float, double, float, A1_RESID>(
+                h, (const double*)x, P.u, b, h->part1, row_map(h), h->x3_raw, h->datt_raw,
+                h->stream)));
         }
-        launch_init<float, float>(h, P, h->stream);
+        launch_init<float, float>(h, P, n_part(h, outer == 1 ? h->nbr : h->nb1), h->stream);
         HIP_TRY(hipGetLastError());
         LSQR_TRY(read_scalars(h));
         if (outer == 1) bnorm = h->sc_host->bnorm;
