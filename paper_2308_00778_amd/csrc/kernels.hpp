@@ -329,7 +329,7 @@ __global__ __launch_bounds__(kBlock) void k_section_sums(SliceView att, SliceVie
                                                           const Scalars* __restrict__ sc)
 {
     __shared__ double red[kBlock];
-    if (sc != nullptr && (sc->done || sc->beta_zero)) return;
+    if (sc != nullptr && sc->done) return;
     auto add = [q](int64_t j, double sum) { q[j] = (Acc)((double)q[j] + sum); };
     for_columns(att, ins, att.cols() + ins.cols(), red, add, [](int64_t) {});
     for_globals<Acc>(glob, red, add);
@@ -404,42 +404,56 @@ struct Gate {
     int32_t n;
 };
 
-// Sum of n partials by the first kBlock threads of a block of NT, in the order
-// of sum_partials; valid on thread 0. lds >= kWavesPerBlock.
-template <int NT>
-__device__ __forceinline__ double sum_partials_nt(const double* part, int n, double* lds)
+// The gate's loads (each thread's partials, the state's flag), issued before
+// the staging of LDS so that they arrive beside it.
+struct GateIn {
+    double dd, xx;
+    int32_t done;
+    double coef;
+};
+
+__device__ __forceinline__ GateIn gate_load(const Gate& G)
 {
-    double v = 0.0;
-    if (threadIdx.x < kBlock)
-        for (int k = threadIdx.x; k < n; k += kBlock) v += part[k];
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_down(v, off);
-    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-    __syncthreads();
-    if (lane == 0 && w < kWavesPerBlock) lds[w] = v;
-    __syncthreads();
-    double r = 0.0;
-    if (threadIdx.x == 0)
-        for (int k = 0; k < kWavesPerBlock; ++k) r += lds[k];
-    return r;
+    GateIn in = {0.0, 0.0, 0, 0.0};
+    const Scalars* s = G.B ? G.B : G.A;
+    if (s == nullptr) return in;  // an operator, outside a solve
+    if (G.B != nullptr && threadIdx.x < kBlock)
+        for (int k = threadIdx.x; k < G.n; k += kBlock) {  // as sum_partials
+            in.dd += G.dd[k];
+            in.xx += G.xx[k];
+        }
+    in.done = s->done;
+    in.coef = s->coef_u;
+    return in;
 }
 
-// True while the solve runs (uniform over the block); coef: coef_u of the step.
-template <int NT>
-__device__ __forceinline__ bool gate_open(const Gate& G, double* red, int32_t* flag, double* coef)
+// True while the solve runs (uniform over the block). red: 2 kWavesPerBlock.
+// All threads of the block call this.
+__device__ __forceinline__ bool gate_open(const Gate& G, const GateIn& in, double* red,
+                                          int32_t* flag)
 {
-    if (G.B == nullptr) {
-        if (G.A == nullptr) return true;  // an operator, outside a solve
-        *coef = G.A->coef_u;
-        return G.A->done == 0;
-    }
-    if (G.B->done) return false;  // A was final already
-    *coef = G.B->coef_u;
+    if (in.done) return false;  // B pending: A was final already
+    if (G.B == nullptr) return true;
     if (blockIdx.x == 0) copy_state(G.A, G.B);  // before the barriers of the sums
-    const double dd = sum_partials_nt<NT>(G.dd, G.n, red);
-    const double xx = sum_partials_nt<NT>(G.xx, G.n, red);
+    double dd = in.dd, xx = in.xx;
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) {
+        dd += __shfl_down(dd, off);
+        xx += __shfl_down(xx, off);
+    }
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    if (lane == 0 && w < kWavesPerBlock) {
+        red[w] = dd;
+        red[kWavesPerBlock + w] = xx;
+    }
+    __syncthreads();
     if (threadIdx.x == 0) {
-        const StopUpdate o = stop_update(*G.B, dd, xx);
+        double sd = 0.0, sx = 0.0;
+        for (int k = 0; k < kWavesPerBlock; ++k) {
+            sd += red[k];
+            sx += red[kWavesPerBlock + k];
+        }
+        const StopUpdate o = stop_update(*G.B, sd, sx);
         *flag = o.done;
         if (blockIdx.x == 0) {
             G.A->ddnorm = o.ddnorm;
@@ -454,14 +468,28 @@ __device__ __forceinline__ bool gate_open(const Gate& G, double* red, int32_t* f
     return *flag == 0;
 }
 
+// dst[0, n) = src[0, n) by the block's NT threads, four loads in flight each.
+template <int NT, typename V>
+__device__ __forceinline__ void stage(V* dst, const V* src, int64_t n)
+{
+    for (int64_t j = threadIdx.x; j < n; j += 4 * NT) {
+        V v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (j + k * NT < n) v[k] = src[j + k * NT];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (j + k * NT < n) dst[j + k * NT] = v[k];
+    }
+}
+
 // The same as a kernel of its own: after the last iteration of a launch, and
 // where the next iteration's first pass has no gate.
 __global__ __launch_bounds__(kBlock) void k_scalar_stop(Gate gate)
 {
-    __shared__ double red[kWavesPerBlock];
+    __shared__ double red[2 * kWavesPerBlock];
     __shared__ int32_t flag;
-    double coef;
-    (void)gate_open<kBlock>(gate, red, &flag, &coef);
+    (void)gate_open(gate, gate_load(gate), red, &flag);
 }
 
 // ------------------------------------------------------------------- aprod 1
@@ -685,6 +713,101 @@ __device__ __forceinline__ Acc wave_sum(Acc v)
     return v;
 }
 
+// Cross-lane moves in the vector unit (no LDS): a reduction by ds_bpermute of the
+// five sums of a star takes 60 LDS instructions, and 16 waves of a compute unit
+// share one LDS (4000 cycles for each end of a star).
+template <typename V, typename F>
+__device__ __forceinline__ V by_words(V a, F&& f)
+{
+    if constexpr (sizeof(V) == 8) {
+        const uint64_t b = __builtin_bit_cast(uint64_t, a);
+        const uint32_t lo = f((uint32_t)b), hi = f((uint32_t)(b >> 32));
+        return __builtin_bit_cast(V, (uint64_t)lo | ((uint64_t)hi << 32));
+    } else {
+        return __builtin_bit_cast(V, f(__builtin_bit_cast(uint32_t, a)));
+    }
+}
+
+// Lane l of the result: the sum of a (l < 32) or b over lanes l mod 32 and
+// l mod 32 + 32.
+template <typename V>
+__device__ __forceinline__ V half_sum(V a, V b)
+{
+    auto swap = [](uint32_t x, uint32_t y, int k) {
+        return (uint32_t)__builtin_amdgcn_permlane32_swap(x, y, false, false)[k];
+    };
+    if constexpr (sizeof(V) == 8) {
+        const uint64_t x = __builtin_bit_cast(uint64_t, a), y = __builtin_bit_cast(uint64_t, b);
+        const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)y, false, false);
+        const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32),
+                                                         false, false);
+        return __builtin_bit_cast(V, (uint64_t)lo[0] | ((uint64_t)hi[0] << 32)) +
+               __builtin_bit_cast(V, (uint64_t)lo[1] | ((uint64_t)hi[1] << 32));
+    } else {
+        const uint32_t x = __builtin_bit_cast(uint32_t, a), y = __builtin_bit_cast(uint32_t, b);
+        return __builtin_bit_cast(V, swap(x, y, 0)) + __builtin_bit_cast(V, swap(x, y, 1));
+    }
+}
+
+// Rows of 16 lanes: row r of the result is the sum of two rows of a (r even) or
+// b: rows 0, 1 (r < 2) or 2, 3.
+template <typename V>
+__device__ __forceinline__ V row_pair_sum(V a, V b)
+{
+    if constexpr (sizeof(V) == 8) {
+        const uint64_t x = __builtin_bit_cast(uint64_t, a), y = __builtin_bit_cast(uint64_t, b);
+        const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)y, false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32),
+                                                         false, false);
+        return __builtin_bit_cast(V, (uint64_t)lo[0] | ((uint64_t)hi[0] << 32)) +
+               __builtin_bit_cast(V, (uint64_t)lo[1] | ((uint64_t)hi[1] << 32));
+    } else {
+        const auto w = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, a),
+                                                        __builtin_bit_cast(uint32_t, b), false,
+                                                        false);
+        return __builtin_bit_cast(V, (uint32_t)w[0]) + __builtin_bit_cast(V, (uint32_t)w[1]);
+    }
+}
+
+// Sum over the lanes of a row of 16 that are equal mod K, in all of them.
+template <int K, typename V>
+__device__ __forceinline__ V row_sum(V v)
+{
+    auto ror = [](V x, auto n) {
+        return by_words(x, [](uint32_t w) {
+            return (uint32_t)__builtin_amdgcn_mov_dpp((int)w, 0x120 + decltype(n)::value, 0xf, 0xf,
+                                                      false);
+        });
+    };
+    if constexpr (K <= 8) v += ror(v, std::integral_constant<int, 8>());
+    if constexpr (K <= 4) v += ror(v, std::integral_constant<int, 4>());
+    if constexpr (K <= 2) v += ror(v, std::integral_constant<int, 2>());
+    if constexpr (K <= 1) v += ror(v, std::integral_constant<int, 1>());
+    return v;
+}
+
+// Sums of a star's five values over the lanes equal mod K, then
+// put(j, r, sum) once for each value j and right-hand side r < K, on K lanes a
+// value. Four values share the moves: one each in the four rows of a register.
+// Every lane of the wave must be active.
+template <int K, typename V, typename F>
+__device__ __forceinline__ void star_put(const V (&v)[kAstro], int lane, F&& put)
+{
+    static_assert(kAstro == 5 && K <= 16, "four packed values and one");
+    const V p = row_sum<K>(row_pair_sum(half_sum(v[0], v[1]), half_sum(v[2], v[3])));
+    const V h = half_sum(v[4], v[4]);
+    const V e = row_sum<K>(row_pair_sum(h, h));
+    const int c = lane & 15, row = lane >> 4;
+    const int j = ((row & 1) << 1) | (row >> 1);  // the value of this row of p
+    if constexpr (K <= 8) {
+        const bool last = row == 0 && c >= K && c < 2 * K;
+        if (c < K || last) put(last ? 4 : j, c & (K - 1), last ? e : p);
+    } else {
+        put(j, c, p);
+        if (row == 0) put(4, c, e);
+    }
+}
+
 // Reduction of NV values per row over segments of equal, non-decreasing keys,
 // one 64-row chunk at a time. Each lane keeps running partials of the segment
 // that is still open at the end of the previous chunk; cross-lane work
@@ -702,7 +825,8 @@ struct SegAcc {
     }
 };
 
-// emit(key, totals) runs on lane 0 once per finished segment.
+// emit(key, values) runs on the whole wave once per finished segment, with each
+// lane's share of its sums.
 template <typename Acc, int NV, typename Emit>
 __device__ __forceinline__ void seg_chunk(SegAcc<Acc, NV>& S, int64_t key, const Acc (&v)[NV],
                                           int lane, Emit&& emit)
@@ -713,10 +837,7 @@ __device__ __forceinline__ void seg_chunk(SegAcc<Acc, NV>& S, int64_t key, const
     uint64_t rest = __ballot(!cont);
     if (rest == 0) return;  // the whole chunk continues the open segment
     if (S.key >= 0) {       // keys are sorted: the open segment ends here
-        Acc t[NV];
-#pragma unroll
-        for (int j = 0; j < NV; ++j) t[j] = wave_sum(S.acc[j]);
-        if (lane == 0) emit(S.key, t);
+        emit(S.key, S.acc);
     }
     S.key = -1;
 #pragma unroll
@@ -735,8 +856,8 @@ __device__ __forceinline__ void seg_chunk(SegAcc<Acc, NV>& S, int64_t key, const
         }
         Acc t[NV];
 #pragma unroll
-        for (int j = 0; j < NV; ++j) t[j] = wave_sum(mine ? v[j] : (Acc)0);
-        if (lane == 0) emit(k2, t);
+        for (int j = 0; j < NV; ++j) t[j] = mine ? v[j] : (Acc)0;
+        emit(k2, t);
         rest &= ~same;
     }
 }
@@ -745,10 +866,7 @@ template <typename Acc, int NV, typename Emit>
 __device__ __forceinline__ void seg_finish(SegAcc<Acc, NV>& S, int lane, Emit&& emit)
 {
     if (S.key < 0) return;
-    Acc t[NV];
-#pragma unroll
-    for (int j = 0; j < NV; ++j) t[j] = wave_sum(S.acc[j]);
-    if (lane == 0) emit(S.key, t);
+    emit(S.key, S.acc);
     S.key = -1;
 }
 
@@ -766,8 +884,8 @@ __device__ __forceinline__ void seg_flush(int64_t key, const Acc (&v)[NV], int l
         const uint64_t same = __ballot(mine);
         Acc t[NV];
 #pragma unroll
-        for (int j = 0; j < NV; ++j) t[j] = wave_sum(mine ? v[j] : (Acc)0);
-        if (lane == 0) emit(k2, t);
+        for (int j = 0; j < NV; ++j) t[j] = mine ? v[j] : (Acc)0;
+        emit(k2, t);
         rest &= ~same;
     }
 }
@@ -796,7 +914,7 @@ __global__ __launch_bounds__(NT) void k_aprod2(SysView s, const VU* __restrict__
     extern __shared__ __align__(16) unsigned char smem_raw[];
     double* lds = reinterpret_cast<double*>(smem_raw);  // FP64 histogram (see k_att_hist)
     __shared__ Acc gred[NT / kWave];
-    if (sc != nullptr && (sc->done || sc->beta_zero)) return;
+    if (sc != nullptr && sc->done) return;
 
     const T* __restrict__ val = static_cast<const T*>(s.val);
     const int64_t m = s.m;
@@ -815,9 +933,8 @@ __global__ __launch_bounds__(NT) void k_aprod2(SysView s, const VU* __restrict__
     for (int j = 0; j < kAstro; ++j) carry[j] = (Acc)0;
     Acc gsum = (Acc)0;
     SegAcc<Acc, kAstro> seg;
-    auto astro_emit = [q](int64_t star, const Acc (&tot)[kAstro]) {
-#pragma unroll
-        for (int j = 0; j < kAstro; ++j) q[kAstro * star + j] += tot[j];
+    auto astro_emit = [q, lane](int64_t star, const Acc (&v)[kAstro]) {
+        star_put<1>(v, lane, [&](int j, int, Acc sum) { q[kAstro * star + j] += sum; });
     };
 
     // Chunks start on 64-row boundaries so that every coefficient stream is
@@ -930,7 +1047,7 @@ __global__ __launch_bounds__(NT) void k_aprod2(SysView s, const VU* __restrict__
 //   u: u~ [m], overwritten (row i at u[inv[i]], or u[i] without inv),
 //   part[blockIdx.x]: FP64 sum of squares of the
 //   stored u~, q: A^T u~ accumulator (astro, instr, glob sections),
-//   gpart[blockIdx.x]: global-column partials, wb: star-aligned wave ranges.
+//   gpart[blockIdx.x]: global-column partials, steps: the waves' rows.
 // Dynamic LDS: the FP64 histogram of instrumental columns [0, hcols) (see
 // k_att_hist; columns from hcols on are left to k_instr_tail), in kAttAll that
 // of the attitude columns ([axis][n_dfa]), then the instrumental slice of x
@@ -951,13 +1068,27 @@ __global__ __launch_bounds__(NT) void k_aprod2(SysView s, const VU* __restrict__
 // slices there (SliceView) instead of being added to q with device atomics.
 // GEN > 0: section sizes from the system view (general layouts with at most GEN
 // global columns: five of them cost 20 registers more); the loads stay unrolled,
-// each under a uniform test. A2: Eq. (3) alone, u unchanged.
+// each under a uniform test. A2: Eq. (3) alone, u unchanged. kPlain: loads without
+// the nontemporal hint, for a matrix that the last-level cache holds from one
+// iteration to the next.
+// The rows are dealt to the waves in whole 64-row steps, an equal number each
+// but for one (WaveSteps), not in ranges that begin with a star: a range of a
+// few steps otherwise takes one or two more, and the waves wait for the
+// longest (1e5 rows of 100-row stars: three steps where one does, 18.2 -> us).
 enum { kAttX = 0, kAttX3 = 1, kAttPre = 2, kAttGather = 3, kAttAll = 4 };
+
+// Step ranges of the waves: wave w takes `each` 64-row steps, and one more if
+// w < more, from first(w).
+struct WaveSteps {
+    int64_t each;
+    int32_t more;
+    __device__ int64_t first(int32_t w) const { return w * each + (w < more ? w : more); }
+};
 template <typename T, typename Acc, int NT, bool LDSX, int AM, bool CIDX, int GEN = 0,
-          bool WIN = false, bool A2 = false>
+          bool WIN = false, bool A2 = false, bool kPlain = false>
 __global__ __launch_bounds__(NT) void k_fused(SysView s, const Acc* __restrict__ x,
                                                const Acc* __restrict__ x3, Acc* __restrict__ u,
-                                               Acc* __restrict__ q, const int64_t* __restrict__ wb,
+                                               Acc* __restrict__ q, WaveSteps steps,
                                                Acc* __restrict__ gpart, double* __restrict__ part,
                                                int64_t hcols, Gate gate,
                                                const int32_t* __restrict__ inv,
@@ -967,13 +1098,12 @@ __global__ __launch_bounds__(NT) void k_fused(SysView s, const Acc* __restrict__
                                                double* __restrict__ sins = nullptr)
 {
     constexpr bool kNoAtt = AM == kAttPre || AM == kAttGather;
-    constexpr bool kPlain = AM == kAttAll;
     constexpr int kAtt = kAxes * kParAxis;
     constexpr int NG = GEN ? GEN : 1;
     constexpr int W = NT / kWave;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     __shared__ Acc gred[NG * W];
-    __shared__ double sred[W];
+    __shared__ double sred[W < 2 * kWavesPerBlock ? 2 * kWavesPerBlock : W];
     __shared__ int32_t gflag;
     const int na = GEN ? s.na : kAstro, ni = GEN ? s.ni : kInstr, ng = GEN ? s.ng : 1;
     const bool att = !kNoAtt && (!GEN || s.natt > 0);
@@ -988,24 +1118,24 @@ __global__ __launch_bounds__(NT) void k_fused(SysView s, const Acc* __restrict__
     double* ahist = hist + hcols;
     const Acc* xi = A2 ? nullptr : x + s.instr_base;
     const Acc* xw = x3;
+    const GateIn gin = gate_load(gate);
     for (int64_t j = threadIdx.x; j < hcols + hatt; j += NT) hist[j] = 0.0;
     if (LDSX && !A2) {
         const int64_t off = ((hcols + hatt) * 8 + 15) & ~(int64_t)15;
         Acc* xl = reinterpret_cast<Acc*>(smem_raw + off);
-        for (int64_t j = threadIdx.x; j < ninst; j += NT) xl[j] = xi[j];
+        stage<NT>(xl, xi, ninst);
         xi = xl;
         if (WIN) {
             Acc* wl = xl + ninst;
-            for (int64_t j = threadIdx.x; j < hatt; j += NT) wl[j] = x3[j];
+            stage<NT>(wl, x3, hatt);
             xw = wl;
         }
     }
     Acc coef = (Acc)0;
     if (!A2) {
-        double cf = 0.0;
-        if (!gate_open<NT>(gate, sred, &gflag, &cf)) return;
-        coef = (Acc)cf;
-    } else if (gate.A != nullptr && (gate.A->done || gate.A->beta_zero)) {
+        if (!gate_open(gate, gin, sred, &gflag)) return;
+        coef = (Acc)gin.coef;
+    } else if (gate.A != nullptr && gate.A->done) {
         return;
     }
     __syncthreads();
@@ -1014,8 +1144,9 @@ __global__ __launch_bounds__(NT) void k_fused(SysView s, const Acc* __restrict__
 #pragma unroll
     for (int g = 0; g < NG; ++g) xg[g] = (!A2 && g < ng) ? x[s.glob_base + g] : (Acc)0;
     const int lane = threadIdx.x & (kWave - 1);
-    const int64_t wave = (int64_t)blockIdx.x * W + threadIdx.x / kWave;
-    const int64_t rb = wb[wave], re = wb[wave + 1];
+    const int32_t wave = (int32_t)(blockIdx.x * W + threadIdx.x / kWave);
+    const int64_t rb = steps.first(wave) * kWave;
+    const int64_t re = steps.first(wave + 1) * kWave < m ? steps.first(wave + 1) * kWave : m;
     Acc* __restrict__ qins = q + s.instr_base;
 
     double ssq = 0.0;
@@ -1023,28 +1154,32 @@ __global__ __launch_bounds__(NT) void k_fused(SysView s, const Acc* __restrict__
 #pragma unroll
     for (int g = 0; g < NG; ++g) gsum[g] = (Acc)0;
     SegAcc<Acc, kAstro> seg;
-    // A star's rows belong to one wave and its columns of q are zero here (the
-    // column kernel leaves them so), so a step stores its sums; an addition
-    // would make the wave wait for its loads, and with them for every load
-    // issued before (loads return in issue order), at each end of a star.
-    auto astro_emit = [=](int64_t star, const Acc (&tot)[kAstro]) {
-#pragma unroll
-        for (int j = 0; j < kAstro; ++j)
-            if (!GEN || j < na) {
-                Acc* dst = &q[(int64_t)na * star + j];
-                if (A2) *dst += tot[j];
-                else *dst = tot[j];
-            }
+    // Every star's columns of q are zero here in an LSQR step (the column kernel
+    // leaves them so), so a step stores a star's sums; an addition would make
+    // the wave wait for its loads, and with them for every load issued before
+    // (loads return in issue order), at each end of a star. Only the first and
+    // the last star of a wave's rows may go on in another wave's: their sums are
+    // added with device atomics.
+    bool shared = true;
+    auto astro_emit = [=, &shared](int64_t star, const Acc (&v)[kAstro]) {
+        star_put<1>(v, lane, [&](int j, int, Acc sum) {
+            if (GEN && j >= na) return;
+            Acc* dst = &q[(int64_t)na * star + j];
+            if (shared) atomicAdd(dst, sum);
+            else if (A2) *dst += sum;
+            else *dst = sum;
+        });
+        shared = false;
     };
 
-    // 64-row aligned chunks, as in k_aprod2; lanes outside [rb, re) compute on
-    // a clamped row and contribute nothing.
-    for (int64_t r0 = rb < re ? (rb & ~(int64_t)(kWave - 1)) : re; r0 < re; r0 += kWave) {
+    // 64-row steps; lanes past the last row compute on it and contribute
+    // nothing.
+    for (int64_t r0 = rb; r0 < re; r0 += kWave) {
         const int64_t i = r0 + lane;
-        const bool ok = i >= rb && i < re;
-        const int64_t ic = i < rb ? rb : (i < re ? i : re - 1);
+        const bool ok = i < re;
+        const int64_t ic = ok ? i : re - 1;
         const int64_t stc = star_of<CIDX, kPlain>(s, ic);
-        const int64_t st = i < re ? stc : kNoStar;
+        const int64_t st = ok ? stc : kNoStar;
         const int64_t t = att ? ld_stream<kPlain>(&s.att[ic]) : 0;
         T aa[kAstro], at[kAtt], ai[kInstr], ag[NG];
         int32_t ix[kInstr];
@@ -1134,6 +1269,7 @@ __global__ __launch_bounds__(NT) void k_fused(SysView s, const Acc* __restrict__
         for (int j = 0; j < kAstro; ++j) pa[j] = (Acc)aa[j] * d;
         if (!GEN || na > 0) seg_chunk(seg, st, pa, lane, astro_emit);
     }
+    shared = true;
     seg_finish(seg, lane, astro_emit);
 
     // per-workgroup partials: global columns and ||u~||^2
@@ -1192,7 +1328,7 @@ __device__ __forceinline__ SideBySide side_by_side(int64_t block, int n)
 // FP64 LDS histogram of one window (the windows of a part side by side), then
 // flushes it with one device atomic per column. U holds K
 // values per row, row i at U[inv[i] K + r] (U[i K + r] without inv); frozen
-// RHS (done or beta_zero) are skipped.
+// RHS are skipped.
 // GEN: section sizes from the system view (general layouts); otherwise the
 // full layout's constants.
 template <typename T, typename Acc, int K, bool SQUARE, int NT, bool GEN, bool PLAIN = false>
@@ -1211,7 +1347,7 @@ __global__ __launch_bounds__(NT) void k_instr_tail(SysView s, const Acc* __restr
     uint32_t live = 0;
 #pragma unroll
     for (int r = 0; r < K; ++r)
-        live |= (sc != nullptr && (sc[r].done || sc[r].beta_zero)) ? 0u : (1u << r);
+        live |= (sc != nullptr && sc[r].done) ? 0u : (1u << r);
     if (live == 0) return;
     const T* __restrict__ val = static_cast<const T*>(s.val);
     const int64_t m = s.m, w = c1 - c0;
@@ -1344,7 +1480,7 @@ __global__ __launch_bounds__(kBlock) void k_gen_aprod2(SysView s, const VU* __re
     extern __shared__ __align__(16) unsigned char smem_raw[];
     double* lds = reinterpret_cast<double*>(smem_raw);
     __shared__ Acc gred[kGlobMax][kWavesPerBlock];
-    if (sc != nullptr && (sc->done || sc->beta_zero)) return;
+    if (sc != nullptr && sc->done) return;
     const T* __restrict__ val = static_cast<const T*>(s.val);
     const int64_t m = s.m;
     const int na = s.na, ni = s.ni, ng = s.ng;
@@ -1357,8 +1493,10 @@ __global__ __launch_bounds__(kBlock) void k_gen_aprod2(SysView s, const VU* __re
 #pragma unroll
     for (int g = 0; g < kGlobMax; ++g) gsum[g] = (Acc)0;
     SegAcc<Acc, kAstro> seg;
-    auto astro_emit = [q, na](int64_t star, const Acc (&tot)[kAstro]) {
-        for (int j = 0; j < na; ++j) q[(int64_t)na * star + j] += tot[j];
+    auto astro_emit = [q, na, lane](int64_t star, const Acc (&v)[kAstro]) {
+        star_put<1>(v, lane, [&](int j, int, Acc sum) {
+            if (j < na) q[(int64_t)na * star + j] += sum;
+        });
     };
     for (int64_t r0 = rb < re ? (rb & ~(int64_t)(kWave - 1)) : re; r0 < re; r0 += kWave) {
         const int64_t i = r0 + lane;
@@ -1517,7 +1655,7 @@ __global__ __launch_bounds__(kBlock) void k_con_aprod2(int64_t nc,
                                                         Acc* __restrict__ q,
                                                         const Scalars* __restrict__ sc)
 {
-    if (sc != nullptr && (sc->done || sc->beta_zero)) return;
+    if (sc != nullptr && sc->done) return;
     for (int64_t r = blockIdx.x; r < nc; r += gridDim.x) {
         const Acc ur = SQUARE ? (Acc)0 : (Acc)u[r];
         const int64_t e1 = rowptr[r + 1];
@@ -1579,11 +1717,11 @@ __global__ __launch_bounds__(kBlock) void k_col_a(int64_t n, const double* __res
 {
     __shared__ double red[kBlock];
     __shared__ double bsh;
+    double t = 0.0;  // loaded beside the flag
+    for (int k = threadIdx.x; k < bv.npart; k += kBlock) t += bv.part[k];
+    for (int k = threadIdx.x; k < bv.ncon; k += kBlock) t += bv.con[k];
     if (sc->done) return;
     if (bv.npart > 0) {
-        double t = 0.0;
-        for (int k = threadIdx.x; k < bv.npart; k += kBlock) t += bv.part[k];
-        for (int k = threadIdx.x; k < bv.ncon; k += kBlock) t += bv.con[k];
         const double ssq = block_sum(t, red);
         if (threadIdx.x == 0) {
             const double b = sqrt(ssq);
@@ -1677,11 +1815,13 @@ __global__ __launch_bounds__(kBlock) void k_col_b(int64_t n, const double* __res
 {
     __shared__ double red[kWavesPerBlock];
     __shared__ double bc[4];
+    double t = 0.0;  // loaded beside the flag
+    for (int k = threadIdx.x; k < npartc; k += kBlock) t += partc[k];
     if (A->done) {
         if (blockIdx.x == 0 && threadIdx.x == 0) *B = *A;
         return;
     }
-    const double ssq = sum_partials(partc, npartc, red);
+    const double ssq = block_sum(t, red);
     if (threadIdx.x == 0) {
         Scalars s = *A;
         rotate_update(s, ssq);
@@ -2032,7 +2172,7 @@ __global__ __launch_bounds__(kBlock) void k_att_gather(const T* __restrict__ val
 // GATED (single right-hand side): the pass makes the previous iteration's
 // stopping tests first (Gate); otherwise sc holds the K current states.
 template <typename T, typename Acc, int K, int KS, int NT, bool SEP = false,
-          bool PIPE = (KS * sizeof(Acc) <= 8), bool GATED = false>
+          bool PIPE = (KS * sizeof(Acc) <= 8), bool GATED = false, bool PLAIN = false>
 __global__ __launch_bounds__(NT) void k_att_dot(int64_t ld, const T* __restrict__ att_sorted,
                                                  const int32_t* __restrict__ tloc,
                                                  const int64_t* __restrict__ bstart,
@@ -2043,8 +2183,10 @@ __global__ __launch_bounds__(NT) void k_att_dot(int64_t ld, const T* __restrict_
 {
     static_assert(K % KS == 0, "sweeps of KS right-hand sides cover the tile");
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    __shared__ double red[kWavesPerBlock];
+    __shared__ double red[2 * kWavesPerBlock];
     __shared__ int32_t gflag;
+    GateIn gin = {};
+    if constexpr (GATED) gin = gate_load(gate);
     Acc* win = reinterpret_cast<Acc*>(smem_raw);
     const int64_t span = width + kParAxis - 1;
     const SideBySide sb = side_by_side(blockIdx.x, K / KS);
@@ -2068,15 +2210,18 @@ __global__ __launch_bounds__(NT) void k_att_dot(int64_t ld, const T* __restrict_
             if (live == 0) return;  // uniform over the workgroup
         }
         const int32_t plane = (int32_t)(kAxes * span);
-        for (int32_t e = threadIdx.x; e < (int32_t)(kAxes * ncol) * KS; e += NT) {
-            const int32_t col = e / KS, j = e - col * KS;
-            win[j * plane + col] = x3[(kAxes * c0 + col) * K + s0 + j];
+        if constexpr (K == 1) {
+            stage<NT>(win, x3 + kAxes * c0, kAxes * ncol);
+        } else {
+            for (int32_t e = threadIdx.x; e < (int32_t)(kAxes * ncol) * KS; e += NT) {
+                const int32_t col = e / KS, j = e - col * KS;
+                win[j * plane + col] = x3[(kAxes * c0 + col) * K + s0 + j];
+            }
         }
-        if constexpr (GATED) {  // beside the window's loads
-            double cf = 0.0;
-            if (!gate_open<NT>(gate, red, &gflag, &cf)) return;
+        if constexpr (GATED) {
+            if (!gate_open(gate, gin, red, &gflag)) return;
             live = 1u;
-            coef[0] = (Acc)cf;
+            coef[0] = (Acc)gin.coef;
         }
         __syncthreads();
         constexpr int kAtt = kAxes * kParAxis;
@@ -2109,9 +2254,9 @@ __global__ __launch_bounds__(NT) void k_att_dot(int64_t ld, const T* __restrict_
             };
             auto load = [&](Row& r, int64_t k) {
                 const int64_t kk = k < b0 ? b0 : k;
-                r.tl = ldnt(&tloc[kk]);
+                r.tl = ld_stream<PLAIN>(&tloc[kk]);
 #pragma unroll
-                for (int c = 0; c < kAtt; ++c) r.a[c] = ldnt(&att_sorted[c * ld + kk]);
+                for (int c = 0; c < kAtt; ++c) r.a[c] = ld_stream<PLAIN>(&att_sorted[c * ld + kk]);
 #pragma unroll
                 for (int j = 0; j < KS; ++j) r.uo[j] = SEP ? (Acc)0 : u[kk * K + s0 + j];
             };
@@ -2158,10 +2303,10 @@ __global__ __launch_bounds__(NT) void k_att_dot(int64_t ld, const T* __restrict_
         } else {
             for (int64_t k = a0 + g * NT + threadIdx.x; k < r1; k += stride) {
                 if (k < b0) continue;
-                const int64_t tl = ldnt(&tloc[k]);
+                const int64_t tl = ld_stream<PLAIN>(&tloc[k]);
                 T a[kAtt];
 #pragma unroll
-                for (int c = 0; c < kAtt; ++c) a[c] = ldnt(&att_sorted[c * ld + k]);
+                for (int c = 0; c < kAtt; ++c) a[c] = ld_stream<PLAIN>(&att_sorted[c * ld + k]);
                 Acc d[KS];
                 row_dot_win(tl, a, d);
 #pragma unroll
@@ -2186,7 +2331,7 @@ __global__ __launch_bounds__(NT) void k_att_dot(int64_t ld, const T* __restrict_
 // 150 KB: 1550 vs 204 G/s), and the sums are more accurate. U is in bucket
 // order ([m][K]); the K / KS sweeps of a tile are workgroups side by side (one sweep
 // after the other read every row from memory K / KS times; slices = nbk G).
-// Frozen RHS (done or beta_zero) are skipped. GATHER: U is in star order instead, and the row at
+// Frozen RHS are skipped. GATHER: U is in star order instead, and the row at
 // bucket position k is read at U[perm[k]] (a read through the permutation,
 // whose targets form one increasing run per bucket).
 // PIPE: each thread issues the loads of its next row before the atomics of
@@ -2195,7 +2340,7 @@ __global__ __launch_bounds__(NT) void k_att_dot(int64_t ld, const T* __restrict_
 // att_sorted and the row blocks as in k_att_dot (64-row aligned; lanes below
 // the bucket's first row load that row with a zero weight).
 template <typename T, typename Acc, int K, int KS, int NT, bool GATHER = false,
-          bool PIPE = (KS <= 2)>
+          bool PIPE = (KS <= 2), bool PLAIN = false>
 __global__ __launch_bounds__(NT) void k_att_hist(int64_t ld, const T* __restrict__ att_sorted,
                                                   const int32_t* __restrict__ tloc,
                                                   const int64_t* __restrict__ bstart,
@@ -2218,7 +2363,7 @@ __global__ __launch_bounds__(NT) void k_att_hist(int64_t ld, const T* __restrict
         uint32_t live = 0;
 #pragma unroll
         for (int j = 0; j < KS; ++j)
-            live |= (sc != nullptr && (sc[s0 + j].done || sc[s0 + j].beta_zero) ? 0u : 1u) << j;
+            live |= (sc != nullptr && sc[s0 + j].done ? 0u : 1u) << j;
         if (live == 0) return;  // uniform over the workgroup
         for (int64_t e = threadIdx.x; e < kAxes * span * KS; e += NT) hist[e] = 0.0;
         __syncthreads();
@@ -2247,10 +2392,10 @@ __global__ __launch_bounds__(NT) void k_att_hist(int64_t ld, const T* __restrict
             };
             auto load = [&](Row& r, int64_t k) {
                 const int64_t kk = k < b0 ? b0 : k;
-                r.tl = ldnt(&tloc[kk]);
-                r.ku = GATHER ? (int64_t)ldnt(&perm[kk]) : kk;
+                r.tl = ld_stream<PLAIN>(&tloc[kk]);
+                r.ku = GATHER ? (int64_t)ld_stream<PLAIN>(&perm[kk]) : kk;
 #pragma unroll
-                for (int c = 0; c < kAtt; ++c) r.a[c] = ldnt(&att_sorted[c * ld + kk]);
+                for (int c = 0; c < kAtt; ++c) r.a[c] = ld_stream<PLAIN>(&att_sorted[c * ld + kk]);
                 if (!GATHER)
 #pragma unroll
                     for (int j = 0; j < KS; ++j) r.uk[j] = (double)U[kk * K + s0 + j];
@@ -2298,14 +2443,14 @@ __global__ __launch_bounds__(NT) void k_att_hist(int64_t ld, const T* __restrict
         } else {
             for (int64_t k = a0 + g * NT + threadIdx.x; k < r1; k += stride) {
                 if (k < b0) continue;
-                const int64_t tl = ldnt(&tloc[k]);
-                const int64_t ku = GATHER ? (int64_t)ldnt(&perm[k]) : k;
+                const int64_t tl = ld_stream<PLAIN>(&tloc[k]);
+                const int64_t ku = GATHER ? (int64_t)ld_stream<PLAIN>(&perm[k]) : k;
                 double uk[KS];
 #pragma unroll
                 for (int j = 0; j < KS; ++j) uk[j] = (double)U[ku * K + s0 + j];
                 T a[kAtt];  // all loads issued before the first atomic
 #pragma unroll
-                for (int c = 0; c < kAtt; ++c) a[c] = ldnt(&att_sorted[c * ld + k]);
+                for (int c = 0; c < kAtt; ++c) a[c] = ld_stream<PLAIN>(&att_sorted[c * ld + k]);
                 scatter(tl, a, uk);
             }
         }
@@ -2337,7 +2482,7 @@ __global__ __launch_bounds__(kBlock) void k_slice_reduce(SliceView V, Acc* __res
         for (int r = blockIdx.y; r < K; r += gridDim.y) {
             const double sum = slice_tile_sum<K>(V, col < total, col, r, red);
             if (threadIdx.x >= V.ct() || col >= total) continue;
-            if (sc != nullptr && (sc[r].done || sc[r].beta_zero)) continue;
+            if (sc != nullptr && sc[r].done) continue;
             qs[col * K + r] = (Acc)((double)qs[col * K + r] + sum);
         }
     }
@@ -2502,7 +2647,7 @@ __global__ __launch_bounds__(NT) void k_aprod2(SysView s, const Acc* __restrict_
     __shared__ Acc gred[K * (NT / kWave)];
     uint32_t live = 0;
 #pragma unroll
-    for (int r = 0; r < K; ++r) live |= ((sc[r].done || sc[r].beta_zero) ? 0u : 1u) << r;
+    for (int r = 0; r < K; ++r) live |= (sc[r].done ? 0u : 1u) << r;
     if (live == 0) return;
     const T* __restrict__ val = static_cast<const T*>(s.val);
     const int64_t m = s.m;
@@ -2517,10 +2662,13 @@ __global__ __launch_bounds__(NT) void k_aprod2(SysView s, const Acc* __restrict_
 #pragma unroll
     for (int r = 0; r < K; ++r) gsum[r] = (Acc)0;
     SegAcc<Acc, kAstro * K> seg;
-    auto astro_emit = [Q](int64_t star, const Acc (&tot)[kAstro * K]) {
+    auto astro_emit = [Q, lane](int64_t star, const Acc (&v)[kAstro * K]) {
         Acc* dst = Q + kAstro * star * K;
 #pragma unroll
-        for (int j = 0; j < kAstro * K; ++j) dst[j] += tot[j];
+        for (int j = 0; j < kAstro * K; ++j) {
+            const Acc tot = wave_sum(v[j]);
+            if (lane == 0) dst[j] += tot;
+        }
     };
     // Chunks start on 64-row boundaries so that every coefficient stream is
     // read in whole cache lines; lanes before rb (owned by the previous wave)
@@ -2803,12 +2951,14 @@ __global__ __launch_bounds__(NT) void k_fused(SysView s, const Acc* __restrict__
     }
     constexpr bool kChunkFlush = NT > 512 && K > 1;
     SegAcc<Acc, kChunkFlush ? 1 : kAstro * K> seg;
-    auto astro_emit = [Q](int64_t star, const Acc (&tot)[kAstro * K]) {
+    auto astro_emit = [Q, lane](int64_t star, const Acc (&v)[kAstro * K]) {
         Acc* dst = Q + kAstro * star * K;
 #pragma unroll
         for (int j = 0; j < kAstro * K; ++j) {
-            if (kChunkFlush) dst[j] += tot[j];  // a star in several pieces
-            else dst[j] = tot[j];
+            const Acc tot = wave_sum(v[j]);
+            if (lane != 0) continue;
+            if (kChunkFlush) dst[j] += tot;  // a star in several pieces
+            else dst[j] = tot;
         }
     };
     for (int64_t r0 = rb < re ? (rb & ~(int64_t)(kWave - 1)) : re; r0 < re; r0 += kWave) {
@@ -2935,8 +3085,7 @@ __device__ __forceinline__ V rhs_sum(V v)
 
 // Per-star segmented sums (SegAcc) in the RHS-across-lanes layout: the keys
 // of the K lanes of a row slot are equal, segments are runs of row slots;
-// emit(key, totals) runs on lanes 0..K-1 (lane j for RHS j) once per
-// finished segment.
+// emit(key, values) runs on the whole wave once per finished segment.
 template <typename Acc, int K, typename Emit>
 __device__ __forceinline__ void seg_chunk_rl(SegAcc<Acc, kAstro>& S, int64_t key,
                                              const Acc (&v)[kAstro], int lane, Emit&& emit)
@@ -2947,10 +3096,7 @@ __device__ __forceinline__ void seg_chunk_rl(SegAcc<Acc, kAstro>& S, int64_t key
     uint64_t rest = __ballot(!cont);
     if (rest == 0) return;
     if (S.key >= 0) {
-        Acc t[kAstro];
-#pragma unroll
-        for (int j = 0; j < kAstro; ++j) t[j] = rhs_sum<K>(S.acc[j]);
-        if (lane < K) emit(S.key, t);
+        emit(S.key, S.acc);
     }
     S.key = -1;
 #pragma unroll
@@ -2969,8 +3115,8 @@ __device__ __forceinline__ void seg_chunk_rl(SegAcc<Acc, kAstro>& S, int64_t key
         }
         Acc t[kAstro];
 #pragma unroll
-        for (int j = 0; j < kAstro; ++j) t[j] = rhs_sum<K>(mine ? v[j] : (Acc)0);
-        if (lane < K) emit(k2, t);
+        for (int j = 0; j < kAstro; ++j) t[j] = mine ? v[j] : (Acc)0;
+        emit(k2, t);
         rest &= ~same;
     }
 }
@@ -2979,10 +3125,7 @@ template <typename Acc, int K, typename Emit>
 __device__ __forceinline__ void seg_finish_rl(SegAcc<Acc, kAstro>& S, int lane, Emit&& emit)
 {
     if (S.key < 0) return;
-    Acc t[kAstro];
-#pragma unroll
-    for (int j = 0; j < kAstro; ++j) t[j] = rhs_sum<K>(S.acc[j]);
-    if (lane < K) emit(S.key, t);
+    emit(S.key, S.acc);
     S.key = -1;
 }
 
@@ -3124,7 +3267,7 @@ __global__ __launch_bounds__(NT) void k_fused_rl(SysView s, const Acc* __restric
     uint32_t live = 0;
 #pragma unroll
     for (int r = 0; r < K; ++r)
-        live |= ((sc[r].done || (A2 && sc[r].beta_zero)) ? 0u : 1u) << r;
+        live |= (sc[r].done ? 0u : 1u) << r;
     if (live == 0) return;
     const T* __restrict__ val = static_cast<const T*>(s.val);
     const int64_t ninst = s.n_instr_cols;
@@ -3150,13 +3293,12 @@ __global__ __launch_bounds__(NT) void k_fused_rl(SysView s, const Acc* __restric
     double ssq = 0.0;
     Acc gsum = (Acc)0;
     SegAcc<Acc, kAstro> seg;
-    auto astro_emit = [Q, lane](int64_t star, const Acc (&tot)[kAstro]) {
-        Acc* dst = Q + kAstro * star * K + lane;
-#pragma unroll
-        for (int j = 0; j < kAstro; ++j) {
-            if (A2) dst[j * K] += tot[j];
-            else dst[j * K] = tot[j];  // as in the single-RHS pass
-        }
+    auto astro_emit = [Q, lane](int64_t star, const Acc (&v)[kAstro]) {
+        star_put<K>(v, lane, [&](int j, int r, Acc sum) {
+            Acc* dst = Q + (kAstro * star + j) * K + r;
+            if (A2) *dst += sum;
+            else *dst = sum;  // as in the single-RHS pass
+        });
     };
     // one R-row step: the row of slot `slot` (clamped), its coefficients,
     // indices, star and place in U already loaded

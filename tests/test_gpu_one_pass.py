@@ -137,3 +137,30 @@ def test_one_pass_solve(torch_cuda, name, graph):
     g.close()
     for x in xs:
         assert rel_inf(x, x_ref) <= 1e-10
+
+
+# A right-hand side that the first iteration solves exactly (one column of ones:
+# every quantity is a power of two), so that beta is exactly 0 and the next
+# iteration starts from u = 0: the solution stays, in one pass and in bucket
+# order.
+@pytest.mark.parametrize("buckets", [0, 1])
+def test_zero_residual_keeps_solution(torch_cuda, buckets):
+    torch = torch_cuda
+    from paper_2308_00778_amd import LsqrSystem
+
+    say(f"zero residual: att_buckets={buckets}")
+    m = 4
+    values = torch.zeros((12, m), dtype=torch.float64, device="cuda")
+    values[0] = 1.0
+    zero = torch.zeros(m, dtype=torch.int64, device="cuda")
+    g = LsqrSystem(values, zero, zero.clone(), torch.zeros((0, m), dtype=torch.int32, device="cuda"),
+                   n_stars=1, n_dfa=4, n_instr_cols=0, n_astro=0, n_instr=0, n_glob=0)
+    g.set_option("tests", 0)
+    if buckets:
+        g.set_option("att_buckets", buckets)
+    x, info = g.solve(torch.full((m,), 2.0, dtype=torch.float64, device="cuda"), 2, atol=0.0,
+                      btol=0.0)
+    got = x.cpu().numpy()
+    g.close()
+    assert info.itn == 2 and info.rnorm == 0.0
+    assert got[0] == 2.0 and np.all(got[1:] == 0.0)
