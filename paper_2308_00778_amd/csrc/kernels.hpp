@@ -2470,19 +2470,48 @@ __global__ __launch_bounds__(NT) void k_att_hist(int64_t ld, const T* __restrict
 // Bound by the latency of the slice loads where the columns are few (256
 // slices of 180 ... 30,000 columns: 44-59 -> 4-6 us), by the bytes of the
 // slices otherwise.
+// The last blocks (blockIdx.x == gridDim.x - 1) finish the row pass before it
+// instead: beta_r = ||u~_r|| and anorm from part[npart][K] (if any), and the
+// global columns' partials gpart[nblk][K] added to qglob. Nothing else of this launch reads what they store.
 template <typename Acc, int K>
 __global__ __launch_bounds__(kBlock) void k_slice_reduce(SliceView V, Acc* __restrict__ q,
-                                                          const Scalars* __restrict__ sc)
+                                                          Scalars* __restrict__ sc,
+                                                          const double* __restrict__ part,
+                                                          int npart,
+                                                          const Acc* __restrict__ gpart, int nblk,
+                                                          Acc* __restrict__ qglob)
 {
     __shared__ double red[kBlock];
+    if (blockIdx.x == gridDim.x - 1) {
+        for (int r = blockIdx.y; r < K; r += gridDim.y) {
+            if (sc[r].done) continue;  // uniform over the block
+            double ssq = 0.0, g = 0.0;
+            for (int k = threadIdx.x; k < npart; k += kBlock) ssq += part[(int64_t)k * K + r];
+            for (int k = threadIdx.x; k < nblk; k += kBlock) g += (double)gpart[(int64_t)k * K + r];
+            ssq = block_sum(ssq, red);
+            g = block_sum(g, red);
+            if (threadIdx.x != 0) continue;
+            qglob[r] = (Acc)((double)qglob[r] + g);  // 0 with beta_r = 0
+            if (npart == 0) continue;
+            Scalars& s = sc[r];
+            const double beta = sqrt(ssq);
+            s.beta = beta;
+            if (beta > 0.0) {
+                s.anorm = sqrt(s.anorm * s.anorm + s.alpha * s.alpha + beta * beta);
+                s.beta_zero = 0;
+            } else {
+                s.beta_zero = 1;
+            }
+        }
+        return;
+    }
     Acc* __restrict__ qs = q + V.base * K;
     const int64_t total = V.cols(), tiles = V.tiles();
-    for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+    for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x - 1) {
         const int64_t col = tile * V.ct() + (threadIdx.x & (V.ct() - 1));
         for (int r = blockIdx.y; r < K; r += gridDim.y) {
             const double sum = slice_tile_sum<K>(V, col < total, col, r, red);
-            if (threadIdx.x >= V.ct() || col >= total) continue;
-            if (sc != nullptr && sc[r].done) continue;
+            if (threadIdx.x >= V.ct() || col >= total || sc[r].done) continue;
             qs[col * K + r] = (Acc)((double)qs[col * K + r] + sum);
         }
     }
@@ -3422,21 +3451,6 @@ __global__ __launch_bounds__(NT) void k_fused_rl(SysView s, const Acc* __restric
     }
 }
 
-template <typename Acc, int K>
-__global__ __launch_bounds__(kBlock) void k_glob_sum(const Acc* __restrict__ gpart, int nblk,
-                                                      Acc* __restrict__ qglob,
-                                                      const Scalars* __restrict__ sc)
-{
-    __shared__ double red[kWavesPerBlock];
-    for (int r = 0; r < K; ++r) {
-        if (sc[r].done || sc[r].beta_zero) continue;  // uniform over the block
-        double v = 0.0;
-        for (int k = threadIdx.x; k < nblk; k += kBlock) v += (double)gpart[(int64_t)k * K + r];
-        const double tot = block_sum(v, red);
-        if (threadIdx.x == 0) qglob[r] = (Acc)((double)qglob[r] + tot);
-    }
-}
-
 // V~ = p Q / beta_r - beta_r V ; Q = 0 ; alpha^2 partials per RHS.
 template <typename Acc, int K>
 __global__ __launch_bounds__(kBlock) void k_col_a(int64_t n, const double* __restrict__ p,
@@ -3471,11 +3485,13 @@ __global__ __launch_bounds__(kBlock) void k_col_a(int64_t n, const double* __res
     block_sums_k<K>(ssq, part, red);
 }
 
-template <typename VP, int K>
+// FOLD: the attitude section of VP is also kept interleaved by axis, X3.
+template <typename VP, int K, bool FOLD>
 __global__ __launch_bounds__(kBlock) void k_col_b(int64_t n, const double* __restrict__ p,
                                                    double* __restrict__ V, double* __restrict__ W,
                                                    double* __restrict__ Y, VP* __restrict__ VPv,
-                                                   const Scalars* __restrict__ sc,
+                                                   VP* __restrict__ X3, int64_t att_base,
+                                                   int64_t n_dfa, const Scalars* __restrict__ sc,
                                                    double* __restrict__ part_dd,
                                                    double* __restrict__ part_xx)
 {
@@ -3496,13 +3512,17 @@ __global__ __launch_bounds__(kBlock) void k_col_b(int64_t n, const double* __res
     for (int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x; j < n;
          j += (int64_t)gridDim.x * kBlock) {
         const double pj = p[j];
+        const int64_t ca = j - att_base;
+        const int64_t o3 = ca >= 0 && ca < kAxes * n_dfa ? att_place(ca, n_dfa) * K : -1;
 #pragma unroll
         for (int r = 0; r < K; ++r) {
             if (!((act >> r) & 1u)) continue;
             const int64_t o = j * K + r;
             const double vj = V[o] * ia[r];
             V[o] = vj;
-            VPv[o] = (VP)(pj * vj);
+            const VP vpj = (VP)(pj * vj);
+            VPv[o] = vpj;
+            if (FOLD && o3 >= 0) X3[o3 + r] = vpj;
             const double wj = W[o];
             const double dk = wj * ir[r];
             dd[r] += dk * dk;
@@ -3516,12 +3536,13 @@ __global__ __launch_bounds__(kBlock) void k_col_b(int64_t n, const double* __res
     block_sums_k<K>(xx, part_xx, red);
 }
 
-template <typename VP, int K>
+template <typename VP, int K, bool FOLD>
 __global__ __launch_bounds__(kBlock) void k_col_init(int64_t n, const double* __restrict__ p,
                                                       double* __restrict__ V,
                                                       double* __restrict__ W,
                                                       double* __restrict__ Y,
-                                                      VP* __restrict__ VPv,
+                                                      VP* __restrict__ VPv, VP* __restrict__ X3,
+                                                      int64_t att_base, int64_t n_dfa,
                                                       const Scalars* __restrict__ sc)
 {
     double ia[K];
@@ -3530,13 +3551,17 @@ __global__ __launch_bounds__(kBlock) void k_col_init(int64_t n, const double* __
     for (int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x; j < n;
          j += (int64_t)gridDim.x * kBlock) {
         const double pj = p[j];
+        const int64_t ca = j - att_base;
+        const int64_t o3 = ca >= 0 && ca < kAxes * n_dfa ? att_place(ca, n_dfa) * K : -1;
 #pragma unroll
         for (int r = 0; r < K; ++r) {
             const int64_t o = j * K + r;
             const double vj = V[o] * ia[r];
             V[o] = vj;
             W[o] = vj;
-            VPv[o] = (VP)(pj * vj);
+            const VP vpj = (VP)(pj * vj);
+            VPv[o] = vpj;
+            if (FOLD && o3 >= 0) X3[o3 + r] = vpj;
             Y[o] = 0.0;
         }
     }
@@ -3565,14 +3590,15 @@ __device__ __forceinline__ double sum_col(const double* part, int nblk, int r, d
     return block_sum(v, lds);
 }
 
-// The single-RHS scalar steps applied per RHS. Each kernel loops over the K
-// RHS of the tile (uniformly over the block) and skips frozen ones.
+// The single-RHS scalar steps applied per RHS, a block each (K blocks); frozen
+// ones are skipped.
 template <int K>
 __global__ __launch_bounds__(kBlock) void k_scalar_init_beta(const double* __restrict__ part,
                                                               int nblk, Scalars* __restrict__ sc)
 {
     __shared__ double red[kWavesPerBlock];
-    for (int r = 0; r < K; ++r) {
+    const int r = blockIdx.x;
+    {
         const double ssq = sum_col<K>(part, nblk, r, red);
         if (threadIdx.x == 0) {
             Scalars& s = sc[r];
@@ -3595,7 +3621,8 @@ __global__ __launch_bounds__(kBlock) void k_scalar_init_alpha(const double* __re
                                                                int nblk, Scalars* __restrict__ sc)
 {
     __shared__ double red[kWavesPerBlock];
-    for (int r = 0; r < K; ++r) {
+    const int r = blockIdx.x;
+    {
         const double ssq = sum_col<K>(part, nblk, r, red);
         if (threadIdx.x == 0 && !sc[r].done) {
             Scalars& s = sc[r];
@@ -3613,34 +3640,13 @@ __global__ __launch_bounds__(kBlock) void k_scalar_init_alpha(const double* __re
 }
 
 template <int K>
-__global__ __launch_bounds__(kBlock) void k_scalar_beta(const double* __restrict__ part, int nblk,
-                                                         Scalars* __restrict__ sc)
-{
-    __shared__ double red[kWavesPerBlock];
-    for (int r = 0; r < K; ++r) {
-        if (sc[r].done) continue;
-        const double ssq = sum_col<K>(part, nblk, r, red);
-        if (threadIdx.x == 0) {
-            Scalars& s = sc[r];
-            const double beta = sqrt(ssq);
-            s.beta = beta;
-            if (beta > 0.0) {
-                s.anorm = sqrt(s.anorm * s.anorm + s.alpha * s.alpha + beta * beta);
-                s.beta_zero = 0;
-            } else {
-                s.beta_zero = 1;
-            }
-        }
-    }
-}
-
-template <int K>
 __global__ __launch_bounds__(kBlock) void k_scalar_alpha(const double* __restrict__ part,
                                                           int nblk, Scalars* __restrict__ sc)
 {
     __shared__ double red[kWavesPerBlock];
-    for (int r = 0; r < K; ++r) {
-        if (sc[r].done) continue;
+    const int r = blockIdx.x;
+    {
+        if (sc[r].done) return;
         const double ssq = sum_col<K>(part, nblk, r, red);
         if (threadIdx.x == 0) {
             Scalars& s = sc[r];
@@ -3676,8 +3682,9 @@ __global__ __launch_bounds__(kBlock) void k_scalar_stop(const double* __restrict
                                                          int nblk, Scalars* __restrict__ sc)
 {
     __shared__ double red[kWavesPerBlock];
-    for (int r = 0; r < K; ++r) {
-        if (sc[r].done) continue;
+    const int r = blockIdx.x;
+    {
+        if (sc[r].done) return;
         const double dd = sum_col<K>(part_dd, nblk, r, red);
         const double xx = sum_col<K>(part_xx, nblk, r, red);
         if (threadIdx.x == 0) {
@@ -3713,15 +3720,6 @@ __global__ __launch_bounds__(kBlock) void k_scalar_stop(const double* __restrict
             if (istop != 0) s.done = 1;
         }
     }
-}
-
-template <int K>
-__global__ void k_all_done(Scalars* __restrict__ sc, int32_t* __restrict__ flag)
-{
-    if (threadIdx.x != 0) return;
-    int32_t all = 1;
-    for (int r = 0; r < K; ++r) all &= sc[r].done ? 1 : 0;
-    *flag = all;
 }
 
 }  // namespace batched

@@ -237,7 +237,6 @@ struct lsqr_handle {
         double* US1 = nullptr;
         float* US1_32 = nullptr;
         Scalars* sc = nullptr;
-        int32_t* flag = nullptr;
         hipGraphExec_t graph[17] = {};    // FP64 tiles, by K
         int graph_chunk[17] = {};
         hipGraphExec_t graph32[17] = {};  // FP32 inner tiles, by K
@@ -745,15 +744,20 @@ void launch_section_sums(const lsqr_handle* h, const SliceView& att, const Slice
                        att, ins, glob, q, sc);
 }
 
+// The sum of the slices and the end of the row pass before it (k_slice_reduce):
+// its npart partials of the sums of squares (or none) and nblk of the global
+// columns.
 template <typename Acc, int K>
-void launch_slice_reduce(const lsqr_handle* h, const SliceView& V, Acc* q, const Scalars* sc,
+void launch_slice_reduce(const lsqr_handle* h, const SliceView& V, Acc* q, Scalars* sc,
+                         const double* part, int npart, const Acc* gpart, int nblk,
                          hipStream_t st)
 {
     // one block for all right-hand sides of a tile's columns (its K stores share
     // lines) where the columns alone fill the chip, else a block for each
     const int64_t grid = std::min<int64_t>(V.tiles(), (int64_t)h->num_cu * 8);
-    hipLaunchKernelGGL((k_slice_reduce<Acc, K>), dim3(grid, grid < h->num_cu * 2 ? K : 1),
-                       dim3(kBlock), 0, st, V, q, sc);
+    hipLaunchKernelGGL((k_slice_reduce<Acc, K>), dim3(grid + 1, grid < h->num_cu * 2 ? K : 1),
+                       dim3(kBlock), 0, st, V, q, sc, part, npart, gpart, nblk,
+                       q + h->sv.glob_base * K);
 }
 
 // The column steps of an iteration: beta, v~ (with the sections' slices and
@@ -1339,7 +1343,7 @@ void batch_free(lsqr_handle* h)
         }
     dfree(B.U); dfree(B.V); dfree(B.W); dfree(B.Y); dfree(B.VP); dfree(B.Q);
     dfree(B.gpart); dfree(B.part1); dfree(B.partc); dfree(B.partdd); dfree(B.partxx);
-    dfree(B.sc); dfree(B.flag); dfree(B.S2); dfree(B.X3);
+    dfree(B.sc); dfree(B.S2); dfree(B.X3);
     dfree(B.U32); dfree(B.VP32); dfree(B.Q32); dfree(B.gpart32); dfree(B.X332);
     dfree(B.US1); dfree(B.US1_32);
     B.kmax = 0;
@@ -1361,7 +1365,6 @@ lsqr_status batch_alloc_once(lsqr_handle* h, int kmax, bool want64, bool want32)
     LSQR_TRY(dalloc(&B.partdd, (int64_t)h->nbc * kmax));
     LSQR_TRY(dalloc(&B.partxx, (int64_t)h->nbc * kmax));
     LSQR_TRY(dalloc(&B.sc, kmax));
-    LSQR_TRY(dalloc(&B.flag, 1));
     if (want64) {
         LSQR_TRY(dalloc(&B.U, m * kmax));
         LSQR_TRY(dalloc(&B.VP, n * kmax));
@@ -1507,14 +1510,31 @@ void by_sweep(int ks, F&& f)
     f(std::integral_constant<int, 1>());
 }
 
+// The column kernel writes the tile's interleaved attitude copy itself where the
+// section is small (a launch less); its strided stores cost more than the copy
+// kernel on a large one (1e5 starts, 4 right-hand sides: k_col_b 50 -> 83 us
+// against 5 us).
+template <int K>
+bool batch_x3_folded(const lsqr_handle* h)
+{
+    return kAxes * h->sv.n_dfa * K <= (int64_t)h->num_cu * 1024;
+}
+
+// The attitude pass of a tile (attitude mode 1) and the end of the row pass
+// before it (npart, nblk: see k_slice_reduce).
 template <typename T, typename Acc, int K>
-void batch_att_pass(lsqr_handle* h, hipStream_t st)
+void batch_att_pass(lsqr_handle* h, int npart, int nblk, hipStream_t st)
 {
     auto& B = h->batch;
     const TileBufs<Acc> tb = tile_bufs<Acc>(h);
     // at most 2 RHS per histogram sweep: 4 FP64 histograms fill LDS, leave
     // one workgroup per CU and halve the rate of its atomics (1e8 rows, 64
     // buckets: one 4-RHS sweep 6.3 ms, two 2-RHS sweeps 2 x 2.15 ms)
+    if (h->att_mode == 0) {
+        launch_slice_reduce<Acc, K>(h, kNoSlices, tb.Q, B.sc, B.part1, npart,
+                                    (const Acc*)tb.gpart, nblk, st);
+        return;
+    }
     const int ks = std::min(2, att_sweep<K>(h));
     by_sweep<K>(ks, [&](auto KS) {
         hipLaunchKernelGGL((k_att_hist<T, Acc, K, KS(), kAttBlock>),
@@ -1524,11 +1544,13 @@ void batch_att_pass(lsqr_handle* h, hipStream_t st)
                            (const int64_t*)h->bstart, h->bwidth, h->att_g, (const Acc*)tb.U,
                            B.S2, att_slices(h), B.sc, (const int32_t*)nullptr);
     });
-    launch_slice_reduce<Acc, K>(h, att_slice_view(h, B.S2), tb.Q, B.sc, st);
+    launch_slice_reduce<Acc, K>(h, att_slice_view(h, B.S2), tb.Q, B.sc, B.part1, npart,
+                                    (const Acc*)tb.gpart, nblk, st);
 }
 
+// npart: partials of the sums of squares that precede it in an iteration.
 template <typename T, typename Acc, int K>
-void batch_aprod2(lsqr_handle* h, hipStream_t st)
+void batch_aprod2(lsqr_handle* h, int npart, hipStream_t st)
 {
     auto& B = h->batch;
     const TileBufs<Acc> tb = tile_bufs<Acc>(h);
@@ -1556,10 +1578,8 @@ void batch_aprod2(lsqr_handle* h, hipStream_t st)
                                lds, st, h->sv, (const Acc*)tb.U, tb.Q, h->wb, tb.gpart, hc, B.sc,
                                batch_row_map(h));
     }
-    hipLaunchKernelGGL((batched::k_glob_sum<Acc, K>), dim3(1), dim3(kBlock), 0, st,
-                       (const Acc*)tb.gpart, grid, tb.Q + h->sv.glob_base * K, B.sc);
     launch_instr_tail<T, Acc, K, false>(h, (const Acc*)tb.U, batch_row_map(h), tb.Q, hc, B.sc, st);
-    if (h->att_mode != 0) batch_att_pass<T, Acc, K>(h, st);
+    batch_att_pass<T, Acc, K>(h, npart, grid, st);
 }
 
 template <typename T, typename Acc, int K, bool LDSX, int AM>
@@ -1622,9 +1642,11 @@ void batch_fused(lsqr_handle* h, hipStream_t st)
     const bool pre = h->fused >= 2;  // fused mode 3 runs as 2 in k-tiles
     const Acc* X3 = nullptr;
     if (h->att_il || pre) {
-        hipLaunchKernelGGL((batched::k_interleave_att<Acc, K>), dim3(h->nbc), dim3(kBlock), 0, st,
-                           (const Acc*)tb.VP, (int64_t)K, h->sv.att_base, h->sv.n_dfa, tb.X3);
         X3 = tb.X3;
+        if (!batch_x3_folded<K>(h))
+            hipLaunchKernelGGL((batched::k_interleave_att<Acc, K>), dim3(h->nbc), dim3(kBlock), 0,
+                               st, (const Acc*)tb.VP, (int64_t)K, h->sv.att_base, h->sv.n_dfa,
+                               tb.X3);
     }
     if (pre) {
         const int ks = att_sweep<K>(h, (int64_t)sizeof(Acc));
@@ -1663,32 +1685,27 @@ void batch_iteration(lsqr_handle* h, hipStream_t st, hipEvent_t* ev)
     if (use_fused(h)) {
         batch_fused<T, Acc, K>(h, st);
         if (ev) (void)hipEventRecord(ev[1], st);
-        hipLaunchKernelGGL((batched::k_scalar_beta<K>), dim3(1), dim3(kBlock), 0, st, B.part1,
-                           batch_fused_grid<K>(h), B.sc);
         if (ev) (void)hipEventRecord(ev[2], st);
-        hipLaunchKernelGGL((batched::k_glob_sum<Acc, K>), dim3(1), dim3(kBlock), 0, st,
-                           (const Acc*)tb.gpart, batch_fused_grid<K>(h),
-                           tb.Q + h->sv.glob_base * K, B.sc);
-        batch_att_pass<T, Acc, K>(h, st);
+        batch_att_pass<T, Acc, K>(h, batch_fused_grid<K>(h), batch_fused_grid<K>(h), st);
     } else if constexpr (K <= 8) {
         hipLaunchKernelGGL((batched::k_aprod1<T, Acc, K>), dim3(h->nbr), dim3(kBlock), 0, st,
                            h->sv, (const Acc*)tb.VP, tb.U, B.sc, B.part1, batch_row_map(h));
         if (ev) (void)hipEventRecord(ev[1], st);
-        hipLaunchKernelGGL((batched::k_scalar_beta<K>), dim3(1), dim3(kBlock), 0, st, B.part1,
-                           h->nbr, B.sc);
         if (ev) (void)hipEventRecord(ev[2], st);
-        batch_aprod2<T, Acc, K>(h, st);
+        batch_aprod2<T, Acc, K>(h, h->nbr, st);
     }
     if (ev) (void)hipEventRecord(ev[3], st);
     hipLaunchKernelGGL((batched::k_col_a<Acc, K>), dim3(h->nbc), dim3(kBlock), 0, st, n, h->p,
                        tb.Q, B.V, B.sc, B.partc);
-    hipLaunchKernelGGL((batched::k_scalar_alpha<K>), dim3(1), dim3(kBlock), 0, st, B.partc, h->nbc,
+    hipLaunchKernelGGL((batched::k_scalar_alpha<K>), dim3(K), dim3(kBlock), 0, st, B.partc, h->nbc,
                        B.sc);
-    hipLaunchKernelGGL((batched::k_col_b<Acc, K>), dim3(h->nbc), dim3(kBlock), 0, st, n, h->p,
-                       B.V, B.W, B.Y, tb.VP, B.sc, B.partdd, B.partxx);
-    hipLaunchKernelGGL((batched::k_scalar_stop<K>), dim3(1), dim3(kBlock), 0, st, B.partdd,
+    by_flag(batch_x3_folded<K>(h), [&](auto fold) {
+        hipLaunchKernelGGL((batched::k_col_b<Acc, K, decltype(fold)::value>), dim3(h->nbc),
+                           dim3(kBlock), 0, st, n, h->p, B.V, B.W, B.Y, tb.VP, tb.X3,
+                           h->sv.att_base, h->sv.n_dfa, B.sc, B.partdd, B.partxx);
+    });
+    hipLaunchKernelGGL((batched::k_scalar_stop<K>), dim3(K), dim3(kBlock), 0, st, B.partdd,
                        B.partxx, h->nbc, B.sc);
-    hipLaunchKernelGGL((batched::k_all_done<K>), dim3(1), dim3(kWave), 0, st, B.sc, B.flag);
 }
 
 // Uploads the controls of a tile's K scalar sets (rel_ar > 0: the relative
@@ -1722,23 +1739,25 @@ lsqr_status batch_init(lsqr_handle* h)
     const TileBufs<Acc> tb = tile_bufs<Acc>(h);
     hipStream_t st = h->stream;
     const int64_t n = h->sv.n;
-    hipLaunchKernelGGL((batched::k_scalar_init_beta<K>), dim3(1), dim3(kBlock), 0, st, B.part1,
+    hipLaunchKernelGGL((batched::k_scalar_init_beta<K>), dim3(K), dim3(kBlock), 0, st, B.part1,
                        h->nbr, B.sc);
     hipLaunchKernelGGL((k_fill<Acc>), dim3(h->nbc), dim3(kBlock), 0, st, n * K, tb.Q, (Acc)0);
     hipLaunchKernelGGL((k_fill<double>), dim3(h->nbc), dim3(kBlock), 0, st, n * K, B.V, 0.0);
-    batch_aprod2<T, Acc, K>(h, st);
+    batch_aprod2<T, Acc, K>(h, 0, st);
     hipLaunchKernelGGL((batched::k_col_a<Acc, K>), dim3(h->nbc), dim3(kBlock), 0, st, n, h->p,
                        tb.Q, B.V, B.sc, B.partc);
-    hipLaunchKernelGGL((batched::k_scalar_init_alpha<K>), dim3(1), dim3(kBlock), 0, st, B.partc,
+    hipLaunchKernelGGL((batched::k_scalar_init_alpha<K>), dim3(K), dim3(kBlock), 0, st, B.partc,
                        h->nbc, B.sc);
-    hipLaunchKernelGGL((batched::k_col_init<Acc, K>), dim3(h->nbc), dim3(kBlock), 0, st, n, h->p,
-                       B.V, B.W, B.Y, tb.VP, B.sc);
-    hipLaunchKernelGGL((batched::k_all_done<K>), dim3(1), dim3(kWave), 0, st, B.sc, B.flag);
+    by_flag(batch_x3_folded<K>(h), [&](auto fold) {
+        hipLaunchKernelGGL((batched::k_col_init<Acc, K, decltype(fold)::value>), dim3(h->nbc),
+                           dim3(kBlock), 0, st, n, h->p, B.V, B.W, B.Y, tb.VP, tb.X3,
+                           h->sv.att_base, h->sv.n_dfa, B.sc);
+    });
     HIP_TRY(hipGetLastError());
     return LSQR_OK;
 }
 
-// Runs the tile's iterations in graph-replayed chunks (one flag read per
+// Runs the tile's iterations in graph-replayed chunks (the states read once per
 // chunk) until every RHS has stopped (or max_chunks chunks, if > 0); host
 // receives the K scalar sets at the end.
 template <typename T, typename Acc, int K>
@@ -1772,9 +1791,15 @@ lsqr_status batch_run(lsqr_handle* h, int32_t itn_limit, int max_chunks, Scalars
             h->events.push_back(e);
         }
     }
-    int32_t done = 0;
-    HIP_TRY(hipMemcpyAsync(&done, B.flag, sizeof done, hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipStreamSynchronize(st));
+    auto read = [&](bool* done) -> lsqr_status {  // the K states; every RHS stopped?
+        HIP_TRY(hipMemcpyAsync(host, B.sc, K * sizeof(Scalars), hipMemcpyDeviceToHost, st));
+        HIP_TRY(hipStreamSynchronize(st));
+        *done = true;
+        for (int r = 0; r < K; ++r) *done = *done && host[r].done;
+        return LSQR_OK;
+    };
+    bool done = false;
+    LSQR_TRY(read(&done));
     int32_t itn_seen = 0;
     for (int c = 0; !done && itn_limit > 0 && (max_chunks <= 0 || c < max_chunks); ++c) {
         if (graph) {
@@ -1784,9 +1809,7 @@ lsqr_status batch_run(lsqr_handle* h, int32_t itn_limit, int max_chunks, Scalars
                 batch_iteration<T, Acc, K>(h, st, h->profile ? &h->events[4 * k] : nullptr);
             HIP_TRY(hipGetLastError());
         }
-        HIP_TRY(hipMemcpyAsync(host, B.sc, K * sizeof(Scalars), hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipMemcpyAsync(&done, B.flag, sizeof done, hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipStreamSynchronize(st));
+        LSQR_TRY(read(&done));
         int32_t itn_max = 0;
         for (int r = 0; r < K; ++r) itn_max = std::max(itn_max, host[r].itn);
         if (h->profile) {
@@ -1805,8 +1828,6 @@ lsqr_status batch_run(lsqr_handle* h, int32_t itn_limit, int max_chunks, Scalars
             return fail(LSQR_E_HIP, "batched LSQR made no progress (itn %d)", itn_max);
         itn_seen = itn_max;
     }
-    HIP_TRY(hipMemcpyAsync(host, B.sc, K * sizeof(Scalars), hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipStreamSynchronize(st));
     return LSQR_OK;
 }
 
