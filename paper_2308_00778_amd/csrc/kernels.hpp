@@ -2044,7 +2044,8 @@ __global__ __launch_bounds__(kBlock) void k_compact_idx(SysView s, int32_t* __re
          i += (int64_t)gridDim.x * kBlock) {
         star32[i] = (int32_t)s.star[i];
 #pragma unroll
-        for (int j = 0; j < kInstr; ++j) instr16[j * s.m + i] = (uint16_t)s.instr[j * s.m + i];
+        for (int j = 0; j < kInstr; ++j)
+            if (j < s.ni) instr16[j * s.m + i] = (uint16_t)s.instr[j * s.m + i];
     }
 }
 
@@ -2131,7 +2132,7 @@ __global__ __launch_bounds__(kBlock) void k_att_gather(const T* __restrict__ val
                                                         const int32_t* __restrict__ perm,
                                                         int64_t width, int off_att, int64_t ld,
                                                         T* __restrict__ att_sorted,
-                                                        int32_t* __restrict__ tloc)
+                                                        uint16_t* __restrict__ tloc)
 {
     constexpr int kAtt = kAxes * kParAxis;
     for (int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x; k < m;
@@ -2140,7 +2141,7 @@ __global__ __launch_bounds__(kBlock) void k_att_gather(const T* __restrict__ val
 #pragma unroll
         for (int c = 0; c < kAtt; ++c) att_sorted[c * ld + k] = val[(off_att + c) * m + i];
         const int64_t t = att[i];
-        tloc[k] = (int32_t)(t - (t / width) * width);
+        tloc[k] = (uint16_t)(t - (t / width) * width);  // width < 2^16: a window fits in LDS
     }
 }
 
@@ -2174,7 +2175,7 @@ __global__ __launch_bounds__(kBlock) void k_att_gather(const T* __restrict__ val
 template <typename T, typename Acc, int K, int KS, int NT, bool SEP = false,
           bool PIPE = (KS * sizeof(Acc) <= 8), bool GATED = false, bool PLAIN = false>
 __global__ __launch_bounds__(NT) void k_att_dot(int64_t ld, const T* __restrict__ att_sorted,
-                                                 const int32_t* __restrict__ tloc,
+                                                 const uint16_t* __restrict__ tloc,
                                                  const int64_t* __restrict__ bstart,
                                                  int64_t width, int G, int64_t n_dfa,
                                                  const Acc* __restrict__ x3, Acc* __restrict__ u,
@@ -2342,7 +2343,7 @@ __global__ __launch_bounds__(NT) void k_att_dot(int64_t ld, const T* __restrict_
 template <typename T, typename Acc, int K, int KS, int NT, bool GATHER = false,
           bool PIPE = (KS <= 2), bool PLAIN = false>
 __global__ __launch_bounds__(NT) void k_att_hist(int64_t ld, const T* __restrict__ att_sorted,
-                                                  const int32_t* __restrict__ tloc,
+                                                  const uint16_t* __restrict__ tloc,
                                                   const int64_t* __restrict__ bstart,
                                                   int64_t width, int G, const Acc* __restrict__ U,
                                                   double* __restrict__ S2, int64_t slices,

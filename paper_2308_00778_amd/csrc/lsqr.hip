@@ -195,7 +195,7 @@ struct lsqr_handle {
     // attitude bucket order (built on first use in attitude mode 1)
     int32_t* perm = nullptr;      // [m] rows in bucket order
     int32_t* invperm = nullptr;   // [m] bucket-order position of each row
-    int32_t* tloc = nullptr;      // [m] attitude start minus its bucket's first start
+    uint16_t* tloc = nullptr;     // [m] attitude start minus its bucket's first start
     void* att_sorted = nullptr;   // [12][att_ld] attitude coefficients in bucket order
     int64_t att_ld = 0;           // its column stride: m rounded up to 64 rows
     int64_t* bstart = nullptr;    // [nbk + 1] first position of each bucket
@@ -566,9 +566,9 @@ void launch_fused_as(const lsqr_handle* h, Path<Acc>& P, const Acc* x3, const Ga
     // kAttGather reads the pre-pass output through invperm; u~ is in star order
     const int32_t* inv = AM == kAttGather ? (const int32_t*)h->invperm : row_map(h);
     const Acc* datt = AM == kAttGather ? (const Acc*)P.datt : nullptr;
-    by_flag(GEN == 0 && h->sv.star32 != nullptr, [&](auto cidx) {
+    by_flag(h->sv.star32 != nullptr, [&](auto cidx) {
         by_flag(AM == kAttPre && plain_on(h), [&](auto plain) {
-            constexpr bool C = decltype(cidx)::value && GEN == 0;
+            constexpr bool C = decltype(cidx)::value;
             constexpr bool PL = decltype(plain)::value && AM == kAttPre;
             hipLaunchKernelGGL((k_fused<T, Acc, kBlock2, LDSX, AM, C, GEN, false, false, PL>),
                                dim3(h->nb2), dim3(kBlock2), P.lds_f, st, h->sv, (const Acc*)P.vp,
@@ -611,10 +611,11 @@ void launch_one_pass(const lsqr_handle* h, const Acc* x, const Acc* x3, Acc* u, 
         else if (win == 1) go(Y(), N(), cidx, gen);
         else go(N(), N(), cidx, gen);
     };
-    if (h->generic && h->sv.ng > 1) by_win(N(), std::integral_constant<int, kGlobMax>());
-    else if (h->generic) by_win(N(), std::integral_constant<int, 1>());
-    else if (h->sv.star32) by_win(Y(), std::integral_constant<int, 0>());
-    else by_win(N(), std::integral_constant<int, 0>());
+    by_flag(h->sv.star32 != nullptr, [&](auto cidx) {
+        if (h->generic && h->sv.ng > 1) by_win(cidx, std::integral_constant<int, kGlobMax>());
+        else if (h->generic) by_win(cidx, std::integral_constant<int, 1>());
+        else by_win(cidx, std::integral_constant<int, 0>());
+    });
 }
 
 // Attitude part of aprod1 in bucket order (x3 must hold the interleaved
@@ -629,7 +630,7 @@ void launch_att_dot_as(const lsqr_handle* h, Path<Acc>& P, const Gate& gate, hip
         hipLaunchKernelGGL((k_att_dot<T, Acc, 1, 1, kAttBlock, SEP, PIPE, true, PL>),
                            dim3(side_grid(att_slices(h), 1)),
                            dim3(kAttBlock), lds, st, h->att_ld, (const T*)h->att_sorted,
-                           (const int32_t*)h->tloc, (const int64_t*)h->bstart, h->bwidth, h->att_g,
+                           (const uint16_t*)h->tloc, (const int64_t*)h->bstart, h->bwidth, h->att_g,
                            h->sv.n_dfa, (const Acc*)P.vp3, SEP ? P.datt : P.u, att_slices(h),
                            (const Scalars*)nullptr,
                            gate);
@@ -653,7 +654,7 @@ void launch_att_part(const lsqr_handle* h, const Acc* x3, Acc* datt, hipStream_t
     hipLaunchKernelGGL((k_att_dot<T, Acc, 1, 1, kAttBlock, true, true, true>),
                        dim3(side_grid(att_slices(h), 1)), dim3(kAttBlock),
                        (size_t)(kAxes * att_span(h)) * sizeof(Acc), st, h->att_ld,
-                       (const T*)h->att_sorted, (const int32_t*)h->tloc,
+                       (const T*)h->att_sorted, (const uint16_t*)h->tloc,
                        (const int64_t*)h->bstart, h->bwidth, h->att_g, h->sv.n_dfa, x3, datt,
                        att_slices(h), (const Scalars*)nullptr, Gate{});
 }
@@ -788,7 +789,7 @@ void launch_att_pass(lsqr_handle* h, const Acc* ub, const Scalars* sc, hipStream
         hipLaunchKernelGGL((k_att_hist<T, Acc, 1, 1, kAttBlock, decltype(gather)::value,
                                        decltype(pipe)::value, decltype(plain)::value>),
                            dim3(side_grid(att_slices(h), 1)), dim3(kAttBlock), lds, st, h->att_ld,
-                           (const T*)h->att_sorted, (const int32_t*)h->tloc,
+                           (const T*)h->att_sorted, (const uint16_t*)h->tloc,
                            (const int64_t*)h->bstart, h->bwidth, h->att_g, ub, h->S2,
                            att_slices(h), sc, gperm);
     };
@@ -1152,15 +1153,16 @@ constexpr int64_t kCompactMemFraction = 32;
 
 lsqr_status ensure_compact(lsqr_handle* h)
 {
-    if (!h->compact || h->compact_tried || h->generic) return LSQR_OK;
+    // general layouts: where the single-RHS fused passes serve them
+    if (!h->compact || h->compact_tried || (h->generic && fused_mode(h) == 0)) return LSQR_OK;
     h->compact_tried = 1;
     const int64_t m = h->sv.m;
     if (h->sv.n_stars > INT32_MAX || h->sv.n_instr_cols > 65536) return LSQR_OK;
     size_t free_b = 0, total_b = 0;
     if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) return LSQR_OK;
-    const int64_t need = m * (int64_t)(sizeof(int32_t) + kInstr * sizeof(uint16_t));
+    const int64_t need = m * (int64_t)(sizeof(int32_t) + h->sv.ni * sizeof(uint16_t));
     if (need > (int64_t)(total_b / kCompactMemFraction) || need >= (int64_t)free_b) return LSQR_OK;
-    if (dalloc(&h->star32, m) != LSQR_OK || dalloc(&h->instr16, (int64_t)kInstr * m) != LSQR_OK) {
+    if (dalloc(&h->star32, m) != LSQR_OK || dalloc(&h->instr16, (int64_t)h->sv.ni * m) != LSQR_OK) {
         dfree(h->star32);
         dfree(h->instr16);
         g_last_error.clear();  // not an error: the fused passes use the caller's arrays
@@ -1540,7 +1542,7 @@ void batch_att_pass(lsqr_handle* h, int npart, int nblk, hipStream_t st)
         hipLaunchKernelGGL((k_att_hist<T, Acc, K, KS(), kAttBlock>),
                            dim3(side_grid(att_slices(h), K / KS())),
                            dim3(kAttBlock), (size_t)(kAxes * att_span(h) * 8 * ks), st, h->att_ld,
-                           (const T*)h->att_sorted, (const int32_t*)h->tloc,
+                           (const T*)h->att_sorted, (const uint16_t*)h->tloc,
                            (const int64_t*)h->bstart, h->bwidth, h->att_g, (const Acc*)tb.U,
                            B.S2, att_slices(h), B.sc, (const int32_t*)nullptr);
     });
@@ -1654,7 +1656,7 @@ void batch_fused(lsqr_handle* h, hipStream_t st)
             hipLaunchKernelGGL((k_att_dot<T, Acc, K, KS(), kAttBlock>),
                                dim3(side_grid(att_slices(h), K / KS())),
                                dim3(kAttBlock), (size_t)(kAxes * att_span(h) * sizeof(Acc) * ks),
-                               st, h->att_ld, (const T*)h->att_sorted, (const int32_t*)h->tloc,
+                               st, h->att_ld, (const T*)h->att_sorted, (const uint16_t*)h->tloc,
                                (const int64_t*)h->bstart, h->bwidth, h->att_g, h->sv.n_dfa, X3,
                                tb.U, att_slices(h), (const Scalars*)B.sc);
         });
