@@ -4,13 +4,14 @@
 // held as structure-of-arrays: coefficient c of row i at values[c*m + i], so
 // that a wave streams 64 consecutive rows of one coefficient as one coalesced
 // 512-byte (FP64) or 256-byte (FP32) request. Index arrays follow the same
-// layout. All streaming loads carry the nontemporal hint so that the matrix
-// does not evict the gathered vector sections from L2.
+// layout. Streaming loads carry the nontemporal hint so that the matrix does not
+// evict the gathered vector sections from L2, except where the last-level cache
+// holds the matrix from one iteration to the next (kPlain).
 //
 // Kernels:
 //   k_aprod1      y = A x (+ mode-specific update), one row per lane, grid
-//                 stride, two rows in flight per lane; FP64 sum of squares of
-//                 the written y per block (the beta norm of the LSQR step).
+//                 stride; FP64 sum of squares of the written y per block (the
+//                 beta norm of the LSQR step).
 //   k_aprod2      x += A^T y over star-aligned per-wave row ranges:
 //                   astrometric: segmented reduction over the star key (rows
 //                     are sorted by star), plain stores, no atomics;
@@ -22,13 +23,16 @@
 //                   instrumental: workgroup-private LDS histogram, flushed
 //                     once per workgroup (k_instr_tail beyond its columns);
 //                   global: wave shuffle -> LDS -> per-workgroup partial,
-//                     summed in a deterministic second stage (k_glob_sum).
-//   k_fused       one sweep doing aprod1 and the non-attitude part of aprod2
-//                 of an LSQR step (the attitude dot product optionally first,
-//                 by k_att_dot in bucket order).
-//   k_col_a/b     column-vector updates of the LSQR step (FP64).
-//   k_scalar_*    single-workgroup kernels: norm finishers, Givens rotation,
-//                 estimates and stopping tests, all FP64.
+//                     summed in a deterministic second stage.
+//   k_fused       one sweep doing aprod1 and aprod2 of an LSQR step, with both
+//                 histograms in LDS where they fit, else without the attitude
+//                 section (k_att_dot before and k_att_hist after it, in bucket
+//                 order).
+//   k_col_a/b     column-vector updates of the LSQR step (FP64), with the norms
+//                 and the Givens rotation in every workgroup; the estimates and
+//                 stopping tests run in the next row pass.
+//   k_scalar_*    single-workgroup kernels: the norms at the start, the tests
+//                 after a launch's last iteration, all FP64.
 //   namespace batched: the same steps for a k-tile of right-hand sides.
 #pragma once
 
@@ -733,9 +737,6 @@ __device__ __forceinline__ V by_words(V a, F&& f)
 template <typename V>
 __device__ __forceinline__ V half_sum(V a, V b)
 {
-    auto swap = [](uint32_t x, uint32_t y, int k) {
-        return (uint32_t)__builtin_amdgcn_permlane32_swap(x, y, false, false)[k];
-    };
     if constexpr (sizeof(V) == 8) {
         const uint64_t x = __builtin_bit_cast(uint64_t, a), y = __builtin_bit_cast(uint64_t, b);
         const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)y, false, false);
@@ -745,7 +746,8 @@ __device__ __forceinline__ V half_sum(V a, V b)
                __builtin_bit_cast(V, (uint64_t)lo[1] | ((uint64_t)hi[1] << 32));
     } else {
         const uint32_t x = __builtin_bit_cast(uint32_t, a), y = __builtin_bit_cast(uint32_t, b);
-        return __builtin_bit_cast(V, swap(x, y, 0)) + __builtin_bit_cast(V, swap(x, y, 1));
+        const auto r = __builtin_amdgcn_permlane32_swap(x, y, false, false);
+        return __builtin_bit_cast(V, (uint32_t)r[0]) + __builtin_bit_cast(V, (uint32_t)r[1]);
     }
 }
 
@@ -896,7 +898,7 @@ __device__ __forceinline__ void seg_flush(int64_t key, const Acc (&v)[NV], int l
 // accumulated in an FP64 LDS histogram (hcols * 8 bytes of dynamic shared
 // memory) flushed with one device atomic per column per workgroup; columns
 // from hcols on are left to k_instr_tail. gpart[blockIdx.x] gets the
-// workgroup's global-column partial; k_glob_sum adds them up.
+// workgroup's global-column partial; a later kernel adds them up.
 // ATT = false leaves the attitude columns to the bucket-order pass
 // (k_att_hist) and skips loading them. SCAN selects the astrometric
 // reduction: a segmented scan every chunk (true) or the accumulate-and-flush
@@ -1074,7 +1076,9 @@ __global__ __launch_bounds__(NT) void k_aprod2(SysView s, const VU* __restrict__
 // The rows are dealt to the waves in whole 64-row steps, an equal number each
 // but for one (WaveSteps), not in ranges that begin with a star: a range of a
 // few steps otherwise takes one or two more, and the waves wait for the
-// longest (1e5 rows of 100-row stars: three steps where one does, 18.2 -> us).
+// longest (a solve of 1e6 rows, layout 3 + 12 + 2 + 3: 3.00 -> 2.42 ms). Stars
+// cut by a step's end make more star sums, which pays with lane swaps only: with
+// ds_bpermute sums a solve of 3e5 rows was 9% slower.
 enum { kAttX = 0, kAttX3 = 1, kAttPre = 2, kAttGather = 3, kAttAll = 4 };
 
 // Step ranges of the waves: wave w takes `each` 64-row steps, and one more if
