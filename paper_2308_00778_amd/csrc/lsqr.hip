@@ -551,6 +551,16 @@ inline Gate gate_of(const lsqr_handle* h, bool pending)
     return {pending ? h->sc + 1 : nullptr, h->sc, h->partdd, h->partxx, h->nbc};
 }
 
+// Where the waves of a workgroup take pieces of its rows in turn (k_fused): the
+// open lines of u~, one of 128 bytes per bucket and wave otherwise, would take
+// more than half of the 32 MB of L2 (32 buckets), and a wave has more steps
+// than a few pieces.
+constexpr int kPiece = 4;
+inline bool fused_pieces(const lsqr_handle* h)
+{
+    return h->nbk > 32 && h->sv.m / kWave >= h->nw * 16 * kPiece;
+}
+
 // The rows of the fused pass's h->nw waves.
 inline WaveSteps wave_steps(const lsqr_handle* h)
 {
@@ -571,10 +581,14 @@ void launch_fused_as(const lsqr_handle* h, Path<Acc>& P, const Acc* x3, const Ga
         by_flag(AM == kAttPre && plain_on(h), [&](auto plain) {
             constexpr bool C = decltype(cidx)::value;
             constexpr bool PL = decltype(plain)::value && AM == kAttPre;
-            hipLaunchKernelGGL((k_fused<T, Acc, kBlock2, LDSX, AM, C, GEN, false, false, PL>),
-                               dim3(h->nb2), dim3(kBlock2), P.lds_f, st, h->sv, (const Acc*)P.vp,
-                               x3, P.u, P.q, wave_steps(h), P.gpart, h->part1, P.f_hcols, gate,
-                               inv, datt, P.ustar, (double*)nullptr, (double*)nullptr);
+            by_flag(AM == kAttPre && !PL && fused_pieces(h), [&](auto pieces) {
+                constexpr int PC = decltype(pieces)::value && AM == kAttPre && !PL ? kPiece : 0;
+                hipLaunchKernelGGL(
+                    (k_fused<T, Acc, kBlock2, LDSX, AM, C, GEN, false, false, PL, PC>),
+                    dim3(h->nb2), dim3(kBlock2), P.lds_f, st, h->sv, (const Acc*)P.vp, x3, P.u, P.q,
+                    wave_steps(h), P.gpart, h->part1, P.f_hcols, gate, inv, datt, P.ustar,
+                    (double*)nullptr, (double*)nullptr);
+            });
         });
     });
 }

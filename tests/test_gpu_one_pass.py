@@ -164,3 +164,30 @@ def test_zero_residual_keeps_solution(torch_cuda, buckets):
     g.close()
     assert info.itn == 2 and info.rnorm == 0.0
     assert got[0] == 2.0 and np.all(got[1:] == 0.0)
+
+
+# Beyond 32 buckets, from 64 steps of 64 rows a wave (4,194,304 x 4 rows with 256
+# CUs), the star-order pass deals its rows in pieces; with 32 buckets it does not.
+# The two solves differ in the order of sums only: 1e-10 as against the oracle.
+def test_pieces_agree_with_ranges(torch_cuda):
+    torch = torch_cuda
+    from paper_2308_00778_amd import LsqrSystem
+
+    spec = synth.tiny(seed=23, n_stars=175003, obs=(50, 150), n_dfa=20011, n_instr_cols=203)
+    arrays, first = synth.device_system(spec, "cuda:0")
+    m = int(first[-1])
+    say(f"pieces: m={m}")
+    assert m > 64 * 64 * 16 * torch.cuda.get_device_properties(0).multi_processor_count
+    b = synth.device_noise(spec, m, 0, "cuda:0")
+    xs = []
+    for buckets in (33, 62, 32):
+        g = LsqrSystem(**arrays, n_stars=spec.n_stars, n_dfa=spec.n_dfa,
+                       n_instr_cols=spec.n_instr_cols)
+        g.set_option("tests", 0)
+        g.set_option("att_buckets", buckets)
+        x, info = g.solve(b, 6, atol=0.0, btol=0.0)
+        assert info.itn == 6
+        xs.append(x.cpu().numpy())
+        g.close()
+    assert rel_inf(xs[0], xs[2]) <= 1e-10
+    assert rel_inf(xs[1], xs[2]) <= 1e-10
