@@ -3216,9 +3216,21 @@ __device__ __forceinline__ constexpr int rl_col(int e)
     return e < kAstro ? e : kOffInstr + (e - kAstro);
 }
 
+// A step reads 64 / K entries of BYTES of a column. Where that is less than a line
+// of 128 bytes the next step reads on in it: loaded plain it is then still in L2,
+// nontemporal it may be gone (2e7 rows, FP32, 4 right-hand
+// sides, a refined solve: 223.3 -> 220.8 ms).
+// PL: all loads plain, for a matrix that the last-level cache holds (1.2e6 rows,
+// FP64, 4 right-hand sides: 9.05 -> 8.69 ms; 1e7 rows 286.5 -> 290.0 ms).
+template <bool PL, int K, int BYTES>
+constexpr bool rl_plain()
+{
+    return PL || kWave / K * BYTES < 128;
+}
+
 // The loads of load_row_rl for K in {2, 4}, before the broadcast: lane r of a
 // row slot loads entries r, r + K, ... of the 12 coefficients and 6 indices.
-template <typename T, int K, bool CIDX>
+template <typename T, int K, bool CIDX, bool PL>
 __device__ __forceinline__ void load_raw_rl(const SysView& s, const T* __restrict__ val,
                                             int64_t ic, int rj, T (&tv)[rl_nv<K>()],
                                             int32_t (&ti)[rl_ni<K>()])
@@ -3226,11 +3238,12 @@ __device__ __forceinline__ void load_raw_rl(const SysView& s, const T* __restric
     static_assert(K == 2 || K == 4, "row slots of 2 or 4 lanes");
     const int64_t m = s.m;
 #pragma unroll
-    for (int t = 0; t < rl_nv<K>(); ++t) tv[t] = ldnt(&val[rl_col(t * K + rj) * m + ic]);
+    for (int t = 0; t < rl_nv<K>(); ++t) tv[t] =
+        ld_stream<rl_plain<PL, K, sizeof(T)>()>(&val[rl_col(t * K + rj) * m + ic]);
 #pragma unroll
     for (int t = 0; t < rl_ni<K>(); ++t) {
         const int j = t * K + rj < kInstr ? t * K + rj : kInstr - 1;
-        ti[t] = instr_of<CIDX>(s, j, ic);
+        ti[t] = instr_of<CIDX, rl_plain<PL, K, CIDX ? 2 : 4>()>(s, j, ic);
     }
 }
 
@@ -3267,7 +3280,7 @@ __device__ __forceinline__ void bcast_row_rl(const T (&tv)[rl_nv<K>()],
 // of its row slot together: lane r of the slot loads entries r, r + K, ...
 // and each entry is then broadcast to the K lanes (K in {2, 4}); for other
 // K every lane loads all of them.
-template <typename T, int K, bool CIDX>
+template <typename T, int K, bool CIDX, bool PL>
 __device__ __forceinline__ void load_row_rl(const SysView& s, const T* __restrict__ val,
                                             int64_t ic, int rj, T (&a)[kPar],
                                             int32_t (&ix)[kInstr])
@@ -3275,14 +3288,15 @@ __device__ __forceinline__ void load_row_rl(const SysView& s, const T* __restric
     if constexpr (K == 2 || K == 4) {
         T tv[rl_nv<K>()];
         int32_t ti[rl_ni<K>()];
-        load_raw_rl<T, K, CIDX>(s, val, ic, rj, tv, ti);
+        load_raw_rl<T, K, CIDX, PL>(s, val, ic, rj, tv, ti);
         bcast_row_rl<T, K>(tv, ti, a, ix);
     } else {
         const int64_t m = s.m;
 #pragma unroll
-        for (int e = 0; e < kNaRl; ++e) a[rl_col(e)] = ldnt(&val[rl_col(e) * m + ic]);
+        for (int e = 0; e < kNaRl; ++e)
+            a[rl_col(e)] = ld_stream<rl_plain<PL, K, sizeof(T)>()>(&val[rl_col(e) * m + ic]);
 #pragma unroll
-        for (int j = 0; j < kInstr; ++j) ix[j] = instr_of<CIDX>(s, j, ic);
+        for (int j = 0; j < kInstr; ++j) ix[j] = instr_of<CIDX, rl_plain<PL, K, CIDX ? 2 : 4>()>(s, j, ic);
     }
 }
 
@@ -3301,7 +3315,7 @@ __device__ __forceinline__ void load_row_rl(const SysView& s, const T* __restric
 // the current one, so each step waits one round trip instead of two. Each
 // step keeps its loads in its own registers (no copies, which would wait).
 template <typename T, typename Acc, int K, int NT, bool LDSX, bool CIDX, bool A2,
-          bool PIPE = false>
+          bool PIPE = false, bool PL = false>
 __global__ __launch_bounds__(NT) void k_fused_rl(SysView s, const Acc* __restrict__ VP,
                                                   Acc* __restrict__ U, Acc* __restrict__ Q,
                                                   const int64_t* __restrict__ wb,
@@ -3338,8 +3352,19 @@ __global__ __launch_bounds__(NT) void k_fused_rl(SysView s, const Acc* __restric
     const int slot = lane / K;        // and row slot
     const bool lj = (live >> rj) & 1u;
     const Acc xg = A2 ? (Acc)0 : VP[s.glob_base * K + rj];
-    const int64_t wave = (int64_t)blockIdx.x * W + threadIdx.x / kWave;
-    const int64_t rb = wb[wave], re = wb[wave + 1];
+    // The wave's rows (a bucket order has fewer than 2^31), in scalar registers where
+    // the instrumental slice is in LDS; where it is not, that makes the compiler
+    // spill two registers a step at K = 4 (FP64: 15% slower).
+    uint32_t rb, re;
+    if constexpr (LDSX) {
+        const int32_t wave = uniform((int32_t)(blockIdx.x * W + threadIdx.x / kWave));
+        rb = (uint32_t)uniform((int32_t)wb[wave]);
+        re = (uint32_t)uniform((int32_t)wb[wave + 1]);
+    } else {
+        const int64_t wave = (int64_t)blockIdx.x * W + threadIdx.x / kWave;
+        rb = (uint32_t)wb[wave];
+        re = (uint32_t)wb[wave + 1];
+    }
     Acc* __restrict__ qins = Q + s.instr_base * K;
     double ssq = 0.0;
     Acc gsum = (Acc)0;
@@ -3353,9 +3378,9 @@ __global__ __launch_bounds__(NT) void k_fused_rl(SysView s, const Acc* __restric
     };
     // one R-row step: the row of slot `slot` (clamped), its coefficients,
     // indices, star and place in U already loaded
-    auto step = [&](int64_t r0, int64_t stc, const T (&a)[kPar], const int32_t (&ix)[kInstr],
+    auto step = [&](uint32_t r0, int64_t stc, const T (&a)[kPar], const int32_t (&ix)[kInstr],
                     int64_t pu) {
-        const int64_t i = r0 + slot;
+        const uint32_t i = r0 + slot;
         const bool ok = i >= rb && i < re;
         const int64_t st = i < re ? stc : kNoStar;
         const Acc uo = U[pu * K + rj];
@@ -3371,7 +3396,12 @@ __global__ __launch_bounds__(NT) void k_fused_rl(SysView s, const Acc* __restric
 #pragma unroll
             for (int j = 0; j < kAstro; ++j) dot += (Acc)a[j] * xa[j * K];
 #pragma unroll
-            for (int j = 0; j < kInstr; ++j) dot += (Acc)a[kOffInstr + j] * xi[ix[j] * K + rj];
+            for (int j = 0; j < kInstr; ++j) {
+                // compact indices: offsets below 65536 x 16 x 8 bytes
+                const Acc x = !LDSX && CIDX ? ld_off<true>(xi, (uint32_t)(ix[j] * K + rj))
+                                            : xi[ix[j] * K + rj];
+                dot += (Acc)a[kOffInstr + j] * x;
+            }
             dot += (Acc)a[kOffGlob] * xg;
             const Acc nu = dot + uo;
             if (on) U[pu * K + rj] = nu;
@@ -3394,24 +3424,25 @@ __global__ __launch_bounds__(NT) void k_fused_rl(SysView s, const Acc* __restric
     // R-row steps aligned to R rows (every coefficient stream read in whole
     // R-row pieces); slots outside [rb, re) use a clamped row and contribute
     // nothing
-    auto row_of = [&](int64_t r0) {
-        const int64_t i = r0 + slot;
+    auto row_of = [&](uint32_t r0) -> int64_t {
+        const uint32_t i = r0 + slot;
         return i < rb ? rb : (i < re ? i : re - 1);
     };
-    const int64_t rstart = rb < re ? (rb & ~(int64_t)(R - 1)) : re;
+    const uint32_t rstart = rb < re ? (rb & ~(uint32_t)(R - 1)) : re;
     if constexpr (PIPE && (K == 2 || K == 4) && !A2) {
         struct Raw {
             T tv[rl_nv<K>()];
             int32_t ti[rl_ni<K>()];
-            int64_t stc, pu;
+            std::conditional_t<CIDX, int32_t, int64_t> stc;
+            int32_t pu;
         };
-        auto load = [&](Raw& w, int64_t r0) {
+        auto load = [&](Raw& w, uint32_t r0) {
             const int64_t ic = row_of(r0);
-            w.stc = star_of<CIDX>(s, ic);
-            load_raw_rl<T, K, CIDX>(s, val, ic, rj, w.tv, w.ti);
-            w.pu = inv ? (int64_t)ldnt(&inv[ic]) : ic;
+            w.stc = (decltype(w.stc))star_of<CIDX, rl_plain<PL, K, 4>()>(s, ic);
+            load_raw_rl<T, K, CIDX, PL>(s, val, ic, rj, w.tv, w.ti);
+            w.pu = inv ? ld_stream<rl_plain<PL, K, 4>()>(&inv[ic]) : (int32_t)ic;
         };
-        auto run = [&](const Raw& w, int64_t r0) {
+        auto run = [&](const Raw& w, uint32_t r0) {
             T a[kPar];
             int32_t ix[kInstr];
             bcast_row_rl<T, K>(w.tv, w.ti, a, ix);
@@ -3420,16 +3451,16 @@ __global__ __launch_bounds__(NT) void k_fused_rl(SysView s, const Acc* __restric
         // r0, re and R are uniform over the wave, so are the branches
         if (rstart < re) {
             Raw A, B;
-            int64_t r0 = rstart;
+            uint32_t r0 = rstart;
             load(A, r0);
             for (;;) {
-                const int64_t r1 = r0 + R;
+                const uint32_t r1 = r0 + R;
                 if (r1 < re) load(B, r1);
                 __builtin_amdgcn_sched_barrier(0);
                 run(A, r0);
                 __builtin_amdgcn_sched_barrier(0);
                 if (r1 >= re) break;
-                const int64_t r2 = r1 + R;
+                const uint32_t r2 = r1 + R;
                 if (r2 < re) load(A, r2);
                 __builtin_amdgcn_sched_barrier(0);
                 run(B, r1);
@@ -3439,13 +3470,13 @@ __global__ __launch_bounds__(NT) void k_fused_rl(SysView s, const Acc* __restric
             }
         }
     } else {
-        for (int64_t r0 = rstart; r0 < re; r0 += R) {
+        for (uint32_t r0 = rstart; r0 < re; r0 += R) {
             const int64_t ic = row_of(r0);
-            const int64_t stc = star_of<CIDX>(s, ic);
+            const int64_t stc = star_of<CIDX, rl_plain<PL, K, 4>()>(s, ic);
             T a[kPar];
             int32_t ix[kInstr];
-            load_row_rl<T, K, CIDX>(s, val, ic, rj, a, ix);
-            const int64_t pu = inv ? (int64_t)ldnt(&inv[ic]) : ic;
+            load_row_rl<T, K, CIDX, PL>(s, val, ic, rj, a, ix);
+            const int64_t pu = inv ? (int64_t)ld_stream<rl_plain<PL, K, 4>()>(&inv[ic]) : ic;
             step(r0, stc, a, ix, pu);
         }
     }

@@ -1641,16 +1641,15 @@ void batch_fused_as(lsqr_handle* h, const Acc* X3, int64_t hc, size_t lds, hipSt
             // would spill
             auto go = [&](auto pipe) {
                 constexpr bool P = decltype(pipe)::value;
-                if (h->sv.star32)
-                    hipLaunchKernelGGL(
-                        (batched::k_fused_rl<T, Acc, K, kBlock2, LDSX, true, false, P>),
-                        dim3(h->nb2), dim3(kBlock2), lds, st, h->sv, (const Acc*)tb.VP, tb.U,
-                        tb.Q, h->wb, tb.gpart, B.part1, hc, B.sc, batch_row_map(h));
-                else
-                    hipLaunchKernelGGL(
-                        (batched::k_fused_rl<T, Acc, K, kBlock2, LDSX, false, false, P>),
-                        dim3(h->nb2), dim3(kBlock2), lds, st, h->sv, (const Acc*)tb.VP, tb.U,
-                        tb.Q, h->wb, tb.gpart, B.part1, hc, B.sc, batch_row_map(h));
+                by_flag(h->sv.star32 != nullptr, [&](auto cidx) {
+                    by_flag(plain_on(h), [&](auto plain) {
+                        hipLaunchKernelGGL(
+                            (batched::k_fused_rl<T, Acc, K, kBlock2, LDSX, decltype(cidx)::value,
+                                                 false, P, decltype(plain)::value>),
+                            dim3(h->nb2), dim3(kBlock2), lds, st, h->sv, (const Acc*)tb.VP, tb.U,
+                            tb.Q, h->wb, tb.gpart, B.part1, hc, B.sc, batch_row_map(h));
+                    });
+                });
             };
             if constexpr (K == 4 || (K == 2 && (sizeof(T) == 4 || sizeof(Acc) == 4))) {
                 if (h->pipe) go(std::true_type());

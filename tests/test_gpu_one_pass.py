@@ -191,3 +191,33 @@ def test_pieces_agree_with_ranges(torch_cuda):
         g.close()
     assert rel_inf(xs[0], xs[2]) <= 1e-10
     assert rel_inf(xs[1], xs[2]) <= 1e-10
+
+
+# k-tiles of a matrix past the last-level cache's size (nontemporal loads; small
+# systems load plain): the solutions of the single solves, to 1e-10 at equal
+# iteration counts.
+@pytest.mark.parametrize("k", [2, 4])
+@pytest.mark.parametrize("f32", [False, True], ids=["f64", "f32"])
+def test_tiles_past_the_cache(torch_cuda, f32, k):
+    torch = torch_cuda
+    from paper_2308_00778_amd import LsqrSystem
+
+    # 224 and 128 bytes a row: more than 320 MB
+    spec = synth.tiny(seed=29, n_stars=30011 if f32 else 17011, obs=(50, 150), n_dfa=9001,
+                      n_instr_cols=203, value_dtype="f32" if f32 else "f64")
+    arrays, first = synth.device_system(spec, "cuda:0")
+    m = int(first[-1])
+    say(f"tiles past the cache: m={m} k={k} f32={f32}")
+    assert m * (128 if f32 else 224) > 320 << 20
+    g = LsqrSystem(**arrays, n_stars=spec.n_stars, n_dfa=spec.n_dfa,
+                   n_instr_cols=spec.n_instr_cols)
+    g.set_option("tests", 0)
+    g.set_option("ktile", k)
+    B = torch.stack([synth.device_noise(spec, m, r, "cuda:0") for r in range(k)], 1).contiguous()
+    X, infos = g.solve_batched(B, 6, 0.0, 0.0)
+    X = X.cpu().numpy()
+    for r in range(k):
+        x, info = g.solve(B[:, r].contiguous(), 6, atol=0.0, btol=0.0)
+        assert info.itn == 6 and infos[r].itn == 6
+        assert rel_inf(X[:, r], x.cpu().numpy()) <= 1e-10
+    g.close()
