@@ -396,21 +396,28 @@ void launch_instr_tail(const lsqr_handle* h, const Acc* U, const int32_t* inv, A
 {
     const int64_t ninst = h->sv.ni > 0 ? h->sv.n_instr_cols : 0;
     const int64_t tw = std::max<int64_t>(1, kLdsInstrBudget / (8 * K));
-    // plain loads where the caller's instrumental columns are not line-aligned
-    const uintptr_t vb = (uintptr_t)h->sv.val, ib = (uintptr_t)h->sv.instr;
+    // plain loads where the instrumental columns are not line-aligned
+    const bool compact = h->sv.instr16 != nullptr && !SQUARE;
+    const uintptr_t vb = (uintptr_t)h->sv.val;
+    const uintptr_t ib = compact ? (uintptr_t)h->sv.instr16 : (uintptr_t)h->sv.instr;
     const bool lined = vb % 128 == 0 && ib % 128 == 0 &&
-                       (h->sv.m * (int64_t)sizeof(T)) % 128 == 0 && (h->sv.m * 4) % 128 == 0;
+                       (h->sv.m * (int64_t)sizeof(T)) % 128 == 0 &&
+                       (h->sv.m * (compact ? 2 : 4)) % 128 == 0;
     if (hcols >= ninst) return;
     const int64_t nw = cdiv(ninst - hcols, tw), wide = std::min(tw, ninst - hcols);
     // parts of the rows: one workgroup (a window of one part) per compute unit
     const int64_t parts = std::max<int64_t>(1, h->num_cu / (nw * kDies)) * kDies;
-    auto go = [&](auto gen, auto plain) {
+    auto go = [&](auto gen, auto plain, auto cidx) {
         hipLaunchKernelGGL((k_instr_tail<T, Acc, K, SQUARE, kAttBlock, decltype(gen)::value,
-                                         decltype(plain)::value>),
+                                         decltype(plain)::value, decltype(cidx)::value && !SQUARE>),
                            dim3(parts * nw), dim3(kAttBlock), (size_t)(wide * K * 8), st, h->sv, U,
                            inv, Q, hcols, tw, (int)nw, sc);
     };
-    by_flag(h->generic, [&](auto gen) { by_flag(!lined, [&](auto plain) { go(gen, plain); }); });
+    by_flag(h->generic, [&](auto gen) {
+        by_flag(!lined, [&](auto plain) {
+            by_flag(compact, [&](auto cidx) { go(gen, plain, cidx); });
+        });
+    });
 }
 
 // LDS of a fused pass over K right-hand sides: the FP64 histogram of the

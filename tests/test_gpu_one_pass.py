@@ -221,3 +221,29 @@ def test_tiles_past_the_cache(torch_cuda, f32, k):
         assert info.itn == 6 and infos[r].itn == 6
         assert rel_inf(X[:, r], x.cpu().numpy()) <= 1e-10
     g.close()
+
+
+# The instrumental tail with and without the compact copy of the indices: columns
+# past one histogram, against the oracle.
+@pytest.mark.parametrize("compact", [1, 0])
+@pytest.mark.parametrize("f32", [False, True], ids=["f64", "f32"])
+def test_instr_tail_indices(torch_cuda, f32, compact):
+    torch = torch_cuda
+    S = synth.make_system(synth.tiny(seed=31, n_stars=300, obs=(10, 70), n_dfa=120,
+                                     n_instr_cols=25001, value_dtype="f32" if f32 else "f64"))
+    o = oracle.OracleSystem.from_synth(S)
+    say(f"instrumental tail: m={S.m} f32={f32} compact={compact}")
+    b = np.stack([o.aprod1(synth.x_true(S.spec), synth.noise(S.spec, S.m, r)) for r in range(4)], 1)
+    g = gpu_system(S)
+    g.set_option("tests", 0)
+    g.set_option("compact_index", compact)
+    g.set_option("ktile", 4)
+    x, _ = g.solve(torch.from_numpy(b[:, 0].copy()).cuda(), 6, atol=0.0, btol=0.0)
+    X, _ = g.solve_batched(torch.from_numpy(b).cuda(), 6, 0.0, 0.0)
+    x, X = x.cpu().numpy(), X.cpu().numpy()
+    g.close()
+    for r in range(4):
+        want = o.lsqr(b[:, r].copy(), 6, atol=0.0, btol=0.0, conlim=0.0, tests=False)[0]
+        assert rel_inf(X[:, r], want) <= 1e-10
+        if r == 0:
+            assert rel_inf(x, want) <= 1e-10
