@@ -34,8 +34,8 @@ HBM_PEAK_GBPS = 8000.0  # MI355X HBM3E
 def bytes_per_row(vb: int, ub: int):
     """Algorithmic bytes per row and launch of each row pass, for values of vb
     bytes and a row vector u of ub bytes (index layout: int64 star, int64
-    attitude start, 6 int32 instrumental indices = 40 B; in bucket order an
-    int32 local attitude start):
+    attitude start, 6 int32 instrumental indices = 40 B; in bucket order 4 B
+    for the local attitude start, which the kernels read as uint16):
       aprod1: 24 values + indices + u read and written
       aprod2: 24 values + indices + u read
       fused (fused mode 1): as aprod1, A read once for both products

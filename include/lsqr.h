@@ -126,7 +126,9 @@ lsqr_status lsqr_destroy(lsqr_handle* h);
  *   LSQR_OPT_CONLIM       condition limit of stopping test 3 (default 1e8; 0 off)
  *   LSQR_OPT_TESTS        1 (default): stopping tests 1..6 on; 0: run exactly
  *                         itn_limit iterations (istop 7)
- *   LSQR_OPT_CHUNK        iterations per HIP-graph launch (default 16, >= 1)
+ *   LSQR_OPT_CHUNK        iterations between two looks at the state, one HIP
+ *                         graph (default 16, >= 1); a few, when a few are left,
+ *                         are launched one by one
  *   LSQR_OPT_GRAPH        1 (default): iterations replayed from a captured HIP
  *                         graph; 0: launched one by one
  *   LSQR_OPT_PROFILE      1: time every aprod1 / aprod2 launch of a solve with
@@ -141,9 +143,10 @@ lsqr_status lsqr_destroy(lsqr_handle* h);
  *                         (W starts per bucket), each bucket's 3 x (W + 3)
  *                         columns accumulated in an LDS histogram (no device
  *                         atomics); costs a copy of the 12 attitude coefficients
- *                         in that order and three int32 per row, built on first
- *                         use, needs n_rows < 2^31; the solver keeps its row
- *                         vector u in bucket order; 0 scatter-add with device
+ *                         in that order and 10 bytes per row, built on first
+ *                         use (not where LSQR_OPT_FUSED 2 runs one pass), needs
+ *                         n_rows < 2^31; the solver keeps its row vector u in
+ *                         bucket order; 0 scatter-add with device
  *                         atomics (no extra memory, about 10x slower)
  *   LSQR_OPT_ASTRO_SCAN   astrometric part of aprod2: 0 (default) running
  *                         per-lane partials reduced only where a star ends;
@@ -151,14 +154,18 @@ lsqr_status lsqr_destroy(lsqr_handle* h);
  *   LSQR_OPT_ATT_BUCKETS  number of attitude buckets: 0 (default) the fewest
  *                         whose FP64 histogram fits in LDS (16 for 10^5 attitude
  *                         columns per axis), n > 0 that many (raised if they do
- *                         not fit); settable only before the first solve or
- *                         aprod2
+ *                         not fit; single-RHS solves and aprod2 then use the
+ *                         bucket order whatever the size); settable only
+ *                         before the first solve or aprod2
  *   LSQR_OPT_ATT_INTERLEAVE  aprod1 reads the 12 attitude values of a row from
  *                         a copy of the attitude section interleaved by axis
  *                         (x3[3 c + axis], rebuilt before every aprod1; the
- *                         values are then consecutive): 1 (default) or 0
+ *                         values are then consecutive), or, once the bucket
+ *                         order exists, adds attitude products computed in that
+ *                         order (8 or 4 more bytes per row): 1 (default) or 0
  *                         (three 4-value windows straight from the vector)
- *   LSQR_OPT_FUSED        with LSQR_OPT_ATT_MODE 1 on the full row layout:
+ *   LSQR_OPT_FUSED        with LSQR_OPT_ATT_MODE 1 (general row layouts: 2, and
+ *                         0 otherwise):
  *                         1: each LSQR iteration reads A once for aprod1 and
  *                         the astrometric, instrumental and global part of
  *                         aprod2 (u~ = Abar v - alpha u is row-local, so every
@@ -168,7 +175,11 @@ lsqr_status lsqr_destroy(lsqr_handle* h);
  *                         aprod1 computed first by a pass over the rows in
  *                         bucket order (the bucket's attitude columns of v in
  *                         LDS, no gathers from global memory) and folded into
- *                         u~, so the fused pass skips the attitude section;
+ *                         u~, so the fused pass skips the attitude section.
+ *                         FP64 and refined solves and aprod2 of systems with
+ *                         3 n_dfa + n_instr_cols <= 19456 (the FP64 histograms
+ *                         of both sections fit in LDS) instead do everything in
+ *                         one sweep over A in row order;
  *                         3: as 2, but u~ stays in star order: the pre-pass
  *                         writes the attitude part to a separate bucket-order
  *                         vector (8 bytes per row, allocated on first use)
@@ -186,10 +197,12 @@ lsqr_status lsqr_destroy(lsqr_handle* h);
  *   LSQR_OPT_COMPACT_INDEX 1 (default): on the first solve, build int32 copies of
  *                         star_of_row and uint16 copies of instr_idx for the
  *                         fused passes (16 instead of 32 index bytes per row;
- *                         full row layout, n_instr_cols <= 65536, n_stars <
- *                         2^31) when they take at most 1/32 of the device
- *                         memory; the caller's arrays are used otherwise and
- *                         by every other pass; 0: never (frees the copies)
+ *                         n_instr_cols <= 65536, n_stars < 2^31; the uint16
+ *                         copies also for the instrumental columns past the
+ *                         fused pass's histogram) when they take at most 1/32
+ *                         of the device memory; the caller's arrays are used
+ *                         otherwise and by every other pass; 0: never (frees
+ *                         the copies)
  *   LSQR_OPT_KTILE        batched solves: right-hand sides advanced together per
  *                         pass over A (1, 2, 4, 8, 16; 16 in fused modes 2 and 3
  *                         with LSQR_OPT_RHS_LANES), 0 (default) = autotune (see
@@ -362,17 +375,16 @@ lsqr_status lsqr_batch_tuning(lsqr_handle* h, int32_t* k_tile, double* ms_per_rh
 
 /* Per-kernel timing of the last solve run with LSQR_OPT_PROFILE = 1:
  * total milliseconds and launch counts of the aprod1 and aprod2 kernels of
- * the iterations (with LSQR_OPT_FUSED: of the fused pass, which includes the
- * attitude-interleave copy, and of the attitude pass). Host pointers; any may
- * be NULL. */
+ * the iterations (with LSQR_OPT_FUSED: of the fused pass with the attitude
+ * pre-pass, and of the attitude pass). Host pointers; any may be NULL. */
 lsqr_status lsqr_kernel_times(lsqr_handle* h, double* ms_aprod1, int64_t* n_aprod1,
                               double* ms_aprod2, int64_t* n_aprod2);
 
 /* Per-pass timing of the last solve run with LSQR_OPT_PROFILE = 1 (FP64 or
- * refined, not batched): ms[0] the attitude pre-pass of fused mode 2 (with the
- * attitude-interleave copy; only that copy in other modes), ms[1] the rest of
- * the aprod1 window (the fused pass, or aprod1), ms[2] the aprod2 window (the
- * attitude pass, or aprod2); n[i] the iterations timed. Host arrays of 3.
+ * refined, not batched): ms[0] the attitude pre-pass of fused mode 2 (an
+ * empty window in other modes and in one pass), ms[1] the rest of the aprod1
+ * window (the fused pass, or aprod1), ms[2] the aprod2 window (the attitude
+ * pass, or aprod2; empty in one pass); n[i] the iterations timed. Host arrays of 3.
  * mode (may be NULL): the fused mode the last FP64 or refined solve ran
  * (0 to 3, see LSQR_OPT_FUSED); compact (may be NULL): 1 when the fused
  * passes read the compact index copies (LSQR_OPT_COMPACT_INDEX). */
