@@ -201,8 +201,9 @@ lsqr_status lsqr_destroy(lsqr_handle* h);
  *                         copies also for the instrumental columns past the
  *                         fused pass's histogram) when they take at most 1/32
  *                         of the device memory; the caller's arrays are used
- *                         otherwise and by every other pass; 0: never (frees
- *                         the copies)
+ *                         otherwise, by every other pass and by the operators
+ *                         (lsqr_aprod1, lsqr_aprod2); 0: never (frees the
+ *                         copies)
  *   LSQR_OPT_KTILE        batched solves: right-hand sides advanced together per
  *                         pass over A (1, 2, 4, 8, 16; 16 in fused modes 2 and 3
  *                         with LSQR_OPT_RHS_LANES), 0 (default) = autotune (see

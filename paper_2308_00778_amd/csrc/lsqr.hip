@@ -377,6 +377,15 @@ void by_flag(bool a, F&& f)
     else f(std::false_type());
 }
 
+// The compact index copies serve the solves, on the stream that wrote them. The
+// operators (no state, sc null) run on the caller's stream, which does not wait
+// for those writes, and may be recorded in a caller's graph that outlives the
+// copies (LSQR_OPT_COMPACT_INDEX 0 frees them): they read the caller's arrays.
+inline bool compact_on(const lsqr_handle* h, const Scalars* sc)
+{
+    return h->sv.star32 != nullptr && sc != nullptr;
+}
+
 // Blocks of a kernel whose n workgroups per part run side by side.
 inline int64_t side_grid(int64_t parts, int n) { return cdiv(parts, kDies) * kDies * n; }
 
@@ -397,7 +406,7 @@ void launch_instr_tail(const lsqr_handle* h, const Acc* U, const int32_t* inv, A
     const int64_t ninst = h->sv.ni > 0 ? h->sv.n_instr_cols : 0;
     const int64_t tw = std::max<int64_t>(1, kLdsInstrBudget / (8 * K));
     // plain loads where the instrumental columns are not line-aligned
-    const bool compact = h->sv.instr16 != nullptr && !SQUARE;
+    const bool compact = compact_on(h, sc) && !SQUARE;
     const uintptr_t vb = (uintptr_t)h->sv.val;
     const uintptr_t ib = compact ? (uintptr_t)h->sv.instr16 : (uintptr_t)h->sv.instr;
     const bool lined = vb % 128 == 0 && ib % 128 == 0 &&
@@ -634,7 +643,7 @@ void launch_one_pass(const lsqr_handle* h, const Acc* x, const Acc* x3, Acc* u, 
         else if (win == 1) go(Y(), N(), cidx, gen);
         else go(N(), N(), cidx, gen);
     };
-    by_flag(h->sv.star32 != nullptr, [&](auto cidx) {
+    by_flag(compact_on(h, gate.A), [&](auto cidx) {
         if (h->generic && h->sv.ng > 1) by_win(cidx, std::integral_constant<int, kGlobMax>());
         else if (h->generic) by_win(cidx, std::integral_constant<int, 1>());
         else by_win(cidx, std::integral_constant<int, 0>());
