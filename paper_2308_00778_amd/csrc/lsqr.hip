@@ -2175,8 +2175,9 @@ void ensure_datt(const lsqr_handle* h, V*& datt)
 // residual: once the attitude bucket order is there (an aprod2 or a solve has
 // built it) the attitude part comes from a pass over it, which gathers nothing
 // from memory: 1.5e7 rows, 1e5 starts 1.05 -> 0.84 ms. x3, datt: the handle's
-// scratch of the vector's type. Without memory for datt, and where it or x3 would
-// have to be allocated while the stream is captured, the rows gather.
+// scratch of the vector's type. Without memory for them the rows gather. So they
+// do while the stream is captured: nothing is allocated then, and a caller's
+// graph does not hold datt, which a solve short of memory frees.
 template <typename T, typename V, typename VY, int MODE>
 lsqr_status run_aprod1(lsqr_handle* h, const V* x, VY* y, const double* b, double* part,
                        const int32_t* inv, V*& x3_raw, V*& datt_raw, hipStream_t st)
@@ -2184,15 +2185,17 @@ lsqr_status run_aprod1(lsqr_handle* h, const V* x, VY* y, const double* b, doubl
     const V* x3 = nullptr;
     const V* datt = nullptr;
     const bool il = h->att_il && h->sv.natt > 0 && !h->generic;
+    const bool staged = aprod1_staged(h, (int64_t)sizeof(V));
     bool pre = il && h->att_ready && att_pass_on(h);
-    if (pre && !(x3_raw && datt_raw)) {
+    bool make = il && !x3_raw && (pre || !staged);
+    if (pre || make) {
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         const bool known = hipStreamIsCapturing(st, &cap) == hipSuccess;
         if (!known) (void)hipGetLastError();
-        pre = known && cap == hipStreamCaptureStatusNone;
+        if (!known || cap != hipStreamCaptureStatusNone) pre = make = false;
     }
-    if (il && (pre || !aprod1_staged(h, (int64_t)sizeof(V)))) {
-        if (!x3_raw) LSQR_TRY(dalloc(&x3_raw, (int64_t)kAxes * h->sv.n_dfa));
+    if (make && dalloc(&x3_raw, (int64_t)kAxes * h->sv.n_dfa) != LSQR_OK) g_last_error.clear();
+    if (il && x3_raw && (pre || !staged)) {
         launch_interleave_att<V>(h, x, x3_raw, nullptr, st);
         x3 = x3_raw;
         if (pre && !datt_raw) ensure_datt(h, datt_raw);

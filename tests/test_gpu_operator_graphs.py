@@ -98,3 +98,82 @@ def test_recorded_aprod2_outlives_the_compact_copies(torch_cuda, name):
         close2(x.cpu().numpy(), o.aprod2(yk, x0), ab.aprod2(np.abs(yk), np.abs(x0)), S.m)
     del graph, fill
     g.close()
+
+
+# A x recorded as the first call of a handle whose attitude section the rows'
+# workgroups cannot stage themselves: nothing is allocated inside the capture.
+@pytest.mark.parametrize("name", ["tail", "tail_f32"])
+def test_first_aprod1_can_be_recorded(torch_cuda, name):
+    torch = torch_cuda
+    S, o, ab = system(name)
+    say(f"recorded aprod1, first call: {name} m={S.m} n={o.n}")
+    rng = np.random.default_rng(8)
+    st = torch.cuda.Stream()
+    g = gpu_system(torch, S, st)
+    x = torch.zeros(o.n, dtype=torch.float64, device="cuda")
+    y = torch.zeros(S.m, dtype=torch.float64, device="cuda")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=st):
+        g.aprod1(x, y)
+    for k in range(3):
+        xk, y0 = rng.standard_normal(o.n), rng.standard_normal(S.m)
+        want, bound = o.aprod1(xk, y0), ab.aprod1(np.abs(xk), np.abs(y0))
+        for call in (graph.replay, lambda: g.aprod1(x, y)):
+            x.copy_(torch.from_numpy(xk))
+            y.copy_(torch.from_numpy(y0))
+            torch.cuda.synchronize()
+            call()
+            torch.cuda.synchronize()
+            assert np.all(np.abs(y.cpu().numpy() - want) <= 32 * EPS * bound + 1e-300)
+    del graph
+    g.close()
+
+
+# A x recorded before and after the bucket order and the scratch of its pre-pass
+# exist: the recorded call never uses that scratch (a solve short of memory frees
+# it), so both graphs hold the same kernels and give the same bits.
+@pytest.mark.parametrize("vec", ["f64", "f32"])
+@pytest.mark.parametrize("name,buckets", [("tail", 0), ("tail_f32", 0), ("one_pass", 3)])
+def test_recorded_aprod1_holds_no_scratch_of_the_order(torch_cuda, name, buckets, vec):
+    torch = torch_cuda
+    S, o, ab = system(name)
+    if vec == "f32" and S.values.dtype != np.float32:
+        pytest.skip("FP32 vectors need FP32 values")
+    say(f"recorded aprod1, bucket order: {name} m={S.m} n={o.n} vec={vec}")
+    dt, eps = (torch.float64, EPS) if vec == "f64" else (torch.float32, 2.0 ** -23)
+    rng = np.random.default_rng(9)
+    st = torch.cuda.Stream()
+    g = gpu_system(torch, S, st)
+    if buckets:
+        g.set_option("att_buckets", buckets)
+    ax, aty = (g.aprod1, g.aprod2) if vec == "f64" else (g.aprod1_f32, g.aprod2_f32)
+    x = torch.zeros(o.n, dtype=dt, device="cuda")
+    y = torch.zeros(S.m, dtype=dt, device="cuda")
+    ax(x, y)
+    torch.cuda.synchronize()
+    graphs = [torch.cuda.CUDAGraph() for _ in range(2)]
+    with torch.cuda.graph(graphs[0], stream=st):
+        ax(x, y)
+    aty(x, y)  # builds the bucket order
+    ax(x, y)   # allocates the scratch of the pre-pass
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graphs[1], stream=st):
+        ax(x, y)
+    for k in range(3):
+        xk = torch.from_numpy(rng.standard_normal(o.n)).to(dt)
+        y0 = torch.from_numpy(rng.standard_normal(S.m)).to(dt)
+        got = []
+        for call in (graphs[0].replay, graphs[1].replay, lambda: ax(x, y)):
+            x.copy_(xk)
+            y.copy_(y0)
+            torch.cuda.synchronize()
+            call()
+            torch.cuda.synchronize()
+            got.append(y.cpu())
+        assert torch.equal(got[0], got[1])
+        xn, yn = xk.double().numpy(), y0.double().numpy()
+        want, bound = o.aprod1(xn, yn), ab.aprod1(np.abs(xn), np.abs(yn))
+        for v in got:
+            assert np.all(np.abs(v.double().numpy() - want) <= 32 * eps * bound + 1e-30)
+    del graphs
+    g.close()
