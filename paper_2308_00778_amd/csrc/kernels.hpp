@@ -552,9 +552,12 @@ __global__ __launch_bounds__(NT) void k_aprod1(SysView s, const VX* __restrict__
     const int lane = threadIdx.x & (kWave - 1);
     const int32_t wave = uniform((int32_t)(blockIdx.x * W + threadIdx.x / kWave));
     const int64_t stride = (int64_t)gridDim.x * NT;
+    // a section in LDS has few columns: the low word of its starts is enough
+    using Start = std::conditional_t<XA == kStaged, int32_t, int64_t>;
     struct Idx {
         int64_t star;
-        int32_t t, place, ix[kInstr];
+        Start t;
+        int32_t place, ix[kInstr];
     };
     auto lane_off = [&](int64_t r0) {  // the lane's row, the last one past the end
         return (uint32_t)(lane < m - r0 ? lane : m - 1 - r0);
@@ -563,7 +566,10 @@ __global__ __launch_bounds__(NT) void k_aprod1(SysView s, const VX* __restrict__
         const int64_t base = r0 < m ? r0 : m - 1;
         const uint32_t o = r0 < m ? lane_off(r0) : 0u;
         w.star = na > 0 ? ld_off(&s.star[base], o) : 0;
-        if (att) w.t = ld_off(reinterpret_cast<const int32_t*>(&s.att[base]), 2 * o);
+        if (att) {
+            constexpr uint32_t words = sizeof(int64_t) / sizeof(Start);
+            w.t = ld_off(reinterpret_cast<const Start*>(&s.att[base]), words * o);
+        }
         if (pl) w.place = ld_off(&pl[base], o);
 #pragma unroll
         for (int j = 0; j < kInstr; ++j)
@@ -593,11 +599,10 @@ __global__ __launch_bounds__(NT) void k_aprod1(SysView s, const VX* __restrict__
     Acc xg[NG];
 #pragma unroll
     for (int g = 0; g < NG; ++g) xg[g] = g < ng ? (Acc)x[s.glob_base + g] : (Acc)0;
-    auto att_value = [&](int32_t t, int e) {
+    auto att_value = [&](Start t, int e) {
         const int ax = e / kParAxis, qq = e % kParAxis;
-        return XA == kWindows  ? x[s.att_base + ax * s.n_dfa + t + qq]
-               : XA == kStaged ? xw[kAxes * (t + qq) + ax]
-                               : xw[kAxes * (int64_t)(t + qq) + ax];
+        return XA == kWindows ? x[s.att_base + ax * s.n_dfa + t + qq]
+                              : xw[kAxes * (t + qq) + ax];
     };
 
     double ssq = 0.0;
