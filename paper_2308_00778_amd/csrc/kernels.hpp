@@ -1057,8 +1057,9 @@ __global__ __launch_bounds__(NT) void k_aprod2(SysView s, const VU* __restrict__
 //   gpart[blockIdx.x]: global-column partials, steps: the waves' rows.
 // Dynamic LDS: the FP64 histogram of instrumental columns [0, hcols) (see
 // k_att_hist; columns from hcols on are left to k_instr_tail), in kAttAll that
-// of the attitude columns ([axis][n_dfa]), then the instrumental slice of x
-// (LDSX, n_instr_cols Acc) and the interleaved attitude section (WIN).
+// of the attitude columns ([axis][n_dfa], of FP64 products as in k_att_hist), then
+// the instrumental slice of x (LDSX, n_instr_cols Acc) and the interleaved
+// attitude section (WIN).
 // AM, the attitude part of the dot product: kAttX reads three 4-value windows
 // of x, kAttX3 one 12-value window of x3, kAttPre none: k_att_dot has already
 // replaced u~ by (attitude part of A vp) - coef u~, so the row adds that;
@@ -1277,7 +1278,7 @@ __global__ __launch_bounds__(NT) void k_fused(SysView s, const Acc* __restrict__
 #pragma unroll
                             for (int qq = 0; qq < kParAxis; ++qq)
                                 atomicAdd(&ahist[ax * s.n_dfa + t + qq],
-                                          (double)((Acc)at[ax * kParAxis + qq] * d));
+                                          (double)at[ax * kParAxis + qq] * (double)d);
                     }
                 }
 #pragma unroll

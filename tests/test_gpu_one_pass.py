@@ -247,3 +247,36 @@ def test_instr_tail_indices(torch_cuda, f32, compact):
         assert rel_inf(X[:, r], want) <= 1e-10
         if r == 0:
             assert rel_inf(x, want) <= 1e-10
+
+
+# Eq. (3) in FP32: the attitude columns are sums of FP64 products in both forms,
+# rounded to FP32 once. So each is within half an ulp of the exact sum, and the
+# rounding of a sum of that many terms in FP64.
+@pytest.mark.parametrize("buckets", [0, 3])
+@pytest.mark.parametrize("name", ["small_f32", "no_slice_f32", "mixed_f32"])
+def test_f32_attitude_products_in_fp64(torch_cuda, name, buckets):
+    torch = torch_cuda
+    S, o = system(name)
+    sp = S.spec
+    say(f"FP64 products of FP32 values: {name} m={S.m} buckets={buckets}")
+    y = np.random.default_rng(17).standard_normal(S.m).astype(np.float32)
+    yl = y.astype(np.longdouble)
+    exact, mag, terms = (np.zeros(3 * sp.n_dfa, dtype=np.longdouble) for _ in range(3))
+    for ax in range(3):
+        for q in range(4):
+            p = S.values[sp.n_astro + 4 * ax + q].astype(np.longdouble) * yl  # 48 of 64 bits
+            c = ax * sp.n_dfa + q + S.att_start
+            np.add.at(exact, c, p)
+            np.add.at(mag, c, np.abs(p))
+            np.add.at(terms, c, 1)
+    g = gpu_system(S)
+    if buckets:
+        g.set_option("att_buckets", buckets)
+    x = torch.zeros(o.n, dtype=torch.float32, device="cuda")
+    g.aprod2_f32(x, torch.from_numpy(y).cuda())
+    torch.cuda.synchronize()
+    a0 = sp.n_astro * sp.n_stars
+    got = x.cpu().numpy()[a0:a0 + 3 * sp.n_dfa].astype(np.longdouble)
+    g.close()
+    bound = 2.0 ** -24 * np.abs(exact) + 2.0 * terms * EPS * mag + 1e-45
+    assert np.all(np.abs(got - exact) <= bound)
