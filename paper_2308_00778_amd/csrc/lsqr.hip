@@ -350,6 +350,29 @@ inline bool rhs_lanes_on(const lsqr_handle* h) { return h->rhs_lanes && use_fuse
 // with constraint rows, their share stored right after them.
 inline int n_part(const lsqr_handle* h, int nb) { return nb + (h->nc > 0 ? 1 : 0); }
 
+// Whether nothing can be allocated for work on stream st: it is being captured
+// (or, the legacy stream beside another's capture, cannot be asked).
+bool captured(hipStream_t st)
+{
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cap) == hipSuccess) return cap != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
+// The form of lsqr_aprod2 (one pass or not): the iterations', but while the
+// caller's stream is captured one that has all it needs, if the iterations' has
+// not (a batched solve builds only the bucket order, options may have changed
+// since the last call, and without an attitude section separate passes need
+// nothing).
+inline bool operator_one_pass(const lsqr_handle* h)
+{
+    const bool one = one_pass_on(h);
+    const bool order = h->att_ready || !att_pass_on(h), slices = h->S1 != nullptr;
+    if ((one ? slices : order) || !(one ? order : slices) || !captured(h->user_stream)) return one;
+    return !one;
+}
+
 // Placement of the single-RHS solver's row vector: bucket order in attitude
 // mode 1 (row i at u[invperm[i]]) except in fused mode 3 and in one pass.
 inline const int32_t* row_map(const lsqr_handle* h)
@@ -842,16 +865,17 @@ void launch_att_pass(lsqr_handle* h, const Acc* ub, const Scalars* sc, hipStream
 // without inv), the
 // global-column second stage and, in attitude mode 1, the attitude pass over
 // ub, the same vector in bucket order (or in star order, read through gperm).
+// one_pass: u in row order, everything in one sweep.
 template <typename T, typename Acc>
 void launch_aprod2(lsqr_handle* h, const Acc* u, const int32_t* inv, Acc* q, Acc* gpart,
                    int64_t hcols, const Scalars* sc, hipStream_t st, const Acc* ub,
-                   const int32_t* gperm)
+                   const int32_t* gperm, bool one_pass)
 {
     const size_t lds = (size_t)(hcols * 8);
     const dim3 g(h->nb2), bm(kBlock2), b(kBlock);
     const bool att = !att_pass_on(h);
     launch_con_aprod2<Acc, Acc>(h, u + h->sv.m, q, sc, st);
-    if (fused_mode(h) == kOnePass) {
+    if (one_pass) {
         launch_one_pass<T, Acc, true>(h, nullptr, nullptr, const_cast<Acc*>(u), q, gpart,
                                       Gate{nullptr, const_cast<Scalars*>(sc), nullptr, nullptr, 0},
                                       st);
@@ -933,7 +957,7 @@ void launch_iteration(lsqr_handle* h, Path<Acc>& P, hipStream_t st, hipEvent_t* 
         if (ev) (void)hipEventRecord(ev[1], st);
         if (ev) (void)hipEventRecord(ev[2], st);
         launch_aprod2<T, Acc>(h, P.u, row_map(h), P.q, P.gpart, P.hcols, h->sc, st, P.u,
-                              nullptr);
+                              nullptr, false);
         glob.ng = 0;
     }
     if (ev) (void)hipEventRecord(ev[3], st);
@@ -961,7 +985,7 @@ void launch_init(lsqr_handle* h, Path<Acc>& P, int npart, hipStream_t st)
     hipLaunchKernelGGL((k_fill<Acc>), dim3(h->nbc), dim3(kBlock), 0, st, n, P.q, (Acc)0);
     hipLaunchKernelGGL((k_fill<double>), dim3(h->nbc), dim3(kBlock), 0, st, n, h->v, 0.0);
     launch_aprod2<T, Acc>(h, P.u, row_map(h), P.q, P.gpart, P.hcols, h->sc, st, P.u,
-                          star_order_u(h) ? (const int32_t*)h->perm : nullptr);
+                          star_order_u(h) ? (const int32_t*)h->perm : nullptr, one_pass_on(h));
     GlobView glob = glob_view(h, P.gpart, 0, 1);
     glob.ng = 0;  // launch_aprod2 has added every section
     const int grid = column_grid(h, n, kNoSlices, kNoSlices);
@@ -1146,9 +1170,9 @@ lsqr_status ensure_att(lsqr_handle* h)
 
 // What the single-RHS row passes need: the attitude bucket order, or the
 // slices of the one-pass form.
-lsqr_status ensure_row_order(lsqr_handle* h)
+lsqr_status ensure_row_order(lsqr_handle* h, bool one_pass)
 {
-    if (fused_mode(h) != kOnePass) return ensure_att(h);
+    if (!one_pass) return ensure_att(h);
     if (!h->S1) {
         const int64_t ninst = h->sv.ni > 0 ? h->sv.n_instr_cols : 0;
         const int64_t natt = h->sv.natt > 0 ? kAxes * h->sv.n_dfa : 0;
@@ -1363,7 +1387,7 @@ template <typename T>
 lsqr_status solve_fp64(lsqr_handle* h, const double* b, double* x, int32_t itn_limit, double atol,
                        double btol, lsqr_info* info)
 {
-    LSQR_TRY(ensure_row_order(h));
+    LSQR_TRY(ensure_row_order(h, one_pass_on(h)));
     LSQR_TRY(ensure_compact(h));
     LSQR_TRY((prepare_path<T, double>(h, h->p64)));
     Path<double>& P = h->p64;
@@ -2188,12 +2212,7 @@ lsqr_status run_aprod1(lsqr_handle* h, const V* x, VY* y, const double* b, doubl
     const bool staged = aprod1_staged(h, (int64_t)sizeof(V));
     bool pre = il && h->att_ready && att_pass_on(h);
     bool make = il && !x3_raw && (pre || !staged);
-    if (pre || make) {
-        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-        const bool known = hipStreamIsCapturing(st, &cap) == hipSuccess;
-        if (!known) (void)hipGetLastError();
-        if (!known || cap != hipStreamCaptureStatusNone) pre = make = false;
-    }
+    if ((pre || make) && captured(st)) pre = make = false;
     if (make && dalloc(&x3_raw, (int64_t)kAxes * h->sv.n_dfa) != LSQR_OK) g_last_error.clear();
     if (il && x3_raw && (pre || !staged)) {
         launch_interleave_att<V>(h, x, x3_raw, nullptr, st);
@@ -2666,17 +2685,18 @@ lsqr_status lsqr_aprod2(lsqr_handle* h, double* x, const double* y)
 {
     LSQR_TRY(check_handle(h));
     if (!x || !y) return fail(LSQR_E_INVALID, "null vector");
-    LSQR_TRY(ensure_row_order(h));
+    const bool one_pass = operator_one_pass(h);
+    LSQR_TRY(ensure_row_order(h, one_pass));
     const int64_t hc = instr_hcols(h, 1);
     // y in row order: the attitude pass (where the bucket order exists:
     // attitude section present, mode 1) reads it through the permutation
     const int32_t* gperm = att_pass_on(h) ? (const int32_t*)h->perm : nullptr;
     if (h->value_type == LSQR_F64)
         launch_aprod2<double, double>(h, y, nullptr, x, h->gpart_raw, hc, nullptr,
-                                      h->user_stream, y, gperm);
+                                      h->user_stream, y, gperm, one_pass);
     else
         launch_aprod2<float, double>(h, y, nullptr, x, h->gpart_raw, hc, nullptr,
-                                     h->user_stream, y, gperm);
+                                     h->user_stream, y, gperm, one_pass);
     HIP_TRY(hipGetLastError());
     return LSQR_OK;
 }
@@ -2697,13 +2717,14 @@ lsqr_status lsqr_aprod2_f32(lsqr_handle* h, float* x, const float* y)
     if (!x || !y) return fail(LSQR_E_INVALID, "null vector");
     if (h->value_type != LSQR_F32)
         return fail(LSQR_E_STATE, "lsqr_aprod2_f32 needs an LSQR_F32 system");
-    LSQR_TRY(ensure_row_order(h));
+    const bool one_pass = operator_one_pass(h);
+    LSQR_TRY(ensure_row_order(h, one_pass));
     if (!h->gpart_raw32)
         LSQR_TRY(dalloc(&h->gpart_raw32, std::max<int64_t>(h->nb2, (int64_t)h->nba * kGlobMax)));
     const int64_t hc = instr_hcols(h, 1);
     const int32_t* gperm = att_pass_on(h) ? (const int32_t*)h->perm : nullptr;
     launch_aprod2<float, float>(h, y, nullptr, x, h->gpart_raw32, hc, nullptr, h->user_stream, y,
-                                gperm);
+                                gperm, one_pass);
     HIP_TRY(hipGetLastError());
     return LSQR_OK;
 }
@@ -2764,7 +2785,7 @@ lsqr_status lsqr_solve_refined(lsqr_handle* h, const double* b, double* x, int32
     if (!(atol >= 0.0) || !(btol >= 0.0)) return fail(LSQR_E_INVALID, "atol, btol must be >= 0");
     HIP_TRY(hipStreamSynchronize(h->user_stream));
     h->var_valid = 0;
-    LSQR_TRY(ensure_row_order(h));
+    LSQR_TRY(ensure_row_order(h, one_pass_on(h)));
     LSQR_TRY(ensure_compact(h));
     LSQR_TRY((prepare_path<float, float>(h, h->p32)));
     Path<float>& P = h->p32;

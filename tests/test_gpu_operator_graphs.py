@@ -177,3 +177,68 @@ def test_recorded_aprod1_holds_no_scratch_of_the_order(torch_cuda, name, buckets
             assert np.all(np.abs(v.double().numpy() - want) <= 32 * eps * bound + 1e-30)
     del graphs
     g.close()
+
+
+# The first A^T y of a handle, recorded: the call needs no more than what an
+# earlier call of another kind has left (or nothing, without attitude), whichever
+# form the options and the system's size ask for.
+@pytest.mark.parametrize("before", ["batched", "fused1", "fused2"])
+def test_first_aprod2_recorded_after_other_calls(torch_cuda, before):
+    torch = torch_cuda
+    S, o, ab = system("one_pass")
+    say(f"recorded aprod2, first call after {before}: m={S.m} n={o.n}")
+    rng = np.random.default_rng(10)
+    st = torch.cuda.Stream()
+    g = gpu_system(torch, S, st)
+    b = torch.from_numpy(rng.standard_normal((S.m, 2))).cuda()
+    if before == "batched":  # the bucket order only, and the recorded call asks for one pass
+        g.set_option("ktile", 2)
+        g.solve_batched(b, 2, 0.0, 0.0)
+    else:
+        g.set_option("fused", int(before[-1]))
+        g.solve(b[:, 0].contiguous(), 2, atol=0.0, btol=0.0)
+        g.set_option("fused", 3 - int(before[-1]))
+    _record_aprod2(torch, g, st, S.m, o, ab, rng)
+
+
+def test_first_aprod2_recorded_without_attitude(torch_cuda):
+    torch = torch_cuda
+    from paper_2308_00778_amd import LsqrSystem
+
+    spec = synth.tiny(seed=131, n_stars=300, obs=(10, 70), n_axes=0, n_glob=2)
+    S = synth.make_system(spec)
+    o = oracle.OracleSystem.from_synth(S)
+    ab = oracle.OracleSystem(np.abs(S.values), S.star_of_row, S.att_start, S.instr_idx,
+                             n_stars=spec.n_stars, n_dfa=spec.n_dfa,
+                             n_instr_cols=spec.n_instr_cols, n_axes=0, n_glob=2)
+    say(f"recorded aprod2, first call, no attitude section: m={S.m} n={o.n}")
+    st = torch.cuda.Stream()
+    t = dict(values=torch.from_numpy(S.values).cuda(),
+             star_of_row=torch.from_numpy(S.star_of_row).cuda(),
+             att_start=torch.from_numpy(S.att_start).cuda(),
+             instr_idx=torch.from_numpy(S.instr_idx).cuda())
+    torch.cuda.synchronize()
+    g = LsqrSystem(**t, n_stars=spec.n_stars, n_dfa=spec.n_dfa, n_instr_cols=spec.n_instr_cols,
+                   n_axes=0, n_glob=2, stream=st)
+    _record_aprod2(torch, g, st, S.m, o, ab, np.random.default_rng(11))
+
+
+def _record_aprod2(torch, g, st, m, o, ab, rng):
+    x = torch.zeros(o.n, dtype=torch.float64, device="cuda")
+    y = torch.zeros(m, dtype=torch.float64, device="cuda")
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=st):
+        g.aprod2(x, y)
+    for k in range(3):
+        yk, x0 = rng.standard_normal(m), rng.standard_normal(o.n)
+        want, bound = o.aprod2(yk, x0), ab.aprod2(np.abs(yk), np.abs(x0))
+        for call in (graph.replay, lambda: g.aprod2(x, y)):
+            y.copy_(torch.from_numpy(yk))
+            x.copy_(torch.from_numpy(x0))
+            torch.cuda.synchronize()
+            call()
+            torch.cuda.synchronize()
+            close2(x.cpu().numpy(), want, bound, m)
+    del graph
+    g.close()
