@@ -179,7 +179,8 @@ lsqr_status lsqr_destroy(lsqr_handle* h);
  *                         FP64 and refined solves and aprod2 of systems with
  *                         3 n_dfa + n_instr_cols <= 19456 (the FP64 histograms
  *                         of both sections fit in LDS) instead do everything in
- *                         one sweep over A in row order;
+ *                         one sweep over A in row order (unless
+ *                         LSQR_OPT_ATT_BUCKETS or LSQR_OPT_ASTRO_SCAN is set);
  *                         3: as 2, but u~ stays in star order: the pre-pass
  *                         writes the attitude part to a separate bucket-order
  *                         vector (8 bytes per row, allocated on first use)

@@ -315,11 +315,13 @@ inline size_t one_pass_lds(const lsqr_handle* h, int64_t vbytes, int* win)
 
 // Single-RHS row passes in one sweep over A: where the histograms of the
 // attitude and instrumental columns fit in LDS together, unless options ask
-// for another form (a bucket count asks for the bucket order).
+// for another form (a bucket count asks for the bucket order, the segmented scan
+// for k_aprod2, which general layouts do not run).
 inline bool one_pass_on(const lsqr_handle* h)
 {
     int win = 0;
     return h->fused == 2 && h->att_mode == 1 && h->att_buckets == 0 &&
+           (h->astro_scan == 0 || h->generic) &&
            h->sv.m < ((int64_t)1 << 31) && h->sv.n_dfa < ((int64_t)1 << 31) &&
            one_pass_lds(h, 8, &win) > 0;
 }

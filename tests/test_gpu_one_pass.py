@@ -280,3 +280,28 @@ def test_f32_attitude_products_in_fp64(torch_cuda, name, buckets):
     g.close()
     bound = 2.0 ** -24 * np.abs(exact) + 2.0 * terms * EPS * mag + 1e-45
     assert np.all(np.abs(got - exact) <= bound)
+
+
+# LSQR_OPT_ASTRO_SCAN at one-pass sizes: the scan runs (one writer per column, a
+# fixed order), so the astrometric columns have the bits they have beside a
+# bucket count, which rules the one pass out.
+def test_astro_scan_is_honoured(torch_cuda):
+    torch = torch_cuda
+    S, o = system("small")
+    sp = S.spec
+    say(f"segmented scan at one-pass sizes: m={S.m}")
+    y = np.random.default_rng(19).standard_normal(S.m)
+    got = []
+    for buckets in (0, 1):
+        g = gpu_system(S)
+        g.set_option("astro_scan", 1)
+        if buckets:
+            g.set_option("att_buckets", buckets)
+        x = torch.zeros(o.n, dtype=torch.float64, device="cuda")
+        g.aprod2(x, torch.from_numpy(y).cuda())
+        torch.cuda.synchronize()
+        got.append(x.cpu().numpy()[:sp.n_astro * sp.n_stars])
+        g.close()
+    assert np.array_equal(got[0], got[1])
+    want = o.aprod2(y, np.zeros(o.n))[:sp.n_astro * sp.n_stars]
+    assert rel_inf(got[0], want) <= 1e-12
