@@ -210,6 +210,7 @@ struct lsqr_handle {
     float* x3_raw32 = nullptr;    // the same for lsqr_aprod1_f32
     double* datt_raw = nullptr;   // [m] attitude parts of the operators' rows, bucket order
     float* datt_raw32 = nullptr;
+    bool datt_tried[2] = {};      // asked for (FP64, FP32) since the last release
     float* gpart_raw32 = nullptr; // global-column partials of lsqr_aprod2_f32
     bool att_ready = false;
     bool att_locked = false;      // a solve or aprod2 has run: the bucket options are settled
@@ -1008,6 +1009,20 @@ void release_datt(lsqr_handle* h)
 {
     dfree(h->datt_raw);
     dfree(h->datt_raw32);
+    h->datt_tried[0] = h->datt_tried[1] = false;
+}
+
+// dalloc of what a solve (or A^T y) needs: where memory is short, once more
+// without the scratch that an earlier A x keeps.
+template <typename V>
+lsqr_status dalloc_solver(lsqr_handle* h, V** p, int64_t count)
+{
+    const lsqr_status rc = dalloc(p, count);
+    if (rc != LSQR_E_NOMEM || (!h->datt_raw && !h->datt_raw32)) return rc;
+    HIP_TRY(hipStreamSynchronize(h->user_stream));  // an A x that uses it
+    release_datt(h);
+    g_last_error.clear();
+    return dalloc(p, count);
 }
 
 template <typename Acc>
@@ -1052,11 +1067,13 @@ lsqr_status prepare_path(lsqr_handle* h, Path<Acc>& P)
         P.ready = true;
     }
     if (star_order_u(h) && !P.datt) {  // fused mode 3: the pre-pass output
-        if (dalloc(&P.datt, h->sv.m) == LSQR_E_NOMEM) {
+        lsqr_status rc = dalloc_solver(h, &P.datt, h->sv.m);
+        if (rc == LSQR_E_NOMEM) {
             batch_free(h);
             g_last_error.clear();
-            LSQR_TRY(dalloc(&P.datt, h->sv.m));
+            rc = dalloc(&P.datt, h->sv.m);
         }
+        LSQR_TRY(rc);
     }
     // a fused pass that places u~ through the permutation and leaves
     // instrumental tail windows: a star-order copy of u~ for the tails (an
@@ -1064,7 +1081,7 @@ lsqr_status prepare_path(lsqr_handle* h, Path<Acc>& P)
     if (!P.ustar && !P.ustar_tried && fused_mode(h) > 0 && row_map(h) && h->sv.ni > 0 &&
         P.f_hcols < h->sv.n_instr_cols) {
         P.ustar_tried = true;
-        if (dalloc(&P.ustar, h->sv.m) != LSQR_OK) g_last_error.clear();
+        if (dalloc_solver(h, &P.ustar, h->sv.m) != LSQR_OK) g_last_error.clear();
     }
     return LSQR_OK;
 }
@@ -1178,7 +1195,7 @@ lsqr_status ensure_row_order(lsqr_handle* h, bool one_pass)
     if (!h->S1) {
         const int64_t ninst = h->sv.ni > 0 ? h->sv.n_instr_cols : 0;
         const int64_t natt = h->sv.natt > 0 ? kAxes * h->sv.n_dfa : 0;
-        LSQR_TRY(dalloc(&h->S1, (natt + ninst) * h->nb2));
+        LSQR_TRY(dalloc_solver(h, &h->S1, (natt + ninst) * h->nb2));
     }
     if (att_pass_on(h)) h->att_locked = true;
     return LSQR_OK;
@@ -1401,7 +1418,7 @@ lsqr_status solve_fp64(lsqr_handle* h, const double* b, double* x, int32_t itn_l
     LSQR_TRY(upload_controls(h, itn_limit, atol, btol));
     h->var_valid = 0;
     if (h->var_on) {
-        if (!h->var) LSQR_TRY(dalloc(&h->var, n));
+        if (!h->var) LSQR_TRY(dalloc_solver(h, &h->var, n));
         hipLaunchKernelGGL((k_fill<double>), dim3(h->nbc), dim3(kBlock), 0, h->stream, n, h->var,
                            0.0);
     }
@@ -1479,7 +1496,7 @@ lsqr_status batch_alloc_once(lsqr_handle* h, int kmax, bool want64, bool want32)
             int64_t hc1 = 0;
             int ldsx = 0;
             fused_lds_plan(h, 1, vbytes, &hc1, &ldsx);
-            if (hc1 >= h->sv.n_instr_cols || dalloc(buf, m) == LSQR_OK) return;
+            if (hc1 >= h->sv.n_instr_cols || dalloc_solver(h, buf, m) == LSQR_OK) return;
             release_path(h->p64);
             release_path(h->p32);
             if (dalloc(buf, m) != LSQR_OK) g_last_error.clear();
@@ -2187,12 +2204,19 @@ lsqr_status solve_batched(lsqr_handle* h, bool refined, const double* Bm, double
 }
 
 // Scratch for the operators' attitude parts, where it takes at most a quarter
-// of the free memory; without it their rows gather.
+// of the free memory; without it their rows gather. Asked for once, and again
+// after a solve short of memory has released it.
 template <typename V>
-void ensure_datt(const lsqr_handle* h, V*& datt)
+void ensure_datt(lsqr_handle* h, V*& datt)
 {
+    bool& tried = h->datt_tried[sizeof(V) == 4];
+    if (tried) return;
+    tried = true;
     size_t free_b = 0, total_b = 0;
-    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) return;
+    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) {
+        (void)hipGetLastError();
+        return;
+    }
     if ((size_t)h->sv.m * sizeof(V) > free_b / 4) return;
     if (dalloc(&datt, h->sv.m) != LSQR_OK) g_last_error.clear();
 }
