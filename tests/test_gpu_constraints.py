@@ -240,3 +240,34 @@ def test_constraints_batched_unsupported_and_bad_rows(torch_cuda):
         with pytest.raises(LsqrError) as ei:
             gpu_system(S, bad)
         assert ei.value.status == LSQR_E_INVALID
+
+
+# The constraint rows' share of ||u||^2 is summed by the column kernel up to 1,024
+# rows and by a kernel of its own beyond: both sides of that line, in one pass and
+# in bucket order.
+@pytest.mark.parametrize("graph", [1, 0])
+@pytest.mark.parametrize("buckets", [0, 3])
+@pytest.mark.parametrize("n_con", [1024, 1025, 1700])
+def test_many_constraint_rows(torch_cuda, n_con, buckets, graph):
+    torch = torch_cuda
+    sp = synth.tiny(seed=75, n_stars=300, obs=(20, 60), n_dfa=150, n_instr_cols=31)
+    C = synth.constraints(sp, n_con, nnz=(1, 60), seed=5, row_norm=RN)
+    S = synth.make_system(sp)
+    o = oracle.OracleSystem.from_synth(S, con=C)
+    itn = 20
+    b = _b(S, o)
+    x_ref, i_ref = o.lsqr(b, itn, atol=0.0, btol=0.0, conlim=0.0, tests=False)
+    say(f"many constraint rows: n_con={n_con} buckets={buckets} graph={graph}")
+    g = gpu_system(S, C)
+    g.set_option("att_buckets", buckets)
+    g.set_option("graph", graph)
+    g.set_option("tests", 0)
+    g.set_option("chunk", 7)
+    x, info = g.solve(torch.from_numpy(b).cuda(), itn, atol=0.0, btol=0.0)
+    xg = x.cpu().numpy()
+    g.close()
+    assert info.itn == i_ref.itn == itn
+    assert rel_inf(xg, x_ref) <= 1e-10
+    for k in ("rnorm", "xnorm", "bnorm"):
+        a, r = getattr(info, k), getattr(i_ref, k)
+        assert abs(a - r) <= 1e-8 * abs(r), (k, a, r)
