@@ -35,7 +35,8 @@ def bytes_per_row(vb: int, ub: int):
     """Algorithmic bytes per row and launch of each row pass, for values of vb
     bytes and a row vector u of ub bytes (index layout: int64 star, int64
     attitude start, 6 int32 instrumental indices = 40 B; in bucket order 4 B
-    for the local attitude start, which the kernels read as uint16):
+    for the local attitude start, which the kernels read as uint16: the figures
+    of their own bytes are reported beside, LOCAL_START_SAVING):
       aprod1: 24 values + indices + u read and written
       aprod2: 24 values + indices + u read
       fused (fused mode 1): as aprod1, A read once for both products
@@ -43,9 +44,10 @@ def bytes_per_row(vb: int, ub: int):
         written, in bucket order
       fused_rest (mode 2): the 12 other values + star and instrumental
         indices + u read and written
-      attitude: 12 attitude values + local start + u read, in bucket order"""
+      attitude: 12 attitude values + local start + u read, in bucket order
+      one_pass: as fused, every section in the one sweep"""
     return {"aprod1": 24 * vb + 40 + 2 * ub, "aprod2": 24 * vb + 40 + ub,
-            "fused": 24 * vb + 40 + 2 * ub, "attitude_dot": 12 * vb + 4 + 2 * ub,
+            "fused": 24 * vb + 40 + 2 * ub, "one_pass": 24 * vb + 40 + 2 * ub, "attitude_dot": 12 * vb + 4 + 2 * ub,
             "fused_rest": 12 * vb + 32 + 2 * ub, "attitude": 12 * vb + 4 + ub}
 
 
@@ -55,19 +57,29 @@ BYTES_PER_ROW = bytes_per_row(8, 8)      # FP64 values and vectors
 # per row than the configured layout; the canonical figures keep the
 # configured bytes.
 COMPACT_SAVING = 16
+LOCAL_START_SAVING = 2  # bucket-order passes: the uint16 start as it is read
 BYTES_PER_ROW_F32 = bytes_per_row(4, 4)  # the FP32 inner solve of the refinement
 
 
-def pass_times(g, mode=None):
+def one_pass(spec):
+    """Whether the library's default options solve this system in one sweep per
+    iteration: the FP64 histograms of the attitude and instrumental columns fit
+    in LDS together (LSQR_OPT_FUSED)."""
+    return 3 * spec.n_dfa + spec.n_instr_cols <= 19456
+
+
+def pass_times(g, mode=None, one=False):
     """Per-iteration milliseconds of the row passes of the last profiled solve
-    (fused mode 2: attitude pre-pass, rest of the fused pass, attitude pass;
-    1: fused pass, attitude pass; 0: aprod1, aprod2); mode None: the mode the
-    solve ran."""
+    (fused mode 2: attitude pre-pass, rest of the fused pass, attitude pass,
+    or with `one` the one sweep, whose other two windows are empty; 1: fused
+    pass, attitude pass; 0: aprod1, aprod2); mode None: the mode the solve ran."""
     pt = g.pass_times()
     mode = pt.pop("mode") if mode is None else mode
     pt.pop("mode", None)
     pt.pop("compact", None)
     per = {k: ms / max(1, n) for k, (ms, n) in pt.items()}
+    if mode == 2 and one:
+        return {"one_pass": per["fused"]}
     if mode in (2, 3):
         return {"attitude_dot": per["pre"], "fused_rest": per["fused"],
                 "attitude": per["attitude"]}
@@ -353,7 +365,7 @@ def attitude_ab(dev, cfg: int = 1, itn: int = 20):
         g.set_option("profile", 1)
         g.solve(b, 2, atol=0.0, btol=0.0)
         x, info = g.solve(b, itn, atol=0.0, btol=0.0)
-        ms = pass_times(g, fused if att == 1 else 0)
+        ms = pass_times(g, fused if att == 1 else 0, one_pass(spec))
         key = ("", "fused_", "fused_att_dot_")[fused] + ("atomics", "bucket_pass")[att] + \
             ("_scan" if scan else "_flush") + ("" if il else "_plain_att_gathers")
         out[key] = {**{f"{k}_ms": v for k, v in ms.items()},
@@ -626,7 +638,7 @@ def main():
     kt = g.kernel_times()
     assert info.itn == args.steps and kt["aprod1_n"] == args.steps == kt["aprod2_n"]
     compact = g.pass_times()["compact"]
-    ms = pass_times(g)
+    ms = pass_times(g, one=one_pass(spec))
     gbps = {k: BYTES_PER_ROW[k] * m / (ms[k] * 1e-3) / 1e9 for k in ms}
     dom = max(ms, key=ms.get)
     # counter-measured HBM bytes per launch (committed profile of this workload)
@@ -699,7 +711,11 @@ def main():
                         **({"compact_index_bytes_per_row": BYTES_PER_ROW[k] - COMPACT_SAVING,
                             "compact_index_GBps": (BYTES_PER_ROW[k] - COMPACT_SAVING) * m
                             / (ms[k] * 1e-3) / 1e9}
-                           if compact and k in ("fused", "fused_rest") else {})}
+                           if compact and k in ("fused", "fused_rest", "one_pass") else {}),
+                        **({"local_start_bytes_per_row": BYTES_PER_ROW[k] - LOCAL_START_SAVING,
+                            "local_start_GBps": (BYTES_PER_ROW[k] - LOCAL_START_SAVING) * m
+                            / (ms[k] * 1e-3) / 1e9}
+                           if k in ("attitude_dot", "attitude") else {})}
                     for k in ms},
         "graph_iter_per_s": args.steps / wall_graph,
         # value counts the solve's start and end in its timed region; without them:

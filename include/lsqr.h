@@ -388,7 +388,8 @@ lsqr_status lsqr_kernel_times(lsqr_handle* h, double* ms_aprod1, int64_t* n_apro
  * window (the fused pass, or aprod1), ms[2] the aprod2 window (the attitude
  * pass, or aprod2; empty in one pass); n[i] the iterations timed. Host arrays of 3.
  * mode (may be NULL): the fused mode the last FP64 or refined solve ran
- * (0 to 3, see LSQR_OPT_FUSED); compact (may be NULL): 1 when the fused
+ * (0 to 3, see LSQR_OPT_FUSED; 2 also where it was one sweep for everything:
+ * all of it is in ms[1] then); compact (may be NULL): 1 when the fused
  * passes read the compact index copies (LSQR_OPT_COMPACT_INDEX). */
 lsqr_status lsqr_pass_times(lsqr_handle* h, double* ms, int64_t* n, int32_t* mode,
                             int32_t* compact);

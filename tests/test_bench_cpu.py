@@ -42,3 +42,25 @@ def test_bench_refuses_more_than_one_gpu():
                        capture_output=True, text=True, timeout=120)
     assert r.returncode == 2
     assert "one GPU" in r.stderr
+
+
+class _Profiled:
+    """pass_times() of a solve of 4 iterations, as the handle reports it."""
+
+    def pass_times(self):
+        return {"pre": (0.004, 4), "fused": (0.4, 4), "attitude": (0.004, 4), "mode": 2,
+                "compact": 1}
+
+
+def test_one_pass_solves_are_one_kernel():
+    # 3 n_dfa + n_instr_cols up to 19,456 columns: one sweep, no bucket-order
+    # passes to divide bytes by
+    import synth
+
+    assert [bench.one_pass(synth.WORKLOADS[k]) for k in (0, 1, 3)] == [True, False, False]
+    assert bench.one_pass(synth.tiny(n_dfa=6000, n_instr_cols=1456))
+    assert not bench.one_pass(synth.tiny(n_dfa=6000, n_instr_cols=1457))
+    assert bench.pass_times(_Profiled(), one=True) == {"one_pass": 0.1}
+    assert set(bench.pass_times(_Profiled())) == {"attitude_dot", "fused_rest", "attitude"}
+    b = bench.bytes_per_row(8, 8)
+    assert b["one_pass"] == 192 + 40 + 16
