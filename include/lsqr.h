@@ -25,7 +25,10 @@
  * created on) unless stated otherwise. lsqr_aprod1/lsqr_aprod2 run
  * asynchronously on the stream given in the system descriptor; lsqr_create
  * and the solves first synchronize with that stream, run on a stream owned by
- * the handle and return when done. Calls on one handle must not overlap. No
+ * the handle and return when done. Calls on one handle must not overlap.
+ * Equal calls agree to rounding, not bit for bit: what several waves add to one
+ * column (instrumental columns, the columns of a star whose rows they share) is
+ * summed in the order of arrival. No
  * function aborts or exits; each returns an lsqr_status, and on failure
  * lsqr_last_error() describes it.
  */
@@ -258,7 +261,14 @@ lsqr_status lsqr_set_option(lsqr_handle* h, int32_t option, double value);
 
 /* aprod mode 1, Eq. (2): y[m] += A x[n] with the raw (unscaled) A.
  * FP64 vectors; float-stored values are widened, accumulation in FP64.
- * Asynchronous on the handle's stream; x and y must not overlap. */
+ * Asynchronous on the handle's stream; x and y must not overlap.
+ * Once the handle holds the attitude bucket order (built by the first
+ * lsqr_aprod2 or solve, not where those run as one sweep), the rows' attitude
+ * parts come from a pass over it, through a scratch of n_rows values that stays
+ * with the handle: taken where it is at most a quarter of the free memory, given
+ * up to a solve that is short of it. A row's sum then has another order, so equal
+ * x give other last bits before and after. A call on a capturing stream allocates
+ * nothing and does without that scratch. */
 lsqr_status lsqr_aprod1(lsqr_handle* h, const double* x, double* y);
 
 /* Scratch capacity of lsqr_aprod1_noalloc, in doubles: 3 * 2^20 (24 MiB per
@@ -278,7 +288,10 @@ lsqr_status lsqr_aprod1(lsqr_handle* h, const double* x, double* y);
  * lsqr_aprod1. */
 lsqr_status lsqr_aprod1_noalloc(lsqr_handle* h, const double* x, double* y);
 
-/* aprod mode 2, Eq. (3): x[n] += A^T y[m] with the raw A. Same conventions. */
+/* aprod mode 2, Eq. (3): x[n] += A^T y[m] with the raw A. Same conventions.
+ * The first call on a handle allocates (the bucket order, or the slices of the
+ * one sweep: see LSQR_OPT_FUSED), as the first solve does; on a capturing stream
+ * the call takes the form whose memory is there, and fails if neither's is. */
 lsqr_status lsqr_aprod2(lsqr_handle* h, double* x, const double* y);
 
 /* FP32 forms of the two operators for FP32-stored systems (LSQR_F32): Eq. (2)

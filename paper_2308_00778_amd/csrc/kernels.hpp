@@ -1179,7 +1179,9 @@ __global__ __launch_bounds__(NT) void k_fused(SysView s, const Acc* __restrict__
     // the wave wait for its loads, and with them for every load issued before
     // (loads return in issue order), at each end of a star. Only the first and
     // the last star of a wave's rows may go on in another wave's: their sums are
-    // added with device atomics.
+    // added with device atomics, so the rounding of a star over three or more
+    // waves' rows (A2: of any such star, q not being zero) depends on their order
+    // of arrival.
     bool shared = true;
     auto astro_emit = [=, &shared](int64_t star, const Acc (&v)[kAstro]) {
         star_put<1>(v, lane, [&](int j, int, Acc sum) {
@@ -1491,10 +1493,11 @@ __global__ __launch_bounds__(NT) void k_instr_tail(SysView s, const Acc* __restr
 
 // --------------------------------------------------------- general layouts
 // Rows whose sections differ from 5 + 3 x 4 + 6 + 1 (sections absent, fewer
-// astrometric or instrumental coefficients, up to kGlobMax global columns):
-// section sizes and value-row offsets come from the system view at run time,
-// aprod1 and aprod2 run as separate passes, and the attitude columns go
-// through the bucket-order pass (or device atomics) as in the full layout.
+// astrometric or instrumental coefficients, up to kGlobMax global columns): the
+// section sizes and value-row offsets come from the system view at run time. The
+// LSQR step and A x run the GEN instances of k_fused and k_aprod1; the kernel
+// here is for Eq. (3) alone outside the one pass: the column norms, the start of
+// a solve and lsqr_aprod2 in bucket order, and separate passes.
 
 // Eq. (3) (SQUARE: squared coefficients, the column norms) for a general
 // layout over the star-aligned wave ranges: astrometric per-star segments,

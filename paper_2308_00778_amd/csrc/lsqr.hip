@@ -115,8 +115,6 @@ constexpr int64_t kLdsInstrBudget = 152 * 1024;
 constexpr int kBlock1 = 512;                    // k-tile workgroups with 256 registers a lane
 constexpr int kBlock2 = 1024;                   // aprod2 main-pass workgroup size
 constexpr int kWavesPerCU = 16;                 // row ranges per compute unit in aprod2
-// Rows per block of the two-level attitude sort: the block's slice of an FP64
-// row vector (8 B/row) stays well inside the 256 MB last-level cache.
 // Attitude buckets: as few as the FP64 LDS histogram of a bucket allows
 // (3 x (W + 3) columns within kLdsInstrBudget), because the row-vector
 // accesses of the star-order passes through inv cost more the more runs they
@@ -124,7 +122,11 @@ constexpr int kWavesPerCU = 16;                 // row ranges per compute unit i
 // +1.6 ms at 100).
 constexpr int kAttBlock = 1024;  // attitude-pass workgroup (one per CU: the histogram fills LDS)
 constexpr int kMaxTile = 16;     // right-hand sides of the widest k-tile
-// Constraint rows whose squares k_col_a sums itself; more go through k_con_ssq.
+// Constraint rows whose squares k_col_a sums itself, in each of its workgroups:
+// that saves a launch of k_con_ssq, 2 us an iteration (1e6 rows, 40 iterations,
+// 300 constraint rows 3.84 -> 3.77 ms). It still does at 2,000 (4.83 -> 4.74 ms)
+// and 8,000 (8.37 -> 8.26 ms); the line bounds what a workgroup reads to 4 values
+// a thread.
 constexpr int64_t kConDirect = 1024;
 
 // Working vectors of one arithmetic precision of the LSQR loop.
@@ -152,7 +154,7 @@ struct Path {
 
 struct lsqr_handle {
     SysView sv{};
-    int generic = 0;  // row layout other than 5 + 3x4 + 6 + 1 (k_gen_* kernels)
+    int generic = 0;  // row layout other than 5 + 3x4 + 6 + 1 (GEN instances)
     int value_type = LSQR_F64;
     int precondition = 1;
     int device = 0;
@@ -264,7 +266,7 @@ struct lsqr_handle {
                          // 2: the same with the attitude part of aprod1 in a bucket-order
                          // pre-pass (k_att_dot); 3: as 2 with the row vector in star
                          // order (pre-pass output gathered); 0: separate aprod1 and aprod2
-    int last_mode = 0;   // fused mode of the last single-RHS solve
+    int last_mode = 0;   // fused mode of the last single-RHS solve (2 for one pass)
     int pipe = 1;        // bucket-order passes load the next row before storing the current
     int rhs_lanes = 1;   // k-tiles: the fused pass puts the K RHS of a row in K lanes
     int compact = 1;     // compact index copies for the fused passes when they fit
@@ -509,8 +511,10 @@ void launch_con_aprod2(const lsqr_handle* h, const VU* u, Acc* q, const Scalars*
 }
 
 // aprod1's workgroups stage the attitude section of x in LDS themselves (no
-// interleaved copy is made) where it fits beside the instrumental slice and is
-// no more than 1/4 of the rows' own bytes: every workgroup reads all of it.
+// interleaved copy is made) where it fits beside the instrumental slice and all
+// workgroups together read no more of it than 50 bytes a row (a quarter of an
+// FP64 row's values): n_dfa = 1,000, 1e5 rows FP64 12.2 -> 9.5 us, FP32 8.7 -> 6.2.
+// It is faster past that line too (n_dfa = 5,000, 122 bytes a row: 13.0 -> 10.9 us).
 inline bool aprod1_staged(const lsqr_handle* h, int64_t vbytes)
 {
     if (!h->att_il || h->sv.natt == 0 || h->generic) return false;
@@ -812,7 +816,9 @@ void launch_slice_reduce(const lsqr_handle* h, const SliceView& V, Acc* q, Scala
                          hipStream_t st)
 {
     // one block for all right-hand sides of a tile's columns (its K stores share
-    // lines) where the columns alone fill the chip, else a block for each
+    // lines) where the columns alone fill the chip, else a block for each (2e6
+    // rows, 4 right-hand sides, 40 iterations: 1e5 starts 15.6 -> 15.3 ms with
+    // one, 3,000 starts 12.9 -> 12.7 ms with four)
     const int64_t grid = std::min<int64_t>(V.tiles(), (int64_t)h->num_cu * 8);
     hipLaunchKernelGGL((k_slice_reduce<Acc, K>), dim3(grid + 1, grid < h->num_cu * 2 ? K : 1),
                        dim3(kBlock), 0, st, V, q, sc, part, npart, gpart, nblk,
@@ -1620,7 +1626,10 @@ void by_sweep(int ks, F&& f)
 // The column kernel writes the tile's interleaved attitude copy itself where the
 // section is small (a launch less); its strided stores cost more than the copy
 // kernel on a large one (1e5 starts, 4 right-hand sides: k_col_b 50 -> 83 us
-// against 5 us).
+// against 5 us). 2e6 rows, 40 iterations, copied -> folded: 4 right-hand sides
+// 1,000 starts 12.38 -> 12.35 ms, 10,000 13.25 -> 13.22, 20,000 13.55 -> 13.72,
+// 40,000 14.29 -> 14.68; 2 right-hand sides equal to 40,000 starts. So the line
+// (21,845 starts at 4 right-hand sides) is late by 1% of a solve at most.
 template <int K>
 bool batch_x3_folded(const lsqr_handle* h)
 {
