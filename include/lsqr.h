@@ -263,8 +263,8 @@ lsqr_status lsqr_set_option(lsqr_handle* h, int32_t option, double value);
  * FP64 vectors; float-stored values are widened, accumulation in FP64.
  * Asynchronous on the handle's stream; x and y must not overlap.
  * Once the handle holds the attitude bucket order (built by the first
- * lsqr_aprod2 or solve, not where those run as one sweep), the rows' attitude
- * parts come from a pass over it, through a scratch of n_rows values that stays
+ * lsqr_aprod2 or solve, not where those run as one sweep), the attitude parts of
+ * 2^19 rows or more come from a pass over it, through a scratch of n_rows values that stays
  * with the handle: taken where it is at most a quarter of the free memory, given
  * up to a solve that is short of it. A row's sum then has another order, so equal
  * x give other last bits before and after. A call on a capturing stream allocates

@@ -2230,10 +2230,23 @@ void ensure_datt(lsqr_handle* h, V*& datt)
     if (dalloc(&datt, h->sv.m) != LSQR_OK) g_last_error.clear();
 }
 
+// Whether A x takes its attitude part from the pass over the bucket order, once
+// that is there. Fewer than 2^19 rows, or windows of that pass of more than 64
+// bytes a row, gather: 2e5 rows 14 against 25 us (7,000 starts), 20 / 34 (1e5
+// starts); 1e6 rows and 1e6 starts (1,240 windows, 193 MB) 90 / 158. From there on
+// the pass is 10 us behind at worst and soon ahead (7,000 starts, FP64: 6e5 rows
+// 38 / 43 us, 3e6 169 / 160; FP32 values, FP64 vectors, 4e5 starts: 6e5 rows
+// 48 / 42, 3e6 154 / 122).
+inline bool aprod1_prepass(const lsqr_handle* h, int64_t vbytes)
+{
+    return h->att_ready && att_pass_on(h) && h->sv.m >= (1 << 19) &&
+           att_slices(h) * kAxes * att_span(h) * vbytes <= 64 * h->sv.m;
+}
+
 // y = A x as MODE says on stream st, for the operators and the refinement's
 // residual: once the attitude bucket order is there (an aprod2 or a solve has
-// built it) the attitude part comes from a pass over it, which gathers nothing
-// from memory: 1.5e7 rows, 1e5 starts 1.05 -> 0.84 ms. x3, datt: the handle's
+// built it) the attitude part of many rows comes from a pass over it, which gathers
+// nothing from memory: 1.5e7 rows, 1e5 starts 1.05 -> 0.84 ms. x3, datt: the handle's
 // scratch of the vector's type. Without memory for them the rows gather. So they
 // do while the stream is captured: nothing is allocated then, and a caller's
 // graph does not hold datt, which a solve short of memory frees.
@@ -2245,7 +2258,7 @@ lsqr_status run_aprod1(lsqr_handle* h, const V* x, VY* y, const double* b, doubl
     const V* datt = nullptr;
     const bool il = h->att_il && h->sv.natt > 0 && !h->generic;
     const bool staged = aprod1_staged(h, (int64_t)sizeof(V));
-    bool pre = il && h->att_ready && att_pass_on(h);
+    bool pre = il && aprod1_prepass(h, (int64_t)sizeof(V));
     bool make = il && !x3_raw && (pre || !staged);
     if ((pre || make) && captured(st)) pre = make = false;
     if (make && dalloc(&x3_raw, (int64_t)kAxes * h->sv.n_dfa) != LSQR_OK) g_last_error.clear();
