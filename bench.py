@@ -64,7 +64,8 @@ BYTES_PER_ROW_F32 = bytes_per_row(4, 4)  # the FP32 inner solve of the refinemen
 def one_pass(spec):
     """Whether the library's default options solve this system in one sweep per
     iteration: the FP64 histograms of the attitude and instrumental columns fit
-    in LDS together (LSQR_OPT_FUSED)."""
+    in LDS together (LSQR_OPT_FUSED; a few large systems keep three passes all
+    the same, none of the workloads here)."""
     return 3 * spec.n_dfa + spec.n_instr_cols <= 19456
 
 

@@ -183,7 +183,10 @@ lsqr_status lsqr_destroy(lsqr_handle* h);
  *                         3 n_dfa + n_instr_cols <= 19456 (the FP64 histograms
  *                         of both sections fit in LDS) instead do everything in
  *                         one sweep over A in row order (unless
- *                         LSQR_OPT_ATT_BUCKETS or LSQR_OPT_ASTRO_SCAN is set);
+ *                         LSQR_OPT_ATT_BUCKETS or LSQR_OPT_ASTRO_SCAN is set;
+ *                         solves keep three passes where the matrix is past the
+ *                         caches and the histograms leave the vector no room in
+ *                         LDS, if that is quicker);
  *                         3: as 2, but u~ stays in star order: the pre-pass
  *                         writes the attitude part to a separate bucket-order
  *                         vector (8 bytes per row, allocated on first use)

@@ -316,11 +316,11 @@ inline size_t one_pass_lds(const lsqr_handle* h, int64_t vbytes, int* win)
     return (size_t)std::max<int64_t>(lds, 16);
 }
 
-// Single-RHS row passes in one sweep over A: where the histograms of the
-// attitude and instrumental columns fit in LDS together, unless options ask
-// for another form (a bucket count asks for the bucket order, the segmented scan
-// for k_aprod2, which general layouts do not run).
-inline bool one_pass_on(const lsqr_handle* h)
+// Whether the row passes can be one sweep over A: the histograms of the attitude
+// and instrumental columns fit in LDS together, unless options ask for another
+// form (a bucket count asks for the bucket order, the segmented scan for k_aprod2,
+// which general layouts do not run).
+inline bool one_pass_fits(const lsqr_handle* h)
 {
     int win = 0;
     return h->fused == 2 && h->att_mode == 1 && h->att_buckets == 0 &&
@@ -329,14 +329,46 @@ inline bool one_pass_on(const lsqr_handle* h)
            one_pass_lds(h, 8, &win) > 0;
 }
 
-// Effective fused mode of a single-RHS iteration: 0 separate passes, 1 fused
-// pass with the attitude dot product, 2 attitude pre-pass + fused pass, 3 the
-// same with the row vector kept in star order, kOnePass one sweep for
+inline bool plain_on(const lsqr_handle* h);
+inline size_t fused_lds_plan(const lsqr_handle* h, int64_t K, int64_t vbytes, int64_t* hc,
+                             int* ldsx);
+
+// The single-RHS iterations with vectors of vbytes in one sweep: where that fits,
+// except where nothing of the vector fits beside the histograms, so that a row
+// gathers 12 attitude and 6 instrumental values from the caches, and the matrix
+// comes from memory: the bucket order, which gathers none, then costs only its
+// second read of the attitude coefficients. With FP64 values that second read is
+// 96 bytes a row, and the sweep stays ahead while the instrumental slice is within
+// 32 KB (L1) or too large for the bucket order's fused pass too: 1e7 rows, one
+// sweep against bucket order per iteration, (6,000 starts, 1,456 columns) 748
+// against 757 us, (200, 18,000) 797 / 887, (4,000, 4,500) 824 / 749. With FP32
+// values it is 48, and the sweep loses with FP64 vectors (615 / 492, 641 / 600,
+// 689 / 490) and past L1 with FP32 ones ((3,000, 10,000) 592 / 457; (6,000, 1,456)
+// 466 / 456). Up to kPlainBytes the sweep wins throughout: 1e6 rows 100 / 111,
+// 102 / 154, 105 / 108 in FP64, 79 / 91, 81 / 137, 83 / 92 in FP64 on FP32 values.
+inline bool one_pass_on(const lsqr_handle* h, int64_t vbytes)
+{
+    int win = 0;
+    if (!one_pass_fits(h)) return false;
+    (void)one_pass_lds(h, vbytes, &win);
+    if (win > 0 || !att_pass_on(h) || plain_on(h)) return true;
+    const bool l1 = h->sv.n_instr_cols * vbytes <= 32 * 1024;
+    if (h->value_type == LSQR_F32) return vbytes == 4 && l1;
+    int64_t hc = 0;
+    int ldsx = 0;
+    (void)fused_lds_plan(h, 1, vbytes, &hc, &ldsx);
+    return l1 || hc < h->sv.n_instr_cols;
+}
+
+// Effective fused mode of a single-RHS iteration with vectors of Acc: 0 separate
+// passes, 1 fused pass with the attitude dot product, 2 attitude pre-pass + fused
+// pass, 3 the same with the row vector kept in star order, kOnePass one sweep for
 // everything. General layouts run 2 (with an attitude section), one pass or 0.
 constexpr int kOnePass = 4;
+template <typename Acc>
 inline int fused_mode(const lsqr_handle* h)
 {
-    if (one_pass_on(h)) return kOnePass;
+    if (one_pass_on(h, (int64_t)sizeof(Acc))) return kOnePass;
     if (h->generic) return att_pass_on(h) && h->fused == 2 ? 2 : 0;
     return use_fused(h) ? h->fused : 0;
 }
@@ -344,7 +376,7 @@ inline int fused_mode(const lsqr_handle* h)
 // Fused mode 3 keeps the single-RHS row vector in star order: the star-order
 // pass reads and writes it sequentially, and the bucket-order passes reach it
 // (or the pre-pass's separate output) through the permutation, read-only.
-inline bool star_order_u(const lsqr_handle* h) { return fused_mode(h) == 3; }
+inline bool star_order_u(const lsqr_handle* h) { return use_fused(h) && h->fused == 3; }
 
 // k-tiles of K >= 2 after the attitude pre-pass run the fused pass (and the
 // first aprod2 of a solve) with the K right-hand sides of a row in K lanes
@@ -365,14 +397,15 @@ bool captured(hipStream_t st)
     return true;
 }
 
-// The form of lsqr_aprod2 (one pass or not): the iterations', but while the
-// caller's stream is captured one that has all it needs, if the iterations' has
-// not (a batched solve builds only the bucket order, options may have changed
-// since the last call, and without an attitude section separate passes need
-// nothing).
+// The form of lsqr_aprod2: one pass where it fits (it gathers nothing; 1e7 rows
+// 431 us in either form, 4e7 rows 1.85 against 1.73 ms in FP64, 1.20 against 1.10
+// in FP32, but the bucket order costs a sort and 106 or 58 bytes a row first). While
+// the caller's stream is captured, the form that has all it needs, if only one has
+// (a batched solve builds only the bucket order, options may have changed since
+// the last call, and without an attitude section separate passes need nothing).
 inline bool operator_one_pass(const lsqr_handle* h)
 {
-    const bool one = one_pass_on(h);
+    const bool one = one_pass_fits(h);
     const bool order = h->att_ready || !att_pass_on(h), slices = h->S1 != nullptr;
     if ((one ? slices : order) || !(one ? order : slices) || !captured(h->user_stream)) return one;
     return !one;
@@ -380,9 +413,10 @@ inline bool operator_one_pass(const lsqr_handle* h)
 
 // Placement of the single-RHS solver's row vector: bucket order in attitude
 // mode 1 (row i at u[invperm[i]]) except in fused mode 3 and in one pass.
+template <typename Acc>
 inline const int32_t* row_map(const lsqr_handle* h)
 {
-    const int mode = fused_mode(h);
+    const int mode = fused_mode<Acc>(h);
     return (att_pass_on(h) && mode != 3 && mode != kOnePass) ? h->invperm : nullptr;
 }
 
@@ -622,7 +656,7 @@ void launch_fused_as(const lsqr_handle* h, Path<Acc>& P, const Acc* x3, const Ga
                      hipStream_t st)
 {
     // kAttGather reads the pre-pass output through invperm; u~ is in star order
-    const int32_t* inv = AM == kAttGather ? (const int32_t*)h->invperm : row_map(h);
+    const int32_t* inv = AM == kAttGather ? (const int32_t*)h->invperm : row_map<Acc>(h);
     const Acc* datt = AM == kAttGather ? (const Acc*)P.datt : nullptr;
     by_flag(h->sv.star32 != nullptr, [&](auto cidx) {
         by_flag(AM == kAttPre && plain_on(h), [&](auto plain) {
@@ -741,7 +775,7 @@ void launch_fused(const lsqr_handle* h, Path<Acc>& P, const Gate& gate, hipStrea
     if (P.ustar)
         launch_instr_tail<T, Acc, 1, false>(h, P.ustar, nullptr, P.q, P.f_hcols, h->sc, st);
     else
-        launch_instr_tail<T, Acc, 1, false>(h, P.u, row_map(h), P.q, P.f_hcols, h->sc, st);
+        launch_instr_tail<T, Acc, 1, false>(h, P.u, row_map<Acc>(h), P.q, P.f_hcols, h->sc, st);
 }
 
 // Threads that share the G slices of one column: as many as it takes to fill
@@ -922,7 +956,7 @@ template <typename T, typename Acc>
 void launch_iteration(lsqr_handle* h, Path<Acc>& P, hipStream_t st, hipEvent_t* ev, bool pending)
 {
     const int64_t m = h->sv.m;
-    const int mode = fused_mode(h);
+    const int mode = fused_mode<Acc>(h);
     const bool gated = mode != 0;  // the first row pass makes the pending tests
     const Gate none = gate_of(h, false), gate = gate_of(h, gated && pending);
     SliceView att = kNoSlices, ins = kNoSlices;
@@ -960,12 +994,12 @@ void launch_iteration(lsqr_handle* h, Path<Acc>& P, hipStream_t st, hipEvent_t* 
         }
     } else {
         launch_aprod1<T, Acc, Acc, Acc, A1_LSQR>(
-            h, (const Acc*)P.vp, P.u, nullptr, h->sc, h->part1, st, row_map(h),
+            h, (const Acc*)P.vp, P.u, nullptr, h->sc, h->part1, st, row_map<Acc>(h),
             h->att_il && h->sv.natt > 0 ? (const Acc*)P.vp3 : nullptr);
         beta.npart = n_part(h, h->nb1);
         if (ev) (void)hipEventRecord(ev[1], st);
         if (ev) (void)hipEventRecord(ev[2], st);
-        launch_aprod2<T, Acc>(h, P.u, row_map(h), P.q, P.gpart, P.hcols, h->sc, st, P.u,
+        launch_aprod2<T, Acc>(h, P.u, row_map<Acc>(h), P.q, P.gpart, P.hcols, h->sc, st, P.u,
                               nullptr, false);
         glob.ng = 0;
     }
@@ -980,7 +1014,7 @@ void launch_chunk(lsqr_handle* h, Path<Acc>& P, hipStream_t st, hipEvent_t* ev, 
 {
     for (int k = 0; k < chunk; ++k)
         launch_iteration<T, Acc>(h, P, st, ev ? ev + kEvIter * k : nullptr, k > 0);
-    if (fused_mode(h) != 0)
+    if (fused_mode<Acc>(h) != 0)
         hipLaunchKernelGGL(k_scalar_stop, dim3(1), dim3(kBlock), 0, st, gate_of(h, true));
 }
 
@@ -993,8 +1027,9 @@ void launch_init(lsqr_handle* h, Path<Acc>& P, int npart, hipStream_t st)
     hipLaunchKernelGGL(k_scalar_init_beta, dim3(1), dim3(kBlock), 0, st, h->part1, npart, h->sc);
     hipLaunchKernelGGL((k_fill<Acc>), dim3(h->nbc), dim3(kBlock), 0, st, n, P.q, (Acc)0);
     hipLaunchKernelGGL((k_fill<double>), dim3(h->nbc), dim3(kBlock), 0, st, n, h->v, 0.0);
-    launch_aprod2<T, Acc>(h, P.u, row_map(h), P.q, P.gpart, P.hcols, h->sc, st, P.u,
-                          star_order_u(h) ? (const int32_t*)h->perm : nullptr, one_pass_on(h));
+    launch_aprod2<T, Acc>(h, P.u, row_map<Acc>(h), P.q, P.gpart, P.hcols, h->sc, st, P.u,
+                          star_order_u(h) ? (const int32_t*)h->perm : nullptr,
+                          fused_mode<Acc>(h) == kOnePass);
     GlobView glob = glob_view(h, P.gpart, 0, 1);
     glob.ng = 0;  // launch_aprod2 has added every section
     const int grid = column_grid(h, n, kNoSlices, kNoSlices);
@@ -1084,7 +1119,7 @@ lsqr_status prepare_path(lsqr_handle* h, Path<Acc>& P)
     // a fused pass that places u~ through the permutation and leaves
     // instrumental tail windows: a star-order copy of u~ for the tails (an
     // optimisation only: without the memory they read u~ through invperm)
-    if (!P.ustar && !P.ustar_tried && fused_mode(h) > 0 && row_map(h) && h->sv.ni > 0 &&
+    if (!P.ustar && !P.ustar_tried && fused_mode<Acc>(h) > 0 && row_map<Acc>(h) && h->sv.ni > 0 &&
         P.f_hcols < h->sv.n_instr_cols) {
         P.ustar_tried = true;
         if (dalloc_solver(h, &P.ustar, h->sv.m) != LSQR_OK) g_last_error.clear();
@@ -1235,7 +1270,8 @@ constexpr int64_t kCompactMemFraction = 32;
 lsqr_status ensure_compact(lsqr_handle* h)
 {
     // general layouts: where the single-RHS fused passes serve them
-    if (!h->compact || h->compact_tried || (h->generic && fused_mode(h) == 0)) return LSQR_OK;
+    if (!h->compact || h->compact_tried || (h->generic && fused_mode<double>(h) == 0))
+        return LSQR_OK;
     h->compact_tried = 1;
     const int64_t m = h->sv.m;
     if (h->sv.n_stars > INT32_MAX || h->sv.n_instr_cols > 65536) return LSQR_OK;
@@ -1331,7 +1367,8 @@ int iterations_left(const Scalars& a, const Scalars& b, int cap)
 template <typename T, typename Acc>
 lsqr_status run_iterations(lsqr_handle* h, Path<Acc>& P)
 {
-    h->last_mode = fused_mode(h) == kOnePass ? 2 : fused_mode(h);  // the option's mode
+    const int mode = fused_mode<Acc>(h);
+    h->last_mode = mode == kOnePass ? 2 : mode;  // the option's mode
     const int chunk = std::max(1, h->chunk);
     const bool graph = h->use_graph && !h->profile;
     if (graph && (P.graph == nullptr || P.graph_chunk != chunk)) {
@@ -1412,7 +1449,7 @@ template <typename T>
 lsqr_status solve_fp64(lsqr_handle* h, const double* b, double* x, int32_t itn_limit, double atol,
                        double btol, lsqr_info* info)
 {
-    LSQR_TRY(ensure_row_order(h, one_pass_on(h)));
+    LSQR_TRY(ensure_row_order(h, fused_mode<double>(h) == kOnePass));
     LSQR_TRY(ensure_compact(h));
     LSQR_TRY((prepare_path<T, double>(h, h->p64)));
     Path<double>& P = h->p64;
@@ -1429,7 +1466,7 @@ lsqr_status solve_fp64(lsqr_handle* h, const double* b, double* x, int32_t itn_l
                            0.0);
     }
     hipLaunchKernelGGL((k_copy_ssq<double>), dim3(h->nbr), dim3(kBlock), 0, h->stream, m, b, P.u,
-                       h->part1, row_map(h));
+                       h->part1, row_map<double>(h));
     if (h->nc > 0)  // constraint rows: after the observation rows, one partial
         hipLaunchKernelGGL((k_copy_ssq<double>), dim3(1), dim3(kBlock), 0, h->stream, h->nc, b + m,
                            P.u + m, h->part1 + h->nbr, (const int32_t*)nullptr);
@@ -2833,7 +2870,7 @@ lsqr_status lsqr_solve_refined(lsqr_handle* h, const double* b, double* x, int32
     if (!(atol >= 0.0) || !(btol >= 0.0)) return fail(LSQR_E_INVALID, "atol, btol must be >= 0");
     HIP_TRY(hipStreamSynchronize(h->user_stream));
     h->var_valid = 0;
-    LSQR_TRY(ensure_row_order(h, one_pass_on(h)));
+    LSQR_TRY(ensure_row_order(h, fused_mode<float>(h) == kOnePass));
     LSQR_TRY(ensure_compact(h));
     LSQR_TRY((prepare_path<float, float>(h, h->p32)));
     Path<float>& P = h->p32;
@@ -2857,14 +2894,14 @@ lsqr_status lsqr_solve_refined(lsqr_handle* h, const double* b, double* x, int32
         // (b itself at the first step, where x = 0)
         if (outer == 1) {
             hipLaunchKernelGGL((k_copy_ssq<float>), dim3(h->nbr), dim3(kBlock), 0, h->stream,
-                               h->sv.m, b, P.u, h->part1, row_map(h));
+                               h->sv.m, b, P.u, h->part1, row_map<float>(h));
             if (h->nc > 0)
                 hipLaunchKernelGGL((k_copy_ssq<float>), dim3(1), dim3(kBlock), 0, h->stream,
                                    h->nc, b + h->sv.m, P.u + h->sv.m, h->part1 + h->nbr,
                                    (const int32_t*)nullptr);
         } else {
             LSQR_TRY((run_aprod1<float, double, float, A1_RESID>(
-                h, (const double*)x, P.u, b, h->part1, row_map(h), h->x3_raw, h->datt_raw,
+                h, (const double*)x, P.u, b, h->part1, row_map<float>(h), h->x3_raw, h->datt_raw,
                 h->stream)));
         }
         launch_init<float, float>(h, P, n_part(h, outer == 1 ? h->nbr : h->nb1), h->stream);

@@ -305,3 +305,52 @@ def test_astro_scan_is_honoured(torch_cuda):
     assert np.array_equal(got[0], got[1])
     want = o.aprod2(y, np.zeros(o.n))[:sp.n_astro * sp.n_stars]
     assert rel_inf(got[0], want) <= 1e-12
+
+
+# Systems whose histograms fit in LDS but nothing of the vector beside them, with
+# the matrix past the last-level cache: the bucket order is quicker for FP64
+# vectors (attitude pre-pass: a window of its own in the profile), the sweep for
+# the refined solve's FP32 vectors, whose instrumental slice fits. Either way the
+# iterates of the other fused mode, to 1e-10, and A^T y adjoint to A x.
+@pytest.mark.parametrize("f32", [False, True], ids=["f64", "f32"])
+def test_large_systems_without_windows(torch_cuda, f32):
+    torch = torch_cuda
+    from paper_2308_00778_amd import LsqrSystem
+
+    spec = synth.tiny(seed=37, n_stars=28001 if f32 else 16001, obs=(75, 125), n_dfa=4000,
+                      n_instr_cols=4500, value_dtype="f32" if f32 else "f64")
+    arrays, first = synth.device_system(spec, "cuda:0")
+    m = int(first[-1])
+    say(f"no windows: m={m} f32={f32}")
+    assert m * (128 if f32 else 224) > 320 << 20
+    kw = dict(n_stars=spec.n_stars, n_dfa=spec.n_dfa, n_instr_cols=spec.n_instr_cols)
+    b = synth.device_noise(spec, m, 0, "cuda:0")
+    xs = []
+    for fused in (2, 1):
+        g = LsqrSystem(**arrays, **kw)
+        g.set_option("tests", 0)
+        g.set_option("fused", fused)
+        g.set_option("profile", 1)
+        x, info = g.solve(b, 6, atol=0.0, btol=0.0)
+        assert info.itn == 6
+        pre, n = g.pass_times()["pre"]
+        say(f"  fused={fused}: pre-pass window {1e3 * pre / n:.1f} us")
+        assert (pre / n > 0.015) == (fused == 2)
+        xs.append(x.cpu().numpy())
+        if f32 and fused == 2:
+            xr, _ = g.solve_refined(b, 6, 0.0, 0.0, 1)
+            pre, n = g.pass_times()["pre"]
+            say(f"  refined: pre-pass window {1e3 * pre / n:.1f} us")
+            assert pre / n < 0.015
+            assert rel_inf(xr.cpu().numpy(), xs[0]) <= 1e-3  # one FP32 inner solve
+        if fused == 2:
+            gen = torch.Generator(device="cuda").manual_seed(3)
+            u = torch.randn(g.n, generator=gen, device="cuda", dtype=torch.float64)
+            w = torch.randn(m, generator=gen, device="cuda", dtype=torch.float64)
+            au = g.aprod1(u, torch.zeros(m, dtype=torch.float64, device="cuda"))
+            aw = g.aprod2(torch.zeros(g.n, dtype=torch.float64, device="cuda"), w)
+            torch.cuda.synchronize()
+            lhs, rhs = float(au @ w), float(u @ aw)
+            assert abs(lhs - rhs) <= 1e-12 * float(au.norm() * w.norm())
+        g.close()
+    assert rel_inf(xs[0], xs[1]) <= 1e-10
