@@ -344,8 +344,10 @@ inline size_t fused_lds_plan(const lsqr_handle* h, int64_t K, int64_t vbytes, in
 // against 757 us, (200, 18,000) 797 / 887, (4,000, 4,500) 824 / 749. With FP32
 // values it is 48, and the sweep loses with FP64 vectors (615 / 492, 641 / 600,
 // 689 / 490) and past L1 with FP32 ones ((3,000, 10,000) 592 / 457; (6,000, 1,456)
-// 466 / 456). Up to kPlainBytes the sweep wins throughout: 1e6 rows 100 / 111,
-// 102 / 154, 105 / 108 in FP64, 79 / 91, 81 / 137, 83 / 92 in FP64 on FP32 values.
+// 466 / 456). At 1e6 rows the sweep wins throughout (100 / 111, 102 / 154, 105 / 108
+// in FP64, 79 / 91, 81 / 137, 83 / 92 in FP64 on FP32 values); kPlainBytes is the
+// line since the matrix then comes from memory, 20% late for FP64 on FP32 values
+// (2e6 rows 150 / 126).
 inline bool one_pass_on(const lsqr_handle* h, int64_t vbytes)
 {
     int win = 0;
