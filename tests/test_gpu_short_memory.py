@@ -2,6 +2,8 @@
 the handle is given up for it (1e8 rows, FP32 values: 800 MB of scratch; all but
 about 500 MB of the rest of the memory is taken).
 """
+import contextlib
+
 import pytest
 
 import synth
@@ -46,13 +48,20 @@ def test_solve_takes_the_operators_scratch(torch_cuda):
         g.aprod1(want, y)
         torch.cuda.synchronize()
         assert free0 - torch.cuda.mem_get_info()[0] >= 8 * m  # the scratch
-        for _ in range(4):  # the free memory reported may hold a reserve
-            free = torch.cuda.mem_get_info()[0]
-            if free < 600 << 20:
-                break
-            hogs.append(torch.empty(free - (500 << 20), dtype=torch.uint8, device="cuda"))
-        say(f"  {torch.cuda.mem_get_info()[0] / 1e6:.0f} MB free")
-        assert torch.cuda.mem_get_info()[0] < 8 * m
+        # all of the memory in blocks, then four of 128 MB given back
+        for size in (8 << 30, 1 << 30, 128 << 20):
+            if size == 128 << 20:
+                del hogs[-1]
+                torch.cuda.empty_cache()
+            with contextlib.suppress(torch.cuda.OutOfMemoryError):
+                while True:
+                    hogs.append(torch.empty(size, dtype=torch.uint8, device="cuda"))
+        assert hogs[-4].numel() == 128 << 20
+        del hogs[-4:]
+        torch.cuda.empty_cache()
+        say(f"  {torch.cuda.mem_get_info()[0] / 1e6:.0f} MB reported free")
+        with pytest.raises(torch.cuda.OutOfMemoryError):
+            torch.empty(m, dtype=torch.float64, device="cuda")
         # row-order u~: a vector of m values more
         g.set_option("fused", 3)
         x = torch.empty_like(want)
